@@ -6,9 +6,8 @@
 // activations, FP32 accumulation.  Flat weight layout: W1[o][c][ky][kx]
 // (offset 0), W2[o][c][ky][kx] (offset 288), W3[c][ky][kx] (offset 2592).
 //
-// Training (forward with stored activations, backward, weight gradients,
-// Adam) runs on per-layer VALU kernels; inference inside LOBPCG runs on one
-// fused kernel per 28x28 output tile that keeps the whole receptive field in
+// Training (loss and weight gradient) is in net_train.hip, Adam here;
+// inference inside LOBPCG runs on one fused kernel per 28x28 output tile that keeps the whole receptive field in
 // LDS and does the three convolutions as implicit GEMMs on bf16 MFMA
 // (v_mfma_f32_16x16x16bf16_1k: 16 output channels x 16 pixels per
 // instruction; layer 3 as 9 per-tap 1x1 products summed over the taps).
@@ -21,7 +20,7 @@ namespace gsf {
 
 int vec_blocks(int64_t n);
 
-constexpr int kOffW1 = 0, kOffW2 = 288, kOffW3 = 2592, kNetWeights = 2736;
+constexpr int kOffW1 = 0, kOffW2 = 288, kOffW3 = 2592;
 
 namespace {
 
@@ -58,299 +57,8 @@ __device__ __forceinline__ bool inside(int64_t y, int64_t x, int64_t rows, int64
 }
 
 // ---------------------------------------------------------------------------
-// training kernels (one thread per pixel of the batch)
+// optimiser (the training pass is in net_train.hip)
 // ---------------------------------------------------------------------------
-struct NetTrainArgs {
-  const float* wf;        // BF16-rounded weights as FP32
-  const int32_t* idx;     // sample of each batch position
-  int batch;
-  int64_t rows, cols, hw;
-  const float* inputs;    // [sample][hw][2]
-  const float* targets;   // [sample][hw] (nullptr: forward only)
-  uint16_t* a1;           // [b][hw][16]
-  uint16_t* a2;           // [b][hw][16]
-  float* y;               // [b][hw]
-  float* dy;              // [b][hw]
-  float* dz2;             // [b][hw][16]
-  float* dz1;             // [b][hw][16]
-  double* loss_part;      // one per workgroup
-  float dscale;           // 2 / (batch * hw)
-};
-
-__global__ void __launch_bounds__(kThreads) net_round_weights_kernel(const uint16_t* __restrict__ w,
-                                                                     float* __restrict__ wf) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kNetWeights; i += gridDim.x * blockDim.x)
-    wf[i] = bf2f(w[i]);
-}
-
-__device__ __forceinline__ void load16_bf(const uint16_t* p, float (&v)[16]) {
-  const uint4 a = *(const uint4*)p, b = *(const uint4*)(p + 8);
-  const uint32_t u[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    v[2 * k] = bf2f(u[k] & 0xffffu);
-    v[2 * k + 1] = bf2f(u[k] >> 16);
-  }
-}
-
-__device__ __forceinline__ void store16_relu_bf(uint16_t* p, const float (&v)[16]) {
-  uint32_t u[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    u[k] = f2bf(relu(v[2 * k])) | (f2bf(relu(v[2 * k + 1])) << 16);
-  *(uint4*)p = make_uint4(u[0], u[1], u[2], u[3]);
-  *(uint4*)(p + 8) = make_uint4(u[4], u[5], u[6], u[7]);
-}
-
-__global__ void __launch_bounds__(kThreads) net_fwd1_kernel(NetTrainArgs a) {
-  const int64_t total = (int64_t)a.batch * a.hw;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-    const int64_t b = t / a.hw, p = t - b * a.hw;
-    const int64_t py = p / a.cols, px = p - py * a.cols;
-    const float* in = a.inputs + (size_t)a.idx[b] * a.hw * 2;
-    float acc[16];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) acc[o] = 0.0f;
-#pragma unroll 1
-    for (int tap = 0; tap < 9; ++tap) {
-      const int64_t gy = py + tap / 3 - 1, gx = px + tap % 3 - 1;
-      float x0 = 0.0f, x1 = 0.0f;
-      if (inside(gy, gx, a.rows, a.cols)) {
-        const float2 v = *(const float2*)(in + (gy * a.cols + gx) * 2);
-        x0 = rbf(v.x);
-        x1 = rbf(v.y);
-      }
-#pragma unroll
-      for (int o = 0; o < 16; ++o) {
-        acc[o] = fmaf(a.wf[kOffW1 + o * 18 + tap], x0, acc[o]);
-        acc[o] = fmaf(a.wf[kOffW1 + o * 18 + 9 + tap], x1, acc[o]);
-      }
-    }
-    store16_relu_bf(a.a1 + t * 16, acc);
-  }
-}
-
-__global__ void __launch_bounds__(kThreads) net_fwd2_kernel(NetTrainArgs a) {
-  const int64_t total = (int64_t)a.batch * a.hw;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-    const int64_t b = t / a.hw, p = t - b * a.hw;
-    const int64_t py = p / a.cols, px = p - py * a.cols;
-    float acc[16];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) acc[o] = 0.0f;
-    for (int tap = 0; tap < 9; ++tap) {
-      const int64_t gy = py + tap / 3 - 1, gx = px + tap % 3 - 1;
-      if (!inside(gy, gx, a.rows, a.cols)) continue;
-      float v[16];
-      load16_bf(a.a1 + (b * a.hw + gy * a.cols + gx) * 16, v);
-#pragma unroll
-      for (int c = 0; c < 16; ++c)
-#pragma unroll
-        for (int o = 0; o < 16; ++o) acc[o] = fmaf(a.wf[kOffW2 + o * 144 + c * 9 + tap], v[c], acc[o]);
-    }
-    store16_relu_bf(a.a2 + t * 16, acc);
-  }
-}
-
-// y = conv(a2; W3); with targets also dy = dscale (y - t) and the loss partials.
-__global__ void __launch_bounds__(kThreads) net_fwd3_kernel(NetTrainArgs a) {
-  __shared__ double red[16];
-  const int64_t total = (int64_t)a.batch * a.hw;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  double v[1] = {0.0};
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-    const int64_t b = t / a.hw, p = t - b * a.hw;
-    const int64_t py = p / a.cols, px = p - py * a.cols;
-    float acc = 0.0f;
-    for (int tap = 0; tap < 9; ++tap) {
-      const int64_t gy = py + tap / 3 - 1, gx = px + tap % 3 - 1;
-      if (!inside(gy, gx, a.rows, a.cols)) continue;
-      float x[16];
-      load16_bf(a.a2 + (b * a.hw + gy * a.cols + gx) * 16, x);
-#pragma unroll
-      for (int c = 0; c < 16; ++c) acc = fmaf(a.wf[kOffW3 + c * 9 + tap], x[c], acc);
-    }
-    a.y[t] = acc;
-    if (a.targets != nullptr) {
-      const float e = acc - a.targets[(size_t)a.idx[b] * a.hw + p];
-      a.dy[t] = a.dscale * e;
-      v[0] += (double)e * (double)e;
-    }
-  }
-  if (a.targets == nullptr) return;
-  block_sum<1>(v, red);
-  if (threadIdx.x == 0) a.loss_part[blockIdx.x] = v[0];
-}
-
-// dz2[q][c] = [a2[q][c] > 0] sum_tap W3[c][tap] dy[q - off(tap)]
-__global__ void __launch_bounds__(kThreads) net_bwd3_kernel(NetTrainArgs a) {
-  const int64_t total = (int64_t)a.batch * a.hw;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-    const int64_t b = t / a.hw, p = t - b * a.hw;
-    const int64_t py = p / a.cols, px = p - py * a.cols;
-    float acc[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] = 0.0f;
-#pragma unroll 1
-    for (int tap = 0; tap < 9; ++tap) {
-      const int64_t gy = py - (tap / 3 - 1), gx = px - (tap % 3 - 1);
-      if (!inside(gy, gx, a.rows, a.cols)) continue;
-      const float d = a.dy[b * a.hw + gy * a.cols + gx];
-#pragma unroll
-      for (int c = 0; c < 16; ++c) acc[c] = fmaf(a.wf[kOffW3 + c * 9 + tap], d, acc[c]);
-    }
-    float act[16];
-    load16_bf(a.a2 + t * 16, act);
-    float4* out = (float4*)(a.dz2 + t * 16);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      out[k] = make_float4(act[4 * k] > 0.0f ? acc[4 * k] : 0.0f, act[4 * k + 1] > 0.0f ? acc[4 * k + 1] : 0.0f,
-                           act[4 * k + 2] > 0.0f ? acc[4 * k + 2] : 0.0f,
-                           act[4 * k + 3] > 0.0f ? acc[4 * k + 3] : 0.0f);
-  }
-}
-
-// dz1[q][c] = [a1[q][c] > 0] sum_tap sum_o W2[o][c][tap] dz2[q - off(tap)][o]
-__global__ void __launch_bounds__(kThreads) net_bwd2_kernel(NetTrainArgs a) {
-  const int64_t total = (int64_t)a.batch * a.hw;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-    const int64_t b = t / a.hw, p = t - b * a.hw;
-    const int64_t py = p / a.cols, px = p - py * a.cols;
-    float acc[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] = 0.0f;
-    for (int tap = 0; tap < 9; ++tap) {
-      const int64_t gy = py - (tap / 3 - 1), gx = px - (tap % 3 - 1);
-      if (!inside(gy, gx, a.rows, a.cols)) continue;
-      const float4* d4 = (const float4*)(a.dz2 + (b * a.hw + gy * a.cols + gx) * 16);
-      float d[16];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float4 q = d4[k];
-        d[4 * k] = q.x;
-        d[4 * k + 1] = q.y;
-        d[4 * k + 2] = q.z;
-        d[4 * k + 3] = q.w;
-      }
-#pragma unroll
-      for (int o = 0; o < 16; ++o)
-#pragma unroll
-        for (int c = 0; c < 16; ++c) acc[c] = fmaf(a.wf[kOffW2 + o * 144 + c * 9 + tap], d[o], acc[c]);
-    }
-    float act[16];
-    load16_bf(a.a1 + t * 16, act);
-    float4* out = (float4*)(a.dz1 + t * 16);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      out[k] = make_float4(act[4 * k] > 0.0f ? acc[4 * k] : 0.0f, act[4 * k + 1] > 0.0f ? acc[4 * k + 1] : 0.0f,
-                           act[4 * k + 2] > 0.0f ? acc[4 * k + 2] : 0.0f,
-                           act[4 * k + 3] > 0.0f ? acc[4 * k + 3] : 0.0f);
-  }
-}
-
-// Weight gradient of one layer, dW[o][c][tap] = sum_p dz[p][o] act[p + off(tap)][c],
-// over 16x16 pixel tiles (grid-stride over batch x tiles).  Each thread owns
-// one (o, c) pair and a fixed subset of the tile's pixels; per tile the sums
-// are FP32, across tiles FP64; the per-workgroup partials are reduced later
-// in workgroup order.
-template <int LAYER>
-__global__ void __launch_bounds__(kThreads) net_wgrad_kernel(NetTrainArgs a, int tiles_x, int tiles_per_sample,
-                                                             double* __restrict__ partials) {
-  constexpr int CIN = LAYER == 1 ? 2 : 16, COUT = LAYER == 3 ? 1 : 16;
-  constexpr int P = CIN * COUT, S = kThreads / P;
-  __shared__ float acts[18 * 18 * CIN];
-  __shared__ float dzs[256 * COUT];
-  __shared__ double red[kThreads * 9];
-  const int tid = threadIdx.x, pair = tid % P, sub = tid / P;
-  const int o = pair / CIN, c = pair - (pair / CIN) * CIN;
-  double accd[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) accd[k] = 0.0;
-  const int64_t ntiles = (int64_t)a.batch * tiles_per_sample;
-  for (int64_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-    const int64_t b = tt / tiles_per_sample;
-    const int tl = (int)(tt - b * tiles_per_sample);
-    const int64_t ty = (tl / tiles_x) * 16, tx = (tl % tiles_x) * 16;
-    __syncthreads();
-    for (int e = tid; e < 18 * 18; e += kThreads) {
-      const int64_t gy = ty - 1 + e / 18, gx = tx - 1 + e % 18;
-      const bool in = inside(gy, gx, a.rows, a.cols);
-      const int64_t q = gy * a.cols + gx;
-      if constexpr (LAYER == 1) {
-        float2 v = make_float2(0.0f, 0.0f);
-        if (in) v = *(const float2*)(a.inputs + ((size_t)a.idx[b] * a.hw + q) * 2);
-        acts[e * 2] = rbf(v.x);
-        acts[e * 2 + 1] = rbf(v.y);
-      } else {
-        float v[16];
-        if (in) {
-          load16_bf((LAYER == 2 ? a.a1 : a.a2) + (b * a.hw + q) * 16, v);
-        } else {
-#pragma unroll
-          for (int k = 0; k < 16; ++k) v[k] = 0.0f;
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) acts[e * 16 + k] = v[k];
-      }
-    }
-    for (int e = tid; e < 256 * COUT; e += kThreads) {
-      const int px = e / COUT, oo = e - (e / COUT) * COUT;
-      const int64_t gy = ty + px / 16, gx = tx + px % 16;
-      float v = 0.0f;
-      if (inside(gy, gx, a.rows, a.cols)) {
-        const int64_t q = b * a.hw + gy * a.cols + gx;
-        v = LAYER == 3 ? a.dy[q] : (LAYER == 2 ? a.dz2[q * 16 + oo] : a.dz1[q * 16 + oo]);
-      }
-      dzs[e] = v;
-    }
-    __syncthreads();
-    float acc[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) acc[k] = 0.0f;
-    for (int px = sub; px < 256; px += S) {
-      const float d = dzs[px * COUT + o];
-      const int ly = px >> 4, lx = px & 15;
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap)
-        acc[tap] = fmaf(d, acts[((ly + tap / 3) * 18 + lx + tap % 3) * CIN + c], acc[tap]);
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) accd[k] += (double)acc[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 9; ++k) red[tid * 9 + k] = accd[k];
-  __syncthreads();
-  if (tid < P) {
-    for (int k = 0; k < 9; ++k) {
-      double s = 0.0;
-      for (int q = 0; q < S; ++q) s += red[(q * P + tid) * 9 + k];
-      partials[((size_t)blockIdx.x * P + tid) * 9 + k] = s;
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kThreads) net_wgrad_reduce_kernel(const double* __restrict__ partials, int nparts,
-                                                                    int nw, float* __restrict__ grad) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nw) return;
-  double s = 0.0;
-  for (int g = 0; g < nparts; ++g) s += partials[(size_t)g * nw + w];
-  grad[w] = (float)s;
-}
-
-__global__ void __launch_bounds__(kThreads) net_loss_final_kernel(const double* __restrict__ partials, int nparts,
-                                                                  double inv_count, double* __restrict__ loss) {
-  __shared__ double red[16];
-  double t[1];
-  reduce_partials<1>(partials, nparts, 1, t, red);
-  if (threadIdx.x == 0) *loss = t[0] * inv_count;
-}
-
 __global__ void __launch_bounds__(kThreads) net_adam_kernel(int64_t count, float b1, float b2, float eps,
                                                             float step, float bc1, float bc2, float* __restrict__ w,
                                                             float* __restrict__ mom, float* __restrict__ vel,
@@ -777,97 +485,10 @@ __global__ void __launch_bounds__(kThreads) scg_shift_kernel(const T* __restrict
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-size_t net_train_bytes(int batch, int64_t hw) {
-  const size_t px = (size_t)batch * (size_t)hw;
-  const size_t wg = (size_t)1024 * kNetWeights;  // wgrad partials (at most 1024 workgroups per layer)
-  return align_up(kNetWeights * 4, 256) + 2 * align_up(px * 32, 256) + 2 * align_up(px * 4, 256) +
-         2 * align_up(px * 64, 256) + align_up(1024 * 8, 256) + align_up(wg * 8, 256);
-}
-
-struct NetTrainWs {
-  float* wf;
-  uint16_t *a1, *a2;
-  float *y, *dy, *dz2, *dz1;
-  double *loss_part, *wpart;
-};
-
-static NetTrainWs carve_train(void* ws, int batch, int64_t hw) {
-  const size_t px = (size_t)batch * (size_t)hw;
-  char* p = (char*)ws;
-  NetTrainWs w;
-  w.wf = (float*)p;
-  p += align_up(kNetWeights * 4, 256);
-  w.a1 = (uint16_t*)p;
-  p += align_up(px * 32, 256);
-  w.a2 = (uint16_t*)p;
-  p += align_up(px * 32, 256);
-  w.y = (float*)p;
-  p += align_up(px * 4, 256);
-  w.dy = (float*)p;
-  p += align_up(px * 4, 256);
-  w.dz2 = (float*)p;
-  p += align_up(px * 64, 256);
-  w.dz1 = (float*)p;
-  p += align_up(px * 64, 256);
-  w.loss_part = (double*)p;
-  p += align_up(1024 * 8, 256);
-  w.wpart = (double*)p;
-  return w;
-}
-
 static int px_blocks(int64_t total) {
   int64_t b = (total + kThreads - 1) / kThreads;
   if (b > 4096) b = 4096;
   return (int)(b < 1 ? 1 : b);
-}
-
-gsf_status net_forward_train(const uint16_t* w, int batch, const int32_t* idx, int64_t rows, int64_t cols,
-                             const float* inputs, const float* targets, float* y_out, float* grad, double* loss,
-                             void* ws, hipStream_t s) {
-  const int64_t hw = rows * cols;
-  NetTrainWs t = carve_train(ws, batch, hw);
-  NetTrainArgs a{};
-  a.wf = t.wf;
-  a.idx = idx;
-  a.batch = batch;
-  a.rows = rows;
-  a.cols = cols;
-  a.hw = hw;
-  a.inputs = inputs;
-  a.targets = targets;
-  a.a1 = t.a1;
-  a.a2 = t.a2;
-  a.y = y_out != nullptr ? y_out : t.y;
-  a.dy = t.dy;
-  a.dz2 = t.dz2;
-  a.dz1 = t.dz1;
-  a.loss_part = t.loss_part;
-  a.dscale = (float)(2.0 / ((double)batch * (double)hw));
-  const int nb = px_blocks((int64_t)batch * hw);
-  const int nbl = nb < 1024 ? nb : 1024;
-  net_round_weights_kernel<<<(kNetWeights + kThreads - 1) / kThreads, kThreads, 0, s>>>(w, t.wf);
-  net_fwd1_kernel<<<nb, kThreads, 0, s>>>(a);
-  net_fwd2_kernel<<<nb, kThreads, 0, s>>>(a);
-  net_fwd3_kernel<<<targets != nullptr ? nbl : nb, kThreads, 0, s>>>(a);
-  if (targets == nullptr) return launch_status();
-  net_loss_final_kernel<<<1, kThreads, 0, s>>>(t.loss_part, nbl, 1.0 / ((double)batch * (double)hw), loss);
-  net_bwd3_kernel<<<nb, kThreads, 0, s>>>(a);
-  net_bwd2_kernel<<<nb, kThreads, 0, s>>>(a);
-  const int tiles_x = (int)((cols + 15) / 16), tiles_y = (int)((rows + 15) / 16);
-  const int tps = tiles_x * tiles_y;
-  const int64_t ntiles = (int64_t)batch * tps;
-  const int gw = (int)(ntiles < 1024 ? ntiles : 1024);
-  double* p1 = t.wpart;
-  double* p2 = p1 + (size_t)gw * kOffW2;
-  double* p3 = p2 + (size_t)gw * (kOffW3 - kOffW2);
-  net_wgrad_kernel<1><<<gw, kThreads, 0, s>>>(a, tiles_x, tps, p1);
-  net_wgrad_kernel<2><<<gw, kThreads, 0, s>>>(a, tiles_x, tps, p2);
-  net_wgrad_kernel<3><<<gw, kThreads, 0, s>>>(a, tiles_x, tps, p3);
-  net_wgrad_reduce_kernel<<<(kOffW2 + kThreads - 1) / kThreads, kThreads, 0, s>>>(p1, gw, kOffW2, grad + kOffW1);
-  net_wgrad_reduce_kernel<<<(kOffW3 - kOffW2 + kThreads - 1) / kThreads, kThreads, 0, s>>>(p2, gw, kOffW3 - kOffW2,
-                                                                                        grad + kOffW2);
-  net_wgrad_reduce_kernel<<<1, kThreads, 0, s>>>(p3, gw, kNetWeights - kOffW3, grad + kOffW3);
-  return launch_status();
 }
 
 gsf_status net_adam(int64_t count, int t, double lr, double b1, double b2, double eps, float* w, float* mom,

@@ -459,3 +459,32 @@ def test_learned_precond_cuts_lobpcg_steps(gsf, trained):
     assert res["learned"][3] == gsf.OK
     assert 1.5 * res["learned"][0] <= res["plain"][0]
     assert res["learned"][1] < res["plain"][1]
+
+
+@pytest.mark.parametrize("shape,B", [((1, 1), 1), ((16, 32), 1), ((17, 33), 2), ((15, 31), 3), ((26, 42), 1),
+                                     ((1, 97), 2), ((70, 1), 2), ((48, 96), 5), ((200, 130), 6)])
+def test_net_training_tiles(gsf, shape, B):
+    """Loss, gradient and outputs where the 32 x 16 tiles of the training pass
+    begin and end: single pixels, whole tiles, one pixel more or less, the
+    5-pixel halo, single rows and columns, more tiles than workgroups (the
+    tolerances of the module docstring; a single pixel's gradient has a few
+    hundred non-zero terms, the same bound)."""
+    import torch
+    H, W = shape
+    rng = np.random.default_rng(40)
+    r, t = rng.standard_normal((B, H, W)), rng.standard_normal((B, H, W)) * 3.0
+    g = rng.uniform(0.0, 1.0, (B, H, W))
+    w = convnet_init(41)
+    inp, tg = _train_arrays(r, g, t)
+    tr = gsf.NetTrainer(w, B, H, W)
+    idx = _dev(np.arange(B, dtype=np.int32), torch.int32)
+    loss, grad = tr.loss_grad(idx, inp, tg)
+    y = tr.forward(idx, inp).cpu().numpy().reshape(B, H, W)
+    f32 = lambda a: a.astype(np.float32).astype(np.float64)
+    ref_loss, ref_grad = cn.loss_and_grad(w.astype(np.float64), f32(r), f32(t), f32(g))
+    ref_y = np.stack([cn.forward(w.astype(np.float64), f32(r[b]), f32(g[b]))["y"] for b in range(B)])
+    assert nrel(y, ref_y) <= NET_TOL
+    assert abs(float(loss.cpu()[0]) - ref_loss) <= NET_TOL * ref_loss
+    assert nrel(grad.cpu().numpy(), ref_grad) <= NET_TOL
+    again_loss, again = tr.loss_grad(idx, inp, tg)
+    assert torch.equal(again, grad) and torch.equal(again_loss, loss)  # fixed-order sums
