@@ -13,15 +13,16 @@
 //   gram_reduce /  fixed-order two-level reduction of the tiles (one level,
 //   gram_rr        inside gram_rr, with at most 16 Gram workgroups), then the
 //                  Rayleigh-Ritz step on one workgroup in FP64: unit-diagonal
-//                  scaling, column-dropping Cholesky, reduction to
-//                  L^-1 A L^-T, the m smallest eigenpairs (Householder
-//                  tridiagonalisation, bisection, inverse iteration), m
-//                  smallest Ritz pairs; extra workgroups of both launches run
-//                  the joint driver's CG phases (cg_step.h)
+//                  scaling, elimination of S^T S with column dropping and the
+//                  reduction of S^T A S to the kept columns' standard problem,
+//                  its m smallest eigenpairs (Householder tridiagonalisation,
+//                  bisection, inverse iteration); extra workgroups of the
+//                  launch run the joint driver's CG update (cg_step.h)
 //   lob_update     X = S C, AX = (AS) C, P = [W,P] C, AP likewise, the next
 //                  residual W = AX - X Theta and its norms (and Y^T W)
 //   lob_out_dots / lob_output: y = X X^T z0 (+ Y Y^T z0), x_out = y / sqrt(d)
 #include <cmath>
+#include <type_traits>
 
 #include "cg_step.h"
 #include "gsf_internal.h"
@@ -319,83 +320,56 @@ __global__ void __launch_bounds__(kThreads) gram_kernel(GramArgs g) {
 }
 
 // ---------------------------------------------------------------------------
-// Rayleigh-Ritz on one wave (FP64)
+// Rayleigh-Ritz on one workgroup of four waves (FP64)
 // ---------------------------------------------------------------------------
-// The whole step runs on the first wave of the workgroup (the others only
-// help to load the Gram pair).  Lanes of one wave issue their LDS accesses in
-// program order and the LDS unit completes them in that order, so a store by
-// one lane is seen by a later load of another lane of the same wave: the
-// steps below need no workgroup barrier, only a compiler-level fence that
-// keeps LDS accesses in program order.
+// Every phase is a chain of dependent FP64 operations, and the step runs once
+// per iteration between kernels that evict its code from the instruction
+// cache, so straight-line code costs about twice its issue time (measured in
+// place against back-to-back launches: about 50 cycles per 64 bytes).  The
+// phases therefore spread each matrix over all 256 threads (thread (tr, tc) of
+// a 16 x 16 grid owns entry (tr, tc), and three more above 16 columns) and
+// loop over columns instead of being unrolled; rows of 16 lanes are DPP rows,
+// so row sums need no LDS; and every padded size is a kernel of its own with
+// everything inlined.  In place, per call: m = 4 (12 columns, with CG's update)
+// 21.2 us, m = 3 FP64 (9) 19.5, m = 8 (24) 55.0, m = 1 (3) 8.1, against 39.9,
+// 28.7, 90.6 and 12.8 for lane-per-row phases unrolled over the columns and
+// called as functions (52 KB of code at 12 columns, 2.2 KB of scratch).
+//
+// Lanes of one wave issue their LDS accesses in program order and the LDS unit
+// completes them in that order, so a store by one lane is seen by a later load
+// of another lane of the same wave with no barrier, only a compiler-level
+// fence that keeps LDS accesses in program order.
 __device__ __forceinline__ void wave_fence() { __asm__ volatile("" ::: "memory"); }
 
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
-// Reciprocal square root: the hardware approximation refined by one Newton
-// step (a few ulp).
+// Reciprocal square root and reciprocal: the hardware approximation (a relative
+// error e below 2^-20) and one step of third order, r (1 + e/2 + 3 e^2/8) and
+// r (1 + e + e^2): an ulp or two.
 __device__ __forceinline__ double rsq_nr(double x) {
-  double r = __builtin_amdgcn_rsq(x);
+  const double r = __builtin_amdgcn_rsq(x);
   const double e = fma(-x * r, r, 1.0);
-  return fma(0.5 * r, e, r);
+  return fma(r * e, fma(0.375, e, 0.5), r);
 }
-// Two Newton steps: full FP64 accuracy for the Cholesky pivots.
-__device__ __forceinline__ double rsq_nr2(double x) {
-  const double r = rsq_nr(x);
-  const double e = fma(-x * r, r, 1.0);
-  return fma(0.5 * r, e, r);
+__device__ __forceinline__ double rcp_nr(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 constexpr int KMAX = 24;
 constexpr int LD = KMAX + 1;
 
 struct RRShared {
-  double A[KMAX * LD];   // Gram pair as loaded (A = S^T A S, B = S^T S)
-  double B[KMAX * LD];
-  double L[KMAX * LD];   // Cholesky factor (dropped columns zero)
-  double LK[KMAX * LD];  // compressed factor of the kept columns
-  double M[KMAX * LD];   // the reduced matrix L^-1 A L^-T, then the tridiagonal rows
-  double M2[KMAX * LD];  // work array of the triangular solves
-  double V[KMAX * LD];   // eigenvectors (columns 0..m-1)
-  double Cs[KMAX * 8];   // output coefficients, staged
-  double bc[2][KMAX];    // broadcast rows of the tridiagonalisation (v, w)
-  double H[KMAX][KMAX];  // reflector vectors v_j (row j) of the tridiagonalisation
-  double hb[KMAX];       // their factors beta_j
-  double lu[8][5][KMAX]; // inverse iteration: per eigenvector LU of T - lambda I (u0, u1, u2, f, swap)
-  double Y[8][KMAX];     // eigenvectors of T (rows of the lane-parallel phases)
-  double delta[KMAX];
-  double rinv[KMAX];
-  double ev[KMAX];
-  int idx[KMAX];
-  int order[KMAX];
-  int nk;                // kept columns (shared with the other waves)
+  double A[2][KMAX * LD];  // double-buffered exchange copies of the matrices that are spread over the threads
+  double B[2][KMAX * LD];
+  double G[2][KMAX * LD];
+  double pv[KMAX];         // M v of a reflector step
+  double td[KMAX];         // the tridiagonal matrix
+  double te[KMAX];
+  double diag[KMAX];
+  double Y[8][KMAX];       // eigenvectors of T
+  double ev[8];
+  double C[8][KMAX];       // the Ritz coefficients, before their signs
 };
 
-// ---------------------------------------------------------------------------
-// Small symmetric eigenproblem: the m smallest eigenpairs of the K x K matrix
-// in sh.M (K <= KB <= 24), on the four waves of the workgroup:
-//  1. Householder tridiagonalisation T = Q^T M Q on wave 0 (lane i owns row i
-//     in registers; v and w of each reflector are read from their lanes;
-//     column sums by DPP within rows of 16 lanes);
-//  2. per eigenvalue, multisection bisection of the Sturm count: one wave per
-//     eigenvalue (two for m > 4), its 64 (32) lanes evaluate the count at
-//     evenly spaced shifts of the bracket, which shrinks by 65 (33) per round
-//     down to about 2^-60 of the Gershgorin interval; rows past K are padded
-//     with a diagonal far above the spectrum, so every loop has the fixed
-//     length KB and no branch;
-//  3. inverse iteration for its eigenvector in the first lane of the same
-//     wave: Gaussian elimination with partial pivoting of T - lambda I in
-//     registers, two solves from a fixed start vector;
-//  4. classical Gram-Schmidt, twice, over the m vectors on wave 0, which keeps
-//     the vectors of a cluster of eigenvalues orthonormal;
-//  5. back-transform z = Q y by the reflectors, one wave per vector.
-// Single-wave code is bound by the latency of its dependency chains; these
-// chains are short, branch-free and spread over four SIMDs.  The cyclic Jacobi
-// method this replaces ran 5-6 sweeps of K - 1 rounds, each an LDS round trip
-// and two chained rotations (38-45 us per call at K = 12).
-// ---------------------------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
@@ -407,121 +381,283 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
   return __hiloint2double(hi, lo);
 }
-// Sum over the first KB lanes of the wave (lanes past the rows must hold 0),
-// returned to every lane; every lane must be active.
-template <int KB>
-__device__ __forceinline__ double sum_rows(double v) {
+// Sum (maximum) over each row of 16 lanes, in every lane of the row.
+__device__ __forceinline__ double row_sum(double v) {
   v += dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   v += dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   v += dpp_d<0x141>(v);  // row_half_mirror: the other quad of the half row
   v += dpp_d<0x140>(v);  // row_mirror: the other half of the row
+  return v;
+}
+__device__ __forceinline__ double row_max(double v) {
+  v = fmax(v, dpp_d<0xB1>(v));
+  v = fmax(v, dpp_d<0x4E>(v));
+  v = fmax(v, dpp_d<0x141>(v));
+  return fmax(v, dpp_d<0x140>(v));
+}
+// The same over the wave's first KB lanes, in every lane; the lanes from KB to
+// 31 must hold 0 (or a value already counted, for the maximum).
+template <int KB>
+__device__ __forceinline__ double sum_rows(double v) {
+  v = row_sum(v);
   if constexpr (KB <= 16) return readlane_d(v, 0);
   return readlane_d(v, 0) + readlane_d(v, 16);
+}
+template <int KB>
+__device__ __forceinline__ double max_rows(double v) {
+  v = row_max(v);
+  if constexpr (KB <= 16) return readlane_d(v, 0);
+  return fmax(readlane_d(v, 0), readlane_d(v, 16));
 }
 
 constexpr double kPadDiag = 1e4;  // diagonal of the padding rows: far above any Ritz value of L_sym (<= 2)
 
 // Number of eigenvalues of T below sigma: sign changes of the leading
 // principal minors p_i of T - sigma I (Sturm), by the three-term recurrence
-// p_i = (d_i - sigma) p_(i-1) - e_(i-1)^2 p_(i-2), no divisions; a zero minor
-// takes the sign opposite to its predecessor.  With Ritz values in [0, 2] and
-// at most 24 rows the minors stay within about 1e+-100 (the padding rows
-// multiply by ~1e4 each), so no rescaling is needed.
+// p_i = (d_i - sigma) p_(i-1) - e_(i-1)^2 p_(i-2), no divisions.  A zero minor
+// needs no case of its own: with every e^2 > 0 the minor after it has the sign
+// opposite to the one before it, one change in all whichever sign the zero
+// carries (e2 holds max(e^2, kMinE2); a coupling of 1e-30 moves no eigenvalue).
+// With Ritz values in [0, 2] and at most 24 rows the minors stay within about
+// 1e+-100 (the padding rows multiply by ~1e4 each), so no rescaling is needed.
+constexpr double kMinE2 = 1e-60;
 template <int KB>
 __device__ __forceinline__ int sturm_count(const double (&d)[KB], const double (&e2)[KB], double sigma) {
   double pm2 = 1.0, pm1 = d[0] - sigma;
-  pm1 = pm1 == 0.0 ? -1e-300 : pm1;
-  int c = pm1 < 0.0 ? 1 : 0;
+  // the minors' sign bits, shifted in one after the other (below p_0 = 1)
+  unsigned signs = (unsigned)__double2hiint(pm1) >> 31;
 #pragma unroll
   for (int i = 1; i < KB; ++i) {
-    double p = fma(d[i] - sigma, pm1, -e2[i - 1] * pm2);
-    p = p == 0.0 ? (pm1 < 0.0 ? 1e-300 : -1e-300) : p;
-    c += ((p < 0.0) != (pm1 < 0.0)) ? 1 : 0;
+    const double p = fma(d[i] - sigma, pm1, -e2[i - 1] * pm2);
+    signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(p), 31);
     pm2 = pm1;
     pm1 = p;
   }
-  return c;
+  return __popc(signs ^ (signs >> 1));
 }
 
-// Step 1 (wave 0): T = Q^T M Q; the rows of T back into sh.M, the reflector
-// vectors v_j into sh.H[j] and their factors into sh.hb.
+// Entries of a thread: rows tr + 16 i, columns tc + 16 j
 template <int KB>
-__device__ void tridiagonalize(RRShared& sh, int K) {
-  const int lane = threadIdx.x & 63;
-  const bool row = lane < KB;
-  const int li = lane < K ? lane : 0;
-  double a[KB];
+struct RRGrid {
+  static constexpr int E = KB > 16 ? 2 : 1;
+  // a thread's entries into an exchange copy (entries past the arrays are dropped)
+  static __device__ __forceinline__ void store(double* dst, const double (&v)[E][E], int tr, int tc) {
 #pragma unroll
-  for (int k = 0; k < KB; ++k) a[k] = (lane < K && k < K) ? sh.M[li * LD + k] : 0.0;
+    for (int i = 0; i < E; ++i)
 #pragma unroll
-  for (int j = 0; j + 2 < KB; ++j) {
-    const double xj = (lane > j && row) ? a[j] : 0.0;
-    const double s2 = sum_rows<KB>(xj * xj);
-    const double x0 = readlane_d(a[j], j + 1);
-    const double nrm = sqrt(s2);
+      for (int j = 0; j < E; ++j)
+        if (E == 1 || (tr + 16 * i < KMAX && tc + 16 * j < KMAX)) dst[(tr + 16 * i) * LD + tc + 16 * j] = v[i][j];
+  }
+};
+
+// Elimination of the scaled B with column dropping (B = L D L^T on the kept
+// columns, L unit lower triangular), the same elementary steps on both sides
+// of the scaled A, which leaves L^-1 A L^-T, and on the right of the identity
+// g, which leaves L^-T: step k takes row k of both matrices (symmetric: also
+// column k) and m_c = B_kc / B_kk for c > k, and subtracts m_r B_kc from B,
+// m_r A_kc + m_c (A_kr - m_r A_kk) from A and m_c g_rk from g.  A column whose
+// pivot is at most drop_tol is left out (its factors are zero, no branch).
+// Every thread stores its entries after a step (double-buffered: one barrier
+// per column), which takes fewer instructions than choosing the row's owners.
+// Returns the kept columns; their pivots in sh.diag.
+template <int KB>
+__device__ __forceinline__ unsigned rr_reduce(RRShared& sh, double (&a)[RRGrid<KB>::E][RRGrid<KB>::E],
+                                              double (&b)[RRGrid<KB>::E][RRGrid<KB>::E],
+                                              double (&g)[RRGrid<KB>::E][RRGrid<KB>::E], int ns, unsigned goodm,
+                                              double drop_tol) {
+  constexpr int E = RRGrid<KB>::E;
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+  int ri[E], ci[E];  // this thread's rows and columns, clamped to the arrays
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    ri[i] = E == 1 || tr + 16 * i < KMAX ? tr + 16 * i : 0;
+    ci[i] = E == 1 || tc + 16 * i < KMAX ? tc + 16 * i : 0;
+#pragma unroll
+    for (int j = 0; j < E; ++j) g[i][j] = tr + 16 * i == tc + 16 * j ? 1.0 : 0.0;
+  }
+  unsigned keptm = 0;
+#pragma unroll 1
+  for (int k = 0; k < ns; ++k) {
+    RRGrid<KB>::store(sh.A[k & 1], a, tr, tc);
+    RRGrid<KB>::store(sh.B[k & 1], b, tr, tc);
+    RRGrid<KB>::store(sh.G[k & 1], g, tr, tc);
+    __syncthreads();
+    const double *ra = sh.A[k & 1] + k * LD, *rb = sh.B[k & 1] + k * LD, *cg = sh.G[k & 1] + k;
+    const double piv = rb[k], akk = ra[k];
+    double br[E], bc[E], ar[E], ac[E], gr[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      br[i] = rb[ri[i]];
+      bc[i] = rb[ci[i]];
+      ar[i] = ra[ri[i]];
+      ac[i] = ra[ci[i]];
+      gr[i] = cg[ri[i] * LD];
+    }
+    const bool keep = ((goodm >> k) & 1u) && piv > drop_tol;
+    keptm |= __ballot(keep) ? 1u << k : 0u;
+    const double rp = keep ? rcp_nr(piv) : 0.0;
+    double mr[E], mc[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      mr[i] = tr + 16 * i > k ? br[i] * rp : 0.0;
+      mc[i] = tc + 16 * i > k ? bc[i] * rp : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        b[i][j] = fma(-mr[i], bc[j], b[i][j]);
+        a[i][j] = fma(-mr[i], ac[j], fma(-mc[j], fma(-mr[i], akk, ar[i]), a[i][j]));
+        g[i][j] = fma(-mc[j], gr[i], g[i][j]);
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    if (tr == tc && ri[i] == tr + 16 * i) sh.diag[ri[i]] = b[i][i];
+  return keptm;
+}
+
+// Householder tridiagonalisation T = Q^T M Q of the K x K matrix spread over
+// the threads (a; zero past K): T into sh.td, sh.te; the reflectors are applied
+// to g from the right as they come (g Q, row sums only).  Two barriers per
+// column: for the matrix, of which the rows j and j + 1 are read, and for M v.
+// With v = x - alpha e_(j+1), M v = M x - alpha M e_(j+1), so that M x is
+// summed beside |x|^2.
+template <int KB>
+__device__ __forceinline__ void rr_tridiagonalize(RRShared& sh, double (&a)[RRGrid<KB>::E][RRGrid<KB>::E],
+                                                  double (&g)[RRGrid<KB>::E][RRGrid<KB>::E], int K) {
+  constexpr int E = RRGrid<KB>::E;
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+  int ri[E], ci[E];
+  bool rin[E], cin[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    rin[i] = E == 1 || tr + 16 * i < KMAX;
+    cin[i] = E == 1 || tc + 16 * i < KMAX;
+    ri[i] = rin[i] ? tr + 16 * i : 0;
+    ci[i] = cin[i] ? tc + 16 * i : 0;
+  }
+#pragma unroll 1
+  for (int j = 0; j + 2 < K; ++j) {
+    RRGrid<KB>::store(sh.A[0], a, tr, tc);
+    __syncthreads();
+    const double* row = sh.A[0] + j * LD;
+    double vr[E], vc[E], nr[E], pr[E], pc[E], mx[E];
+    double s2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      vr[i] = row[ri[i]];
+      vc[i] = row[ci[i]];
+      nr[i] = row[LD + ri[i]];
+    }
+    const double x0 = row[j + 1];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      vr[i] = rin[i] && tr + 16 * i > j ? vr[i] : 0.0;
+      vc[i] = cin[i] && tc + 16 * i > j ? vc[i] : 0.0;
+      s2 = fma(vc[i], vc[i], s2);
+    }
+    s2 = row_sum(s2);
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      double p = 0.0;
+#pragma unroll
+      for (int q = 0; q < E; ++q) p = fma(a[i][q], vc[q], p);
+      mx[i] = row_sum(p);
+    }
+    // |x| = s2 / sqrt(s2)
+    const double nrm = s2 > 0.0 ? s2 * rsq_nr(s2) : 0.0;
     const double alpha = x0 >= 0.0 ? -nrm : nrm;
-    const double v = lane == j + 1 ? x0 - alpha : xj;
-    const double vtv = 2.0 * (s2 - alpha * x0);
-    const double beta = vtv > 0.0 ? 2.0 / vtv : 0.0;
-    if (row) sh.H[j][lane] = v;
-    if (lane == 0) sh.hb[j] = beta;
-    // v_k and w_k come from lane k by lane reads (an LDS broadcast with its
-    // waits cost about 1 us per call)
-    double p0 = 0.0, p1 = 0.0;  // two chains: half the dependent FMAs
 #pragma unroll
-    for (int k = j + 1; k < KB; ++k) {
-      if ((k & 1) == 0) p0 = fma(a[k], readlane_d(v, k), p0);
-      else p1 = fma(a[k], readlane_d(v, k), p1);
+    for (int i = 0; i < E; ++i) {
+      // (M v)_r; zero in the rows that are already tridiagonal
+      pr[i] = rin[i] && tr + 16 * i > j ? fma(-alpha, nr[i], mx[i]) : 0.0;
+      if (rin[i]) sh.pv[ri[i]] = pr[i];  // (the row's 16 lanes alike)
+      if (tr + 16 * i == j + 1) vr[i] = x0 - alpha;
+      if (tc + 16 * i == j + 1) vc[i] = x0 - alpha;
     }
-    const double p = (p0 + p1) * beta;
-    const double kc = 0.5 * beta * sum_rows<KB>(row ? v * p : 0.0);
-    const double w = p - kc * v;
-    // A -= v w^T + w v^T: columns left of j are untouched (their rows are
-    // already reduced, so w is zero there); column j takes w_j = p_j
+    sh.te[j] = alpha;  // (every thread alike)
+    // beta = 2 / v^T v = 1 / (s2 - alpha x0)
+    const double hv = fma(-alpha, x0, s2);
+    const double beta = hv > 0.0 ? rcp_nr(hv) : 0.0;
+    // g (I - beta v v^T)
 #pragma unroll
-    for (int k = j; k < KB; ++k) {
-      const double vk = k > j ? readlane_d(v, k) : 0.0;
-      a[k] -= v * readlane_d(w, k) + w * vk;
+    for (int i = 0; i < E; ++i) {
+      double p = 0.0;
+#pragma unroll
+      for (int q = 0; q < E; ++q) p = fma(g[i][q], vc[q], p);
+      p = -beta * row_sum(p);
+#pragma unroll
+      for (int q = 0; q < E; ++q) g[i][q] = fma(p, vc[q], g[i][q]);
     }
-  }
-  wave_fence();
-  if (row) {
+    __syncthreads();
+    double kc = 0.0;
 #pragma unroll
-    for (int k = 0; k < KB; ++k) sh.M[lane * LD + k] = a[k];
+    for (int i = 0; i < E; ++i) {
+      pc[i] = cin[i] ? sh.pv[ci[i]] : 0.0;
+      kc = fma(vc[i], pc[i], kc);
+    }
+    // M - v w^T - w v^T with w = beta M v - (beta^2 / 2) (v^T M v) v
+    kc = 0.5 * beta * beta * row_sum(kc);
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+#pragma unroll
+      for (int q = 0; q < E; ++q) {
+        const double wr = fma(-kc, vr[i], beta * pr[i]), wc = fma(-kc, vc[q], beta * pc[q]);
+        a[i][q] = fma(-vr[i], wc, fma(-wr, vc[q], a[i][q]));
+      }
   }
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      const int r = tr + 16 * i, c = tc + 16 * q;
+      if (r == c && r < K) sh.td[r] = a[i][q];
+      if (r == K - 1 && c == K - 2) sh.te[c] = a[i][q];
+    }
+  __syncthreads();
 }
 
-// Steps 2-3 (every wave): eigenvalues t = wave (and wave + 4 for m > 4) into
-// sh.ev[t], their eigenvectors of T into sh.Y[t].
+// Eigenvalues t = wave (and wave + 4 for m > 4) of T into sh.ev[t], their
+// eigenvectors into sh.Y[t], every wave its own: multisection bisection of the
+// Sturm count (the wave's 64 lanes, 32 for m > 4, evaluate it at evenly spaced
+// shifts of the bracket, which shrinks by 65 (33) per round, down to 2^-54 of
+// the Gershgorin interval), then two steps of inverse iteration from a fixed
+// start vector (Gaussian elimination with partial pivoting of T - lambda I in
+// registers).  Rows past K are padded with a diagonal far above the spectrum.
 template <int KB>
-__device__ void eig_pairs(RRShared& sh, int K, int m) {
+__device__ __forceinline__ void rr_eig_pairs(RRShared& sh, int K, int m) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // T with the padding rows: d = kPadDiag, e = 0 past row K - 1
   double d[KB], e2[KB], eo[KB];
-  double glo = 0.0, ghi = 0.0, tnorm = 0.0;
 #pragma unroll
   for (int i = 0; i < KB; ++i) {
-    d[i] = i < K ? sh.M[i * LD + i] : kPadDiag;
-    eo[i] = i + 1 < K ? sh.M[(i + 1) * LD + i] : 0.0;  // T[i+1][i] = T[i][i+1]
-    e2[i] = eo[i] * eo[i];
-    const double r = fabs(eo[i]) + (i > 0 ? fabs(eo[i - 1]) : 0.0);
-    if (i < K) {
-      glo = (i == 0 || d[i] - r < glo) ? d[i] - r : glo;
-      ghi = (i == 0 || d[i] + r > ghi) ? d[i] + r : ghi;
-      tnorm = fmax(tnorm, fabs(d[i]) + r);
-    }
+    d[i] = i < K ? sh.td[i] : kPadDiag;
+    eo[i] = i + 1 < K ? sh.te[i] : 0.0;  // T[i+1][i] = T[i][i+1]
+    e2[i] = fmax(eo[i] * eo[i], kMinE2);
+  }
+  double lo, hi, tnorm;
+  {
+    // Gershgorin, lane = row (lanes past K repeat row 0)
+    const int i = lane < K ? lane : 0;
+    const double r = (i + 1 < K ? fabs(sh.te[i]) : 0.0) + (i > 0 ? fabs(sh.te[i > 0 ? i - 1 : 0]) : 0.0);
+    const double di = sh.td[i];
+    lo = -max_rows<KB>(r - di);
+    hi = max_rows<KB>(di + r);
+    tnorm = fmax(fabs(lo), fabs(hi));
   }
   const int half = m > 4 ? 1 : 0;            // two eigenvalues per wave
   const int G = half ? 32 : 64;              // lanes per eigenvalue
-  const int rounds = half ? 12 : 10;         // 33^12, 65^10 > 2^60
+  const int rounds = half ? 11 : 9;          // 33^11, 65^9 > 2^54
   const int sub = half ? (lane >> 5) : 0;
   const int t = wave + 4 * sub;              // this lane's eigenvalue (t >= m: idle copy)
   const int tc = t < m ? t : m - 1;
   const int s = lane & (G - 1);
-  const double pad = 1e-14 * fmax(fabs(glo), fabs(ghi)) + 1e-300;
-  double lo = glo - pad, hi = ghi + pad;
+  const double pad = 1e-14 * tnorm + 1e-300;
+  lo -= pad;
+  hi += pad;
+#pragma unroll 1
   for (int rnd = 0; rnd < rounds; ++rnd) {
-    const double step = (hi - lo) * (1.0 / (double)(G + 1));
+    const double step = (hi - lo) * (half ? 1.0 / 33.0 : 1.0 / 65.0);
     const double sig = fma((double)(s + 1), step, lo);
     const int c = sturm_count<KB>(d, e2, sig);
     const unsigned long long bal = __ballot(c <= tc);
@@ -533,57 +669,66 @@ __device__ void eig_pairs(RRShared& sh, int K, int m) {
     hi = nhi;
   }
   const double lam = 0.5 * (lo + hi);
-  // inverse iteration in the first lane of each group
   const double ptiny = 1e-16 * (tnorm > 0.0 ? tnorm : 1.0);
+  // elimination: one reciprocal per row, of the pivot (kept away from zero),
+  // which the multiplier divides by and the back substitution as well (u0)
   double u0[KB], u1[KB], u2[KB], f[KB], y[KB];
-  unsigned int sw = 0;
+  bool sw[KB];
+  auto off_zero = [&](double v) {
+    const double w = fmax(fabs(v), ptiny);
+    return __hiloint2double(__double2hiint(w) | (__double2hiint(v) & 0x80000000), __double2loint(w));
+  };
   {
-    double c0 = d[0] - lam, c1 = eo[0], c2 = 0.0;
+    double c0 = d[0] - lam, c1 = eo[0];
 #pragma unroll
     for (int i = 0; i + 1 < KB; ++i) {
-      const double sb = eo[i], dn = d[i + 1] - lam, sp = eo[i + 1 < KB ? i + 1 : 0] * (i + 1 < KB - 1 ? 1.0 : 0.0);
-      const bool swp = fabs(sb) > fabs(c0);
-      const double piv = fabs(c0) > ptiny ? c0 : (c0 < 0.0 ? -ptiny : ptiny);
-      const double fi = swp ? c0 / sb : sb / piv;
-      u0[i] = swp ? sb : piv;
-      u1[i] = swp ? dn : c1;
-      u2[i] = swp ? sp : c2;
+      const double sb = eo[i], dn = d[i + 1] - lam, sp = i + 1 < KB - 1 ? eo[i + 1] : 0.0;
+      sw[i] = fabs(sb) > fabs(c0);
+      const double r = rcp_nr(sw[i] ? sb : off_zero(c0));
+      const double fi = (sw[i] ? c0 : sb) * r;
+      u0[i] = r;
+      u1[i] = sw[i] ? dn : c1;
+      u2[i] = sw[i] ? sp : 0.0;
       f[i] = fi;
-      sw |= swp ? (1u << i) : 0u;
-      const double n0 = swp ? c1 - fi * dn : dn - fi * c1;
-      const double n1 = swp ? c2 - fi * sp : sp - fi * c2;
-      c0 = n0;
-      c1 = n1;
-      c2 = 0.0;
+      c0 = fma(-fi, u1[i], sw[i] ? c1 : dn);
+      c1 = sw[i] ? -fi * sp : sp;
     }
-    u0[KB - 1] = fabs(c0) > ptiny ? c0 : (c0 < 0.0 ? -ptiny : ptiny);
+    u0[KB - 1] = rcp_nr(off_zero(c0));
     u1[KB - 1] = 0.0;
     u2[KB - 1] = 0.0;
     f[KB - 1] = 0.0;
-#pragma unroll
-    for (int i = 0; i < KB; ++i) u0[i] = 1.0 / u0[i];  // the back substitution multiplies
+    sw[KB - 1] = false;
   }
+  // start vectors that differ between the eigenvalues (of a cluster)
 #pragma unroll
-  for (int i = 0; i < KB; ++i) y[i] = 1.0 + 0.05 * (double)(((i * 7 + tc * 13 + 3) % 11) - 5);
+  for (int i = 0; i < KB; ++i) y[i] = fma(0.0625, (double)((3 * i + 5 * tc) & 7), 0.75);
+#pragma unroll
   for (int it = 0; it < 2; ++it) {
+    // (the running element in a variable of its own: a choice between two
+    // elements of y became an indexed read, a chain of selects over all of y)
+    double cur = y[0];
 #pragma unroll
     for (int i = 0; i + 1 < KB; ++i) {
-      const bool swp = (sw >> i) & 1u;
-      const double ri = y[i], rn = y[i + 1];
-      y[i] = swp ? rn : ri;
-      y[i + 1] = swp ? ri - f[i] * rn : rn - f[i] * ri;
+      const double nx = y[i + 1];
+      const double ri = sw[i] ? nx : cur, rn = sw[i] ? cur : nx;
+      y[i] = ri;
+      cur = fma(-f[i], ri, rn);
     }
+    y[KB - 1] = cur;
 #pragma unroll
     for (int i = KB - 1; i >= 0; --i) {
       double v = y[i];
-      if (i + 1 < KB) v -= u1[i] * y[i + 1];
-      if (i + 2 < KB) v -= u2[i] * y[i + 2];
+      if (i + 2 < KB) v = fma(-u2[i], y[i + 2], v);
+      if (i + 1 < KB) v = fma(-u1[i], y[i + 1], v);
       y[i] = v * u0[i];
     }
-    double nn = 0.0;
+    double n0 = 0.0, n1 = 0.0;
 #pragma unroll
-    for (int i = 0; i < KB; ++i) nn = fma(y[i], y[i], nn);
-    const double sc = 1.0 / sqrt(nn);
+    for (int i = 0; i < KB; ++i) {
+      if (i & 1) n1 = fma(y[i], y[i], n1);
+      else n0 = fma(y[i], y[i], n0);
+    }
+    const double sc = rsq_nr(n0 + n1);
 #pragma unroll
     for (int i = 0; i < KB; ++i) y[i] *= sc;
   }
@@ -591,268 +736,244 @@ __device__ void eig_pairs(RRShared& sh, int K, int m) {
     sh.ev[t] = lam;
 #pragma unroll
     for (int i = 0; i < KB; ++i) sh.Y[t][i] = i < K ? y[i] : 0.0;
+    if constexpr (KB < KMAX)
+      for (int i = KB; i < KMAX; ++i) sh.Y[t][i] = 0.0;
   }
 }
 
-// Step 4 (wave 0): classical Gram-Schmidt twice over sh.Y[0..m), lane = row.
+// Orthonormal sh.Y[0..m) on wave 0: lane group g (16 lanes, one DPP row) holds
+// the vectors g and g + 4, lane l of it the rows l and l + 16.  The unit
+// vectors of separated eigenvalues come out of the inverse iteration
+// orthogonal to about 1e-16 / gap: with every dot product d below 1e-9 one
+// correction y_q - sum_(p < q) d_pq y_p, all pairs at once, leaves d^2.
+// Otherwise (a cluster) modified Gram-Schmidt, a second pass of it if a vector
+// had a component of more than 1e-2 along an earlier one.
 template <int KB>
-__device__ void orthonormalize(RRShared& sh, int m) {
-  const int lane = threadIdx.x & 63;
-  const bool row = lane < KB;
-  double z[8];
+__device__ __forceinline__ void rr_orthonormalize(RRShared& sh, int m) {
+  constexpr int E = RRGrid<KB>::E;
+  const int lane = threadIdx.x & 63, g = lane >> 4, l = lane & 15;
+  double z[2][E];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) z[q] = (q < m && row) ? sh.Y[q][row ? lane : 0] : 0.0;
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    if (q < m) {
-#pragma unroll
-      for (int pass = 0; pass < 2; ++pass) {
-        double dq[8];
-#pragma unroll
-        for (int s = 0; s < q; ++s) dq[s] = sum_rows<KB>(z[s] * z[q]);
-#pragma unroll
-        for (int s = 0; s < q; ++s) z[q] -= dq[s] * z[s];
-      }
-      const double nq = sum_rows<KB>(z[q] * z[q]);
-      z[q] *= 1.0 / sqrt(nq);
+    for (int i = 0; i < E; ++i) {
+      const int q = g + 4 * u, r = l + 16 * i;
+      z[u][i] = (q < m && r < KMAX) ? sh.Y[q < m ? q : 0][r < KMAX ? r : 0] : 0.0;
     }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-    if (q < m && row) sh.Y[q][lane] = z[q];
-}
-
-// Step 5 (every wave): z_t = Q y_t for t = wave (and wave + 4) into column t of sh.V.
-template <int KB>
-__device__ void back_transform(RRShared& sh, int K, int m) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool row = lane < KB;
-  const int t0 = wave, t1 = wave + 4;
-  double z0 = (t0 < m && row) ? sh.Y[t0][row ? lane : 0] : 0.0;
-  double z1 = (t1 < m && row) ? sh.Y[t1 < 8 ? t1 : 0][row ? lane : 0] : 0.0;
-#pragma unroll
-  for (int j = KB - 3; j >= 0; --j) {
-    const double vj = row ? sh.H[j][lane] : 0.0;
-    const double bj = sh.hb[j];
-    const double d0 = sum_rows<KB>(vj * z0);
-    const double d1 = sum_rows<KB>(vj * z1);
-    z0 -= (bj * d0) * vj;
-    z1 -= (bj * d1) * vj;
-  }
-  if (lane < K) {
-    if (t0 < m) sh.V[lane * LD + t0] = z0;
-    if (t1 < m) sh.V[lane * LD + t1] = z1;
-  }
-}
-
-// Solves the Rayleigh-Ritz problem for GA, GB (ns x ns, already loaded into
-// sh.A and sh.B): C (ns x m, row-major with leading dimension m) and theta
-// (ascending) of the m smallest Ritz pairs, the kept flags and their count.
-// Called by all four waves of the workgroup (every thread must call it): the
-// sequential steps run on wave 0, the eigenpairs on all four, with workgroup
-// barriers between the phases.  KB >= ns is the padded size of the
-// triangular solves (the kept block is extended by an identity factor and
-// zero data there, which changes nothing and keeps the loops free of
-// conditionals).  Steps: symmetrise; scale to unit diag(GB) (columns with a
-// negligible diagonal are dropped); Cholesky GB = L L^T that drops columns
-// with a pivot below drop_tol; M = L^-1 GA L^-T on the kept columns; the m
-// smallest eigenpairs Z of M (tridiagonalisation, bisection, inverse
-// iteration on all four waves); C = L^-T Z.  Loads are issued
-// unconditionally (clamped indices) and only stores are masked, so a lane
-// never waits on a load inside a branch.
-template <int KB>
-__device__ void rayleigh_ritz_kb(RRShared& sh, int ns, int m, double drop_tol, double zero_tol,
-                                 double* Cout, double* theta, int* kept_out, int* nkept_out) {
-  const int lane = threadIdx.x & 63;
-  if (threadIdx.x < 64) {
-  // unit-diagonal scaling: delta_j = diag(GB)_j^-1/2, 0 for a negligible column
-  const int lj = lane < ns ? lane : 0;
-  const double dl = sh.B[lj * LD + lj];
-  const double mx = wave_max(lane < ns && dl > 0.0 ? dl : 0.0);
-  const int gd = lane < ns && dl > zero_tol * zero_tol * mx;
-  const unsigned long long goodm = __ballot(gd);  // the flags as a wave-uniform mask
-  if (lane < ns) sh.delta[lane] = gd ? 1.0 / sqrt(dl) : 0.0;
-  wave_fence();
-  // right-looking Cholesky of the symmetrised, scaled B with column dropping,
-  // lane i owning row i (lower triangle) in registers: column j's pivot and
-  // its entries come from their lanes by lane reads for the rank-1 update of
-  // the rows below (an LDS broadcast instead cost 1 us per LOBPCG step at 9
-  // columns); a dropped column leaves L and the trailing rows unchanged.  The
-  // scaled entries (b_ij + b_ji) / 2 delta_i delta_j are formed as the rows
-  // are loaded (and those of A where the compression reads them); only the
-  // lower triangle of the kept columns of L is ever read.
-  unsigned long long keptm = 0;  // kept columns, wave-uniform
   {
-    double sb[KB];
+    double worst = 0.0, cz[2][E];
 #pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      const int kc = k < ns ? k : 0;
-      const double bij = sh.B[lj * LD + kc], bji = sh.B[kc * LD + lj];
-      const double b = lj == kc ? bij : 0.5 * (bij + bji);
-      sb[k] = (lane < ns && k < ns) ? b * (sh.delta[lj] * sh.delta[kc]) : 0.0;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < E; ++i) cz[u][i] = z[u][i];
+#pragma unroll
+    for (int p = 0; p < 7; ++p) {
+      if (p + 1 >= m) break;
+      double zp[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) zp[i] = l + 16 * i < KMAX ? sh.Y[p][l + 16 * i < KMAX ? l + 16 * i : 0] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (u == 0 ? p >= 3 : m <= 4) continue;
+        double dq = 0.0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) dq = fma(z[u][i], zp[i], dq);
+        dq = g + 4 * u > p ? row_sum(dq) : 0.0;
+        worst = fmax(worst, fabs(dq));
+#pragma unroll
+        for (int i = 0; i < E; ++i) cz[u][i] = fma(-dq, zp[i], cz[u][i]);
+      }
     }
+    if (__ballot(!(worst <= 1e-9)) == 0) {
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      if (j < ns) {
-        const double piv = readlane_d(sb[j], j);
-        const int keep = ((goodm >> j) & 1ull) && piv > drop_tol;
-        const double ip = rsq_nr2(keep ? piv : 1.0);  // 1 / L_jj
-        const double lij = sb[j] * ip;
-        keptm |= (unsigned long long)keep << j;
-        if (keep) {
-          if (lane > j && lane < ns) sh.L[lane * LD + j] = lij;
-          if (lane == j) sh.L[j * LD + j] = piv * ip;
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int l = j + 1; l < KB; ++l) {
-            const double llj = readlane_d(lij, l);  // L[l][j], from lane l
-            sb[l] = (lane > j && l <= lane) ? fma(-lij, llj, sb[l]) : sb[l];
-          }
+        for (int i = 0; i < E; ++i)
+          if (g + 4 * u < m && l + 16 * i < KMAX) sh.Y[g + 4 * u][l + 16 * i] = cz[u][i];
+      return;
+    }
+  }
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    double worst = 0.0;
+#pragma unroll 1
+    for (int p = 0; p < m; ++p) {
+      double zs[E], nq = 0.0;
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        zs[i] = p >= 4 ? z[1][i] : z[0][i];
+        nq = fma(zs[i], zs[i], nq);
+      }
+      const double sc = rsq_nr(row_sum(nq));
+      if (g == (p & 3)) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          zs[i] *= sc;
+          if (p >= 4) z[1][i] = zs[i];
+          else z[0][i] = zs[i];
+          if (l + 16 * i < KMAX) sh.Y[p][l + 16 * i] = zs[i];
         }
       }
-    }
-  }
-  wave_fence();
-  const int kp = lane < ns ? (int)((keptm >> lane) & 1ull) : 0;
-  const unsigned long long km = keptm;
-  const int K = __popcll(km);
-  if (kp) sh.idx[__popcll(km & ((1ull << lane) - 1ull))] = lane;
-  if (lane < ns) kept_out[lane] = kp;
-  if (lane == 0) {
-    *nkept_out = K;
-    sh.nk = K;
-  }
-  wave_fence();
-  if (K >= m) {
-  // compressed factor LK and reduced A (in M2), padded to KB x KB with the
-  // identity and zeros; reciprocal pivots (1 on the padding)
-  for (int e = lane; e < KB * KB; e += 64) {
-    const int a = e / KB, b = e - (e / KB) * KB;
-    const int ia = sh.idx[a < K ? a : 0], ib = sh.idx[b < K ? b : 0];
-    const double aij = sh.A[ia * LD + ib], aji = sh.A[ib * LD + ia];
-    const double lv = sh.L[ia * LD + ib];
-    const double av = (ia == ib ? aij : 0.5 * (aij + aji)) * (sh.delta[ia] * sh.delta[ib]);
-    const bool in = a < K && b < K;
-    sh.LK[a * LD + b] = in ? (b <= a ? lv : 0.0) : (a == b ? 1.0 : 0.0);
-    sh.M2[a * LD + b] = in ? av : 0.0;
-  }
-  if (lane < KB) {
-    const int ia = sh.idx[lane < K ? lane : 0];
-    const double lv = sh.L[ia * LD + ia];
-    sh.rinv[lane] = lane < K ? 1.0 / lv : 1.0;
-  }
-  wave_fence();
-  // T = LK^-1 A_K: lane c solves LK t = A_K[:, c] by forward substitution with
-  // its column in registers (LK read as LDS broadcasts), then writes row c of
-  // T^T.  A_K is symmetric, so M = T LK^-T = (LK^-1 T^T)^T.
-  {
-    const int c = lane < KB ? lane : 0;
-    double col[KB];
+      wave_fence();
+      double zp[E];
 #pragma unroll
-    for (int i = 0; i < KB; ++i) {
-      double v = sh.M2[i * LD + c];
+      for (int i = 0; i < E; ++i) zp[i] = l + 16 * i < KMAX ? sh.Y[p][l + 16 * i < KMAX ? l + 16 * i : 0] : 0.0;
 #pragma unroll
-      for (int t = 0; t < i; ++t) v -= sh.LK[i * LD + t] * col[t];
-      col[i] = v * sh.rinv[i];
-    }
-    if (lane < KB) {
+      for (int u = 0; u < 2; ++u) {
+        const int q = g + 4 * u;
+        double dq = 0.0;
 #pragma unroll
-      for (int i = 0; i < KB; ++i) sh.V[c * LD + i] = col[i];  // V = T^T
-    }
-  }
-  wave_fence();
-  {
-    const int c = lane < KB ? lane : 0;
-    double col[KB];
+        for (int i = 0; i < E; ++i) dq = fma(z[u][i], zp[i], dq);
+        dq = row_sum(dq);
+        if (q > p && q < m) {
+          worst = fmax(worst, fabs(dq));
 #pragma unroll
-    for (int i = 0; i < KB; ++i) {
-      double v = sh.V[i * LD + c];
-#pragma unroll
-      for (int t = 0; t < i; ++t) v -= sh.LK[i * LD + t] * col[t];
-      col[i] = v * sh.rinv[i];
-    }
-    if (lane < KB) {
-#pragma unroll
-      for (int i = 0; i < KB; ++i) sh.M2[c * LD + i] = col[i];  // M2 = (LK^-1 T^T)^T = M
-    }
-  }
-  wave_fence();
-  for (int e = lane; e < K * K; e += 64) {
-    const int a = e / K, b = e - (e / K) * K;
-    const double x = sh.M2[a * LD + b], y = sh.M2[b * LD + a];
-    sh.M[a * LD + b] = 0.5 * (x + y);
-  }
-  wave_fence();
-  tridiagonalize<KB>(sh, K);
-  }  // K >= m
-  }  // wave 0
-  __syncthreads();
-  const int K = sh.nk;
-  if (K < m) return;
-  // the m smallest eigenpairs of M: eigenvalues ascending in ev[0..m),
-  // eigenvectors in the columns 0..m-1 of V
-  eig_pairs<KB>(sh, K, m);
-  __syncthreads();
-  if (threadIdx.x < 64) orthonormalize<KB>(sh, m);
-  __syncthreads();
-  back_transform<KB>(sh, K, m);
-  __syncthreads();
-  if (threadIdx.x >= 64) return;
-  const double* Vc = sh.V;
-  if (lane < m) sh.order[lane] = lane;
-  for (int e = lane; e < ns * m; e += 64) sh.Cs[e] = 0.0;
-  wave_fence();
-  // C_K = LK^-T Z_m: lane t solves LK^T c = Z[:, order[t]] by back substitution
-  {
-    const int t = lane < m ? lane : 0;
-    const int col = sh.order[t];
-    if (lane < m) theta[lane] = sh.ev[col];
-    double c[KB];
-#pragma unroll
-    for (int ii = KB - 1; ii >= 0; --ii) {
-      const double z = Vc[(ii < K ? ii : 0) * LD + col];
-      double v = ii < K ? z : 0.0;
-      // oldest coefficients first: c[ii] then waits for c[ii + 1] through one FMA
-#pragma unroll
-      for (int b = KB - 1; b > ii; --b) v -= sh.LK[b * LD + ii] * c[b];
-      c[ii] = v * sh.rinv[ii];
-    }
-    // sign: the largest-magnitude coefficient (first on ties) is positive, so
-    // Ritz vectors (and residuals) have a fixed sign for a non-odd T
-    double big = 0.0, sgn = 1.0;
-#pragma unroll
-    for (int a = 0; a < KB; ++a) {
-      const double v = sh.delta[sh.idx[a < K ? a : 0]] * c[a];
-      const bool more = a < K && fabs(v) > big;
-      big = more ? fabs(v) : big;
-      sgn = more ? (v < 0.0 ? -1.0 : 1.0) : sgn;
-    }
-    if (lane < m) {
-#pragma unroll
-      for (int a = 0; a < KB; ++a) {
-        const int row = sh.idx[a < K ? a : 0];
-        const double v = sgn * (sh.delta[row] * c[a]);
-        if (a < K) sh.Cs[row * m + t] = v;
+          for (int i = 0; i < E; ++i) z[u][i] = fma(-dq, zp[i], z[u][i]);
+        }
+        if (m <= 4) break;
       }
     }
+    if (__ballot(worst > 1e-2) == 0) break;
   }
-  wave_fence();
-  for (int e = lane; e < ns * m; e += 64) Cout[e] = sh.Cs[e];
 }
 
-__device__ void rayleigh_ritz(RRShared& sh, int ns, int m, double drop_tol, double zero_tol,
-                              double* Cout, double* theta, int* kept_out, int* nkept_out) {
-  if (ns <= 4)
-    rayleigh_ritz_kb<4>(sh, ns, m, drop_tol, zero_tol, Cout, theta, kept_out, nkept_out);
-  else if (ns <= 8)
-    rayleigh_ritz_kb<8>(sh, ns, m, drop_tol, zero_tol, Cout, theta, kept_out, nkept_out);
-  else if (ns <= 10)
-    rayleigh_ritz_kb<10>(sh, ns, m, drop_tol, zero_tol, Cout, theta, kept_out, nkept_out);
-  else if (ns <= 12)
-    rayleigh_ritz_kb<12>(sh, ns, m, drop_tol, zero_tol, Cout, theta, kept_out, nkept_out);
-  else if (ns <= 16)
-    rayleigh_ritz_kb<16>(sh, ns, m, drop_tol, zero_tol, Cout, theta, kept_out, nkept_out);
-  else
-    rayleigh_ritz_kb<KMAX>(sh, ns, m, drop_tol, zero_tol, Cout, theta, kept_out, nkept_out);
+// C = delta (L^-T Q) Y with g = L^-T Q spread over the threads (row sums), then
+// per column the largest-magnitude coefficient (the first on ties) made
+// positive, so that Ritz vectors (and residuals) have a fixed sign for a
+// non-odd T.  Rows of dropped columns hold zeros in g.
+template <int KB>
+__device__ __forceinline__ void rr_output(RRShared& sh, const double (&g)[RRGrid<KB>::E][RRGrid<KB>::E],
+                                          const double (&dr)[RRGrid<KB>::E], int ns, int m, double* Cout,
+                                          double* theta) {
+  constexpr int E = RRGrid<KB>::E;
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+#pragma unroll
+  for (int t = 0; t < (KB < 8 ? KB : 8); ++t) {
+    if (t >= m) break;
+    double y[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) y[q] = sh.Y[t][tc + 16 * q < KMAX ? tc + 16 * q : KMAX - 1];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      double v = 0.0;
+#pragma unroll
+      for (int q = 0; q < E; ++q) v = fma(g[i][q], y[q], v);
+      v = dr[i] * row_sum(v);
+      if (tc == 0 && tr + 16 * i < KMAX) sh.C[t][tr + 16 * i] = v;
+    }
+  }
+  __syncthreads();
+  // thread (t, l) of the first 128: rows l and l + 16 of column t
+  const int t = threadIdx.x >> 4, l = threadIdx.x & 15;
+  if (t < 8) {
+    double v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = t < m && l + 16 * i < ns ? sh.C[t][l + 16 * i < KMAX ? l + 16 * i : 0] : 0.0;
+    const double big = row_max(fmax(fabs(v[0]), fabs(v[1])));
+    const unsigned at = (unsigned)(__ballot(fabs(v[0]) == big) >> (threadIdx.x & 48)) & 0xFFFFu;
+    const unsigned at2 = (unsigned)(__ballot(fabs(v[1]) == big) >> (threadIdx.x & 48)) & 0xFFFFu;
+    const int first = at ? __ffs(at) - 1 : 15 + __ffs(at2);
+    const double lead = t < m && first < ns ? sh.C[t][first] : 0.0;
+    const int flip = __double2hiint(lead) & 0x80000000;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (t < m && l + 16 * i < ns)
+        Cout[(l + 16 * i) * m + t] = __hiloint2double(__double2hiint(v[i]) ^ flip, __double2loint(v[i]));
+    if (t < m && l == 0) theta[t] = sh.ev[t];
+  }
+}
+
+// Solves the Rayleigh-Ritz problem for the Gram pair GA, GB (ns x ns), spread
+// over the 256 threads of the workgroup (ga, gb; every thread must call it):
+// C (ns x m, row-major with leading dimension m) and theta (ascending) of the
+// m smallest Ritz pairs.  Steps: symmetrise; scale to unit diag(GB) (columns
+// with a negligible diagonal are dropped); Cholesky GB = L L^T that drops
+// columns with a pivot at most drop_tol, and M = L^-1 GA L^-T on the kept
+// columns; the m smallest eigenpairs Z of M (tridiagonalisation, bisection,
+// inverse iteration); C = L^-T Z.  Returns the kept columns; with fewer than m
+// of them nothing is written.
+template <int KB>
+__device__ __forceinline__ unsigned rayleigh_ritz(RRShared& sh, const double (&ga)[RRGrid<KB>::E][RRGrid<KB>::E],
+                                                  const double (&gb)[RRGrid<KB>::E][RRGrid<KB>::E], int ns, int m,
+                                                  double drop_tol, double zero_tol, double* Cout, double* theta) {
+  constexpr int E = RRGrid<KB>::E;
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int r = tr + 16 * i, c = tc + 16 * j;
+      if (r < ns && c < ns) {
+        sh.A[1][r * LD + c] = ga[i][j];
+        sh.B[1][r * LD + c] = gb[i][j];
+        if (r == c) sh.diag[r] = gb[i][j];
+      }
+    }
+  __syncthreads();
+  // unit-diagonal scaling: delta_j = diag(GB)_j^-1/2, 0 for a negligible column
+  double dc[E], dr[E], mx = 0.0;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int r = tr + 16 * i, c = tc + 16 * i;
+    dr[i] = r < ns ? sh.diag[r < ns ? r : 0] : 0.0;
+    dc[i] = c < ns ? sh.diag[c < ns ? c : 0] : 0.0;
+    mx = fmax(mx, dc[i] > 0.0 ? dc[i] : 0.0);
+  }
+  const double least = zero_tol * zero_tol * row_max(mx);
+  unsigned goodm = 0;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    goodm |= (unsigned)(__ballot(dc[i] > least) & 0xFFFFull) << (16 * i);
+    dc[i] = dc[i] > least ? rsq_nr(dc[i]) : 0.0;
+    dr[i] = dr[i] > least ? rsq_nr(dr[i]) : 0.0;
+  }
+  double a[E][E], b[E][E];
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int r = tr + 16 * i, c = tc + 16 * j;
+      const bool in = r < ns && c < ns;
+      const double at = sh.A[1][in ? c * LD + r : 0], bt = sh.B[1][in ? c * LD + r : 0];
+      const double sc = dr[i] * dc[j];
+      a[i][j] = in ? (r == c ? ga[i][j] : 0.5 * (ga[i][j] + at)) * sc : 0.0;
+      b[i][j] = in ? (r == c ? gb[i][j] : 0.5 * (gb[i][j] + bt)) * sc : 0.0;
+    }
+  double gm[E][E];
+  const unsigned keptm = rr_reduce<KB>(sh, a, b, gm, ns, goodm, drop_tol);
+  const int K = __popc(keptm);
+  if (K < m) return keptm;
+  // the kept columns moved together and scaled by D^-1/2: M symmetrised, L^-T
+  // with zero rows at the dropped columns
+  auto rank = [&](int r) { return __popc(keptm & ((1u << r) - 1u)); };
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int r = tr + 16 * i, c = tc + 16 * j;
+      const bool kr = (keptm >> r) & 1u, kc = (keptm >> c) & 1u;
+      const double sr = kr ? rsq_nr(sh.diag[r]) : 0.0, scl = kc ? rsq_nr(sh.diag[c]) : 0.0;
+      if (kr && kc) sh.A[0][rank(r) * LD + rank(c)] = a[i][j] * (sr * scl);
+      if (r < ns && kc) sh.G[0][r * LD + rank(c)] = kr ? gm[i][j] * scl : 0.0;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int r = tr + 16 * i, c = tc + 16 * j;
+      a[i][j] = r < K && c < K ? 0.5 * (sh.A[0][r * LD + c] + sh.A[0][c * LD + r]) : 0.0;
+      gm[i][j] = r < ns && c < K ? sh.G[0][r * LD + c] : 0.0;
+    }
+  __syncthreads();
+  rr_tridiagonalize<KB>(sh, a, gm, K);
+  rr_eig_pairs<KB>(sh, K, m);
+  __syncthreads();
+  if (threadIdx.x < 64) rr_orthonormalize<KB>(sh, m);
+  __syncthreads();
+  rr_output<KB>(sh, gm, dr, ns, m, Cout, theta);
+  return keptm;
 }
 
 // The previous update's residual sums (|R_j|^2 for j < m, summed over its
@@ -918,40 +1039,51 @@ __global__ void __launch_bounds__(kThreads) gram_reduce_kernel(GramArgs g, RRArg
   g.level2[(size_t)chunk * st + e] = s;
 }
 
-// Workgroup 0: sums the chunks and assembles GA and GB (ns x ns); its first
-// wave then runs the Rayleigh-Ritz step.  Workgroups 1.. (cg.nblk of them)
-// run a CG update phase of the joint driver on the CUs the step leaves idle.
+// Workgroup 0: sums the chunks of its threads' Gram entries (the 16 x 16 tile
+// format is the thread grid of the Rayleigh-Ritz step) and runs the step.
+// Workgroups 1.. (cg.nblk of them) run a CG update phase of the joint driver
+// on the CUs the step leaves idle.
 //
 // direct != 0 (at most kGramDirect Gram workgroups): no
 // reduction launch ran; the partials take the place of the chunk sums (the
 // reduction would have copied them one to one, so the sums are bitwise the
 // same) and this workgroup sums the previous update's residual partials.
+template <int KB>
 __global__ void __launch_bounds__(kThreads) gram_rr_kernel(GramArgs g, RRArgs r, CgStepArgs cg, int direct) {
   if (blockIdx.x > 0) {
     cg_aupdate_step(cg, (int)blockIdx.x - 1);
     return;
   }
+  constexpr int E = RRGrid<KB>::E;
+  constexpr int NT = KB <= 16 ? 2 : 7;  // tiles of the Gram pair
   __shared__ RRShared sh;
-  __shared__ int nkept;
-  __shared__ int keptf[KMAX];
   __shared__ int live;
-  __shared__ int lockm;
-  const int nt = (g.ns + 15) >> 4;
-  const int ntot = n_tiles_b(nt) + n_tiles_a(nt);
   // Everything this kernel reads from global memory was written by earlier
-  // kernels (other XCDs), so each load is a long trip: the chunk values of
-  // every thread's first two entries (all entries for ns <= 16), the solver
-  // state and the residual sums are all issued before any of them is used
-  // (also before the state says whether the step runs at all).
+  // kernels (other XCDs), so each load is a long trip: the chunk values, the
+  // solver state and the residual sums are all issued before any of them is
+  // used (also before the state says whether the step runs at all).
   const double* chunks = direct ? g.partials : g.level2;
   const int nchunks = direct ? g.nparts : kGramChunks;
-  const int e1 = (int)threadIdx.x + (int)blockDim.x;  // ntot >= 2: every thread has two entries
-  double v0[kGramDirect], v1[kGramDirect];
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+  // tile and entry of this thread's entries: GB's lower off-diagonal tile is
+  // the mirror of the upper one
+  auto sum = [&](int tile, int e) {
+    double v[kGramDirect], t = 0.0;
 #pragma unroll
-  for (int c = 0; c < kGramDirect; ++c) {
-    v0[c] = c < nchunks ? chunks[(size_t)c * (ntot * 256) + threadIdx.x] : 0.0;
-    v1[c] = c < nchunks ? chunks[(size_t)c * (ntot * 256) + e1] : 0.0;
-  }
+    for (int c = 0; c < kGramDirect; ++c) v[c] = c < nchunks ? chunks[(size_t)c * (NT * 256) + tile * 256 + e] : 0.0;
+#pragma unroll
+    for (int c = 0; c < kGramDirect; ++c) t += v[c];
+    return t;
+  };
+  double ga[E][E], gb[E][E];
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const bool mirror = i > j;
+      gb[i][j] = sum(E == 1 ? 0 : (mirror ? 1 : i + j), mirror ? tc * 16 + tr : (int)threadIdx.x);
+      ga[i][j] = sum(E == 1 ? 1 : 3 + 2 * i + j, threadIdx.x);
+    }
   LobpcgState* st = r.st;
   const int active = st != nullptr ? st->active : 1;
   const double tol = st != nullptr ? st->tol : 0.0;
@@ -982,86 +1114,73 @@ __global__ void __launch_bounds__(kThreads) gram_rr_kernel(GramArgs g, RRArgs r,
       live = !(tol > 0.0 && mx <= tol);
       if (!live) st->active = 0;
     }
-    __syncthreads();
-    if (!live) return;
-  }
-  // entry e of the Gram tiles (chunk sums in v) into sh.A / sh.B
-  auto place = [&](int e, const double (&v)[kGramDirect]) {
-    double s = 0.0;
-#pragma unroll
-    for (int c = 0; c < kGramDirect; ++c) s += v[c];
-    bool isb;
-    int row, colj;
-    tile_entry(e, nt, isb, row, colj);
-    if (row < g.ns && colj < g.ns) {
-      if (isb) {
-        sh.B[row * LD + colj] = s;
-        if ((row >> 4) != (colj >> 4)) sh.B[colj * LD + row] = s;  // the lower off-diagonal tile is the mirror
-      } else {
-        sh.A[row * LD + colj] = s;
-      }
+    // (a run without a tolerance is always live: its other waves go on)
+    if (tol > 0.0) {
+      __syncthreads();
+      if (!live) return;
     }
-  };
-  place(threadIdx.x, v0);
-  place(e1, v1);
-  for (int e = e1 + blockDim.x; e < ntot * 256; e += blockDim.x) {
-    double v[kGramDirect];
-#pragma unroll
-    for (int c = 0; c < kGramDirect; ++c) v[c] = c < nchunks ? chunks[(size_t)c * (ntot * 256) + e] : 0.0;
-    place(e, v);
   }
   // soft locking (tol > 0): a column whose residual is already at the
   // tolerance adds no search direction, i.e. its W column counts as zero:
   // the W rows and columns of both Gram matrices are cleared, and the
   // Rayleigh-Ritz step drops the column
-  // (tol, like the rest of the condition, is the same for every thread, so
-  // a run without a tolerance skips the mask and its barrier)
   if (!r.init && st != nullptr && tol > 0.0 && g.ns > g.m) {
+    __shared__ int lockm;
     if (threadIdx.x == 0) {
       int mask = 0;
       for (int j = 0; j < g.m; ++j)
         if (st->res[j] <= tol) mask |= 1 << j;
-      lockm = mask;
+      lockm = mask << g.m;
     }
     __syncthreads();
-    if (lockm != 0) {
-      const int lk = lockm;
-      for (int e = threadIdx.x; e < g.ns * g.ns; e += blockDim.x) {
-        const int i = e / g.ns, j = e - (e / g.ns) * g.ns;
-        const bool li = i >= g.m && i < 2 * g.m && ((lk >> (i - g.m)) & 1);
-        const bool lj = j >= g.m && j < 2 * g.m && ((lk >> (j - g.m)) & 1);
-        if (li || lj) {
-          sh.A[i * LD + j] = 0.0;
-          sh.B[i * LD + j] = 0.0;
+    const int lk = lockm;
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+#pragma unroll
+      for (int j = 0; j < E; ++j)
+        if (((lk >> (tr + 16 * i)) & 1) || ((lk >> (tc + 16 * j)) & 1)) ga[i][j] = gb[i][j] = 0.0;
+  }
+  if (r.gram_out != nullptr) {
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        const int row = tr + 16 * i, col = tc + 16 * j;
+        if (row < g.ns && col < g.ns) {
+          r.gram_out[row * g.ns + col] = ga[i][j];
+          r.gram_out[g.ns * g.ns + row * g.ns + col] = gb[i][j];
         }
+      }
+  }
+  const unsigned kept = rayleigh_ritz<KB>(sh, ga, gb, g.ns, g.m, r.drop_tol, r.zero_tol, r.C, r.theta);
+  const int nkept = __popc(kept);
+  if (st != nullptr) {
+    if ((int)threadIdx.x < g.ns) st->kept[threadIdx.x] = (kept >> threadIdx.x) & 1u;
+    if (nkept >= g.m && (int)threadIdx.x < g.m) st->theta[threadIdx.x] = sh.ev[threadIdx.x];
+    if (threadIdx.x == 0) {
+      st->nkept = nkept;
+      st->dropped = dropped0 + g.ns - nkept;
+      if (nkept < g.m) {
+        st->status = GSF_EBREAKDOWN;
+        st->active = 0;
+        if (r.init) st->start_failed = 1;
       }
     }
   }
-  __syncthreads();
-  if (r.gram_out != nullptr) {
-    for (int e = threadIdx.x; e < g.ns * g.ns; e += blockDim.x) {
-      const int i = e / g.ns, j = e - (e / g.ns) * g.ns;
-      r.gram_out[e] = sh.A[i * LD + j];
-      r.gram_out[g.ns * g.ns + e] = sh.B[i * LD + j];
-    }
-  }
-  rayleigh_ritz(sh, g.ns, g.m, r.drop_tol, r.zero_tol, r.C, r.theta, keptf, &nkept);
-  if (threadIdx.x >= 64) return;
-  wave_fence();
-  if (threadIdx.x == 0 && st != nullptr) {
-    st->nkept = nkept;
-    for (int j = 0; j < g.ns; ++j) st->kept[j] = keptf[j];
-    st->dropped = dropped0 + g.ns - nkept;
-    if (nkept < g.m) {
-      st->status = GSF_EBREAKDOWN;
-      st->active = 0;
-      if (r.init) st->start_failed = 1;
-    } else {
-      for (int j = 0; j < g.m; ++j) st->theta[j] = sh.ev[sh.order[j]];
-    }
-  }
-  if (r.kept_out != nullptr && (int)threadIdx.x < g.ns) r.kept_out[threadIdx.x] = keptf[threadIdx.x];
+  if (r.kept_out != nullptr && (int)threadIdx.x < g.ns) r.kept_out[threadIdx.x] = (kept >> threadIdx.x) & 1u;
   if (r.nkept_out != nullptr && threadIdx.x == 0) *r.nkept_out = nkept;
+}
+
+// Runs f<KB> for the smallest padded size KB >= ns (the eigenvalue part of the
+// step is unrolled over KB rows)
+template <class F>
+void rr_dispatch(int ns, F&& f) {
+  if (ns <= 4) f(std::integral_constant<int, 4>{});
+  else if (ns <= 8) f(std::integral_constant<int, 8>{});
+  else if (ns <= 10) f(std::integral_constant<int, 10>{});
+  else if (ns <= 12) f(std::integral_constant<int, 12>{});
+  else if (ns <= 16) f(std::integral_constant<int, 16>{});
+  else f(std::integral_constant<int, KMAX>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1360,10 +1479,6 @@ gsf_status lob_launch_project(const LobArgs& a, void* B, int nb, hipStream_t s) 
   return launch_status();
 }
 
-// The Gram pair is loaded by one workgroup of four waves; the Rayleigh-Ritz
-// step runs on its first wave.
-int rr_threads(int ns) { return kThreads; }
-
 int gram_tiles_total(int ns) {
   const int nt = (ns + 15) >> 4;
   return nt == 1 ? 2 : 7;
@@ -1403,31 +1518,37 @@ gsf_status lob_launch_gram(const GramArgs& g, const RRArgs& r, int prec, hipStre
   // shares it (the CG phase itself ends long before the step)
   constexpr size_t kHalfCu = 80 * 1024 + 1024;
   constexpr size_t kReserve = sizeof(RRShared) < kHalfCu ? kHalfCu - sizeof(RRShared) : 0;
-  gram_rr_kernel<<<1 + ca.nblk, rr_threads(g.ns), ca.nblk > 0 ? kReserve : 0, s>>>(g, r, ca, direct);
+  rr_dispatch(g.ns, [&](auto kb) {
+    gram_rr_kernel<decltype(kb)::value><<<1 + ca.nblk, kThreads, ca.nblk > 0 ? kReserve : 0, s>>>(g, r, ca, direct);
+  });
   return launch_status();
 }
 
+namespace {
 // Rayleigh-Ritz alone on a Gram pair already in device memory (GA then GB,
-// ns x ns each, row-major) -- one workgroup, the step itself on its first wave.
+// ns x ns each, row-major), one workgroup.
+template <int KB>
 __global__ void __launch_bounds__(kThreads) rr_only_kernel(const double* __restrict__ G, int ns, int m, RRArgs r) {
+  constexpr int E = RRGrid<KB>::E;
   __shared__ RRShared sh;
-  __shared__ int nkept;
-  __shared__ int keptf[KMAX];
-  for (int e = threadIdx.x; e < ns * ns; e += blockDim.x) {
-    const int i = e / ns, j = e - (e / ns) * ns;
-    sh.A[i * LD + j] = G[e];
-    sh.B[i * LD + j] = G[ns * ns + e];
-  }
-  __syncthreads();
-  rayleigh_ritz(sh, ns, m, r.drop_tol, r.zero_tol, r.C, r.theta, keptf, &nkept);
-  if (threadIdx.x >= 64) return;
-  wave_fence();
-  if ((int)threadIdx.x < ns) r.kept_out[threadIdx.x] = keptf[threadIdx.x];
-  if (threadIdx.x == 0) *r.nkept_out = nkept;
+  double ga[E][E], gb[E][E];
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int row = (threadIdx.x >> 4) + 16 * i, col = (threadIdx.x & 15) + 16 * j;
+      const bool in = row < ns && col < ns;
+      ga[i][j] = in ? G[row * ns + col] : 0.0;
+      gb[i][j] = in ? G[ns * ns + row * ns + col] : 0.0;
+    }
+  const unsigned kept = rayleigh_ritz<KB>(sh, ga, gb, ns, m, r.drop_tol, r.zero_tol, r.C, r.theta);
+  if ((int)threadIdx.x < ns) r.kept_out[threadIdx.x] = (kept >> threadIdx.x) & 1u;
+  if (threadIdx.x == 0) *r.nkept_out = __popc(kept);
 }
+}  // namespace
 
 gsf_status lob_launch_rr_only(const double* G, int ns, int m, const RRArgs& r, hipStream_t s) {
-  rr_only_kernel<<<1, rr_threads(ns), 0, s>>>(G, ns, m, r);
+  rr_dispatch(ns, [&](auto kb) { rr_only_kernel<decltype(kb)::value><<<1, kThreads, 0, s>>>(G, ns, m, r); });
   return launch_status();
 }
 

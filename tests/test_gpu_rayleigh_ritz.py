@@ -1,0 +1,76 @@
+"""The Rayleigh-Ritz step (Algorithm 3) at the sizes where its kernels change:
+the padded sizes 4, 8, 10, 12, 16, 24 and their neighbours, the 16-column edge
+of the thread grid, one column, and the structures that take other paths
+(dropped and zero columns, exactly decoupled and clustered Ritz values).
+
+Tolerances.  The step is a congruence with the Cholesky factor of the
+unit-diagonal Gram matrix followed by an orthogonal eigensolver, both backward
+stable: with at most 24 columns and a scaled Gram matrix of condition below
+1e3 (checked), errors stay below 24^2 * 1e3 * 2^-53 ~ 6e-11 relative in the
+worst case; Ritz values, B-orthonormality and the residual of the pencil are
+gated at 1e-11."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-11
+
+
+def _check(gsf, GA, GB, m, drop_tol=1e-10, zero_tol=1e-13):
+    th, C, kept, nk = gsf.rayleigh_ritz(GA, GB, m, drop_tol, zero_tol)
+    rth, _, rkept = oracle.rayleigh_ritz(GA, GB, m, drop_tol, zero_tol)
+    assert np.array_equal(kept, rkept) and nk == np.count_nonzero(rkept)
+    d = np.sqrt(np.diag(GB)[kept])
+    A, B = (G[np.ix_(kept, kept)] / d[:, None] / d for G in (GA, GB))
+    assert np.linalg.cond(B) < 1e3
+    Z = C[kept] * d[:, None]
+    scale = np.linalg.norm(A, 2)
+    assert np.abs(th - rth).max() <= TOL * scale
+    assert np.all(np.diff(th) >= -TOL * scale)
+    assert np.abs(Z.T @ B @ Z - np.eye(m)).max() <= TOL
+    assert np.abs(A @ Z - B @ Z * th).max() <= TOL * scale
+    assert not C[~kept].any()
+    lead = C[np.abs(C).argmax(0), np.arange(m)]
+    assert np.all(lead > 0.0)
+
+
+@pytest.mark.parametrize("ns,m", [(1, 1), (2, 1), (3, 1), (4, 2), (5, 5), (8, 4), (9, 3), (10, 4), (11, 4), (12, 4),
+                                  (13, 5), (15, 5), (16, 8), (17, 6), (21, 7), (23, 8), (24, 8), (24, 3)])
+def test_sizes(gsf, ns, m):
+    rng = np.random.default_rng(100 * ns + m)
+    S = rng.standard_normal((300, ns)) * 10.0 ** rng.uniform(-6, 2, ns)
+    lam = np.linspace(0.0, 1.0, 300) ** 3 * 2.0
+    _check(gsf, S.T @ (lam[:, None] * S), S.T @ S, m)
+
+
+@pytest.mark.parametrize("ns,m", [(6, 3), (12, 4), (16, 8), (24, 8)])
+def test_decoupled_and_clustered(gsf, ns, m):
+    rng = np.random.default_rng(ns)
+    I = np.eye(ns)
+    _check(gsf, np.diag(rng.uniform(0, 2, ns)), I, m)                 # no coupling at all
+    _check(gsf, np.diag(np.repeat(0.5, ns)), I, m)                    # one eigenvalue
+    Q, _ = np.linalg.qr(rng.standard_normal((ns, ns)))
+    lam = np.sort(rng.uniform(0, 2, ns))
+    lam[:m] = 1e-3 + 1e-14 * np.arange(m)                             # a cluster at rounding distance
+    A = (Q * lam) @ Q.T
+    _check(gsf, 0.5 * (A + A.T), I, m)
+    lam[:m] = 1e-3 + 1e-8 * np.arange(m)                              # separated below 1e-7
+    A = (Q * lam) @ Q.T
+    _check(gsf, 0.5 * (A + A.T), I, m)
+
+
+@pytest.mark.parametrize("ns,m,drop", [(6, 2, [3]), (12, 4, [0, 5, 11]), (17, 5, [16]), (24, 8, [8, 9, 15, 16, 23])])
+def test_dropped_columns(gsf, ns, m, drop):
+    rng = np.random.default_rng(7 * ns)
+    S = rng.standard_normal((200, ns))
+    lam = np.linspace(0.0, 1.5, 200)
+    for k, j in enumerate(drop):
+        S[:, j] = 0.0 if k % 2 == 0 else S[:, j - 1] * 3.0            # a zero column, a copy
+    GA, GB = S.T @ (lam[:, None] * S), S.T @ S
+    _check(gsf, GA, GB, m)
+    # fewer columns than asked for
+    G1 = np.ones((ns, ns))
+    th, C, kept, nk = gsf.rayleigh_ritz(G1, G1, m, 1e-10, 1e-13)
+    assert nk == 1 and kept[0] and not kept[1:].any()
