@@ -7,7 +7,7 @@
 // (offset 0), W2[o][c][ky][kx] (offset 288), W3[c][ky][kx] (offset 2592).
 //
 // Training (loss and weight gradient) is in net_train.hip, Adam here;
-// inference inside LOBPCG runs on one fused kernel per 28x28 output tile that keeps the whole receptive field in
+// inference inside LOBPCG runs on one fused kernel per 30x30 output tile that keeps the whole receptive field in
 // LDS and does the three convolutions as implicit GEMMs on bf16 MFMA
 // (v_mfma_f32_16x16x16bf16_1k: 16 output channels x 16 pixels per
 // instruction; layer 3 as 9 per-tap 1x1 products summed over the taps).
@@ -26,6 +26,10 @@ namespace {
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float floatx2_t __attribute__((ext_vector_type(2)));
 
 // FP32 -> BF16, round to nearest, ties to even (NaN stays NaN).
 __device__ __forceinline__ uint32_t f2bf(float f) {
@@ -34,9 +38,6 @@ __device__ __forceinline__ uint32_t f2bf(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return u >> 16;
 }
-__device__ __forceinline__ float bf2f(uint32_t b) { return __uint_as_float(b << 16); }
-__device__ __forceinline__ float rbf(float f) { return bf2f(f2bf(f)); }
-
 // FP64 -> BF16 with a single rounding: the FP32 conversion can create an
 // exact BF16 tie that the FP64 value does not have; then the FP32 value is
 // moved one unit towards the FP64 value, so the tie breaks the right way.
@@ -50,11 +51,7 @@ __device__ __forceinline__ uint32_t d2bf(double d) {
 
 // ReLU that keeps NaN (so a NaN inside the network reaches the output and
 // triggers the T = I fallback).
-__device__ __forceinline__ float relu(float v) { return (v > 0.0f || v != v) ? v : 0.0f; }
-
-__device__ __forceinline__ bool inside(int64_t y, int64_t x, int64_t rows, int64_t cols) {
-  return y >= 0 && y < rows && x >= 0 && x < cols;
-}
+__device__ __forceinline__ float relu(float v) { return __builtin_elementwise_maximum(v, 0.0f); }
 
 // ---------------------------------------------------------------------------
 // optimiser (the training pass is in net_train.hip)
@@ -87,15 +84,20 @@ __global__ void __launch_bounds__(kThreads) net_to_bf16_kernel(int64_t count, co
 // ---------------------------------------------------------------------------
 // fused inference
 // ---------------------------------------------------------------------------
-constexpr int kOT = 28;             // output tile side
-constexpr int kA2 = kOT + 2;        // layer-2 output region side (30)
-constexpr int kA1 = kOT + 4;        // layer-1 output region side (32)
-constexpr int kXS = kOT + 6;        // input region side (34)
-constexpr int kA2N = kA2 * kA2;     // 900
-constexpr int kA1N = kA1 * kA1;     // 1024
-constexpr int kXN = kXS * kXS;      // 1156
-constexpr int kA2Chunks = (kA2N + 15) / 16;  // 57
-static_assert(kA1N / 16 % 16 == 0, "layer-1 chunks must split into pairs over 8 waves");
+// A tile of 30 x 30 outputs keeps the region each layer needs in LDS: the
+// input (36 x 36), a1 (34 x 34) and the nine per-tap products of layer 3 over
+// the 32 x 32 pixels of a2, which themselves stay in registers (64 groups of
+// 16 pixels, so that layer 2 needs no division for a pixel's row).
+constexpr int kOT = 30;             // output tile side
+constexpr int kA2 = kOT + 2;        // layer-2 output region side (32)
+constexpr int kA1 = kOT + 4;        // layer-1 output region side (34)
+constexpr int kXS = kOT + 6;        // input region side (36)
+constexpr int kA2N = kA2 * kA2;
+constexpr int kA1N = kA1 * kA1;
+constexpr int kXN = kXS * kXS;
+constexpr int kA1G = (kA1N + 15) / 16, kA2G = kA2N / 16;  // groups of 16 pixels
+constexpr int kA1P = kA1G * 16;     // pixels of an a1 plane
+constexpr int kC3P = kA2N + 4;      // pitch of a tap's products: lane groups q store taps 4q.. 16 banks apart
 
 struct NetInferArgs {
   const uint16_t* w;       // BF16 weights (flat layout)
@@ -114,55 +116,107 @@ struct NetInferArgs {
 __device__ __forceinline__ floatx4 mfma_bf16(short4_t a, short4_t b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
-
-__device__ __forceinline__ short4_t as_short4(uint32_t lo, uint32_t hi) {
-  short4_t r;
-  r[0] = (short)(lo & 0xffffu);
-  r[1] = (short)(lo >> 16);
-  r[2] = (short)(hi & 0xffffu);
-  r[3] = (short)(hi >> 16);
-  return r;
+__device__ __forceinline__ floatx4 mfma_bf16_k32(uint4_t a, uint4_t b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                 0, 0, 0);
+}
+// two FP32 values rounded to BF16 (nearest even), the first in the low half
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  const floatx2_t v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
 constexpr int kNetThreads = 512;    // 8 waves per tile
 constexpr int kNetWaves = kNetThreads / 64;
-constexpr int kA2PerWave = (kA2Chunks + kNetWaves - 1) / kNetWaves;  // 8
+constexpr int kXIter = (kXN + kNetThreads - 1) / kNetThreads;
+constexpr int kOIter = (kOT * kOT + kNetThreads - 1) / kNetThreads;
 
-// Two independent 16-pixel chunks per step keep two MFMA chains in flight.
-// Layer 1 writes a1 to LDS; layer 2 feeds its BF16 output (already in the
-// layer-3 operand layout) straight into the layer-3 per-tap products.
-template <typename T>
-__global__ void __launch_bounds__(kNetThreads) net_infer_kernel(NetInferArgs a) {
-  __shared__ uint32_t xs[kXN];                         // (r/s, g) as a BF16 pair per pixel
-  __shared__ __align__(16) uint16_t a1s[kA1N * 16];    // layer-1 output
-  __shared__ float c3[9 * kA2N];                       // layer-3 per-tap products
-  __shared__ double red[16 * 3];
-  if (a.st != nullptr && !a.st->active) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int q = lane >> 4, l16 = lane & 15;
-  const int tile = xcd_tile(blockIdx.x, a.ntiles);
-  const int ty = tile / a.tiles_x, tx = tile - (tile / a.tiles_x) * a.tiles_x;
-  const int64_t y0 = (int64_t)ty * kOT, x0 = (int64_t)tx * kOT;
+// i / D for 0 <= i < N by one 24-bit product
+constexpr bool div_exact(int d, int n) {
+  for (int i = 0; i < n; ++i)
+    if (i / d != (i * ((65536 + d - 1) / d)) >> 16) return false;
+  return true;
+}
+template <int D, int N>
+__device__ __forceinline__ int div_px(int i) {
+  static_assert(div_exact(D, N), "the reciprocal is exact over the range");
+  return __mul24(i, (65536 + D - 1) / D) >> 16;
+}
 
-  // MFMA A operands (weights): lane holds A[row = l16][k = 4q + i]
-  short4_t w1a[2], w2a[9], w3a;
+// Workgroup barrier that orders LDS only (the next column's loads stay in flight)
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// One tile of all m columns.  Per column two phases, with one barrier between:
+//   layer 2 of column j (a1 -> c3, the layer-3 products) and the input of
+//   column j + 1 (R / s to BF16);   output of column j and layer 1 of j + 1.
+// Layers 1 and 2 run on v_mfma_f32_16x16x32_bf16: K = 32 holds all nine taps
+// of the two inputs, and two taps of the 16 channels (bitwise the sum of two
+// K = 16 products in order).  The ninth tap takes a K = 32 product with a zero
+// half too: a K = 16 product that accumulates onto a K = 32 result right after
+// it delivers later than the wait before its use allows for (outputs differed
+// from run to run), so that the two forms are never chained.
+// Bound by vector instructions (conversions, addresses, the FP64 scaling) at
+// four waves per SIMD.  An m = 4 block at 2048^2, FP32: 411 us per call, 717
+// with 28 x 28 tiles, K = 16 products only, 64-bit coordinates, FP64
+// divisions, BF16 rounding by integer operations, the guidance converted
+// again for every column and six barriers per column.
+struct NetInferShared {
+  uint32_t xs[kXN + 4];                       // (r/s, g) as a BF16 pair per pixel, and a zero
+  __align__(16) char a1[2 * kA1P * 16];       // layer-1 output [channel half][pixel][8]
+  float c3[9 * kC3P];                         // layer-3 products [tap][pixel]
+  double red[kMaxBlock * 3 * kNetWaves];
+};
+
+// INNER: the tile and its halo lie on the image.
+template <typename T, bool INNER>
+__device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferShared& sh, int ty, int tx) {
+  uint32_t* xs = sh.xs;
+  char* a1s = sh.a1;
+  float* c3 = sh.c3;
+  double* red = sh.red;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, l16 = lane & 15, half = q & 1, sel = q >> 1;
+  const int rows = (int)a.rows, cols = (int)a.cols;
+  const int y0 = ty * kOT, x0 = tx * kOT;
+  auto on_image = [&](int gy, int gx) { return INNER || ((unsigned)gy < (unsigned)rows && (unsigned)gx < (unsigned)cols); };
+
+  // MFMA A operands (weights): lane holds A[row = l16][k]; k = 8q + i (K = 32), 4q + i (K = 16)
+  uint4_t w1, w2[5];
+  short4_t w3a;
+  {
+    auto pack = [](const uint32_t (&v)[8]) {
+      return uint4_t{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+    };
+    uint32_t v[8];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+    for (int i = 0; i < 8; ++i) {
+      const int tap = 4 * q + (i >> 1);
+      v[i] = tap < 9 ? a.w[kOffW1 + l16 * 18 + (i & 1) * 9 + tap] : 0u;
+    }
+    w1 = pack(v);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 16 * h + 4 * q + i, tap = k >> 1, c = k & 1;
-      w1a[h][i] = tap < 9 ? (short)a.w[kOffW1 + l16 * 18 + c * 9 + tap] : (short)0;
+    for (int t = 0; t < 5; ++t) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        v[i] = 2 * t + sel < 9 ? a.w[kOffW2 + l16 * 144 + (8 * half + i) * 9 + 2 * t + sel] : 0u;
+      w2[t] = pack(v);
     }
 #pragma unroll
-  for (int tap = 0; tap < 9; ++tap)
+    for (int i = 0; i < 4; ++i) {
+      w3a[i] = l16 < 9 ? (short)a.w[kOffW3 + (4 * q + i) * 9 + l16] : (short)0;
+    }
+  }
+  // layer-1 B operand: the lane's taps 4q + i, past the last one the zero word
+  int xo[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w2a[tap][i] = (short)a.w[kOffW2 + l16 * 144 + (4 * q + i) * 9 + tap];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) w3a[i] = l16 < 9 ? (short)a.w[kOffW3 + (4 * q + i) * 9 + l16] : (short)0;
-
-  // layer-1 B operand taps of this lane: k = 16h + 4q + i -> taps 8h + 2q, 8h + 2q + 1
-  const int t0 = 2 * q, t1 = 2 * q + 1;
-  const int xo0 = (t0 / 3) * kXS + t0 % 3, xo1 = (t1 / 3) * kXS + t1 % 3, xo8 = 2 * kXS + 2;
+  for (int i = 0; i < 4; ++i) {
+    const int tap = 4 * q + i;
+    xo[i] = tap < 9 ? (tap / 3) * kXS + tap % 3 : -1;
+  }
 
   const T* R = (const T*)a.R;
   T* Z = (T*)a.Z;
@@ -170,119 +224,147 @@ __global__ void __launch_bounds__(kNetThreads) net_infer_kernel(NetInferArgs a) 
   const T* sqd = (const T*)a.sqd;
   const double yinv = (a.st != nullptr && sqd != nullptr) ? a.st->ynorm_inv : 0.0;
   const double rn = sqrt((double)a.n);
+  const int m = a.m;
 
-  for (int j = 0; j < a.m; ++j) {
-    const double s = a.colnorm[j] / rn;
-    // stage the input region
-    for (int e = threadIdx.x; e < kXN; e += kNetThreads) {
-      const int64_t gy = y0 - 3 + e / kXS, gx = x0 - 3 + e % kXS;
-      uint32_t v = 0;
-      if (inside(gy, gx, a.rows, a.cols)) {
-        const int64_t i = gy * a.cols + gx;
-        const double r = (double)R[i * a.m + j];
-        v = (s > 0.0 ? d2bf(r / s) : 0u) | (d2bf((double)G[i]) << 16);
-      }
-      xs[e] = v;
+  // the thread's input pixels: offset (or -1) and guidance, alike for every column
+  int64_t xi[kXIter];
+  uint32_t gv[kXIter];
+#pragma unroll
+  for (int k = 0; k < kXIter; ++k) {
+    const int e = tid + k * kNetThreads;
+    const int ey = div_px<kXS, kXIter * kNetThreads>(e), gy = y0 - 3 + ey, gx = x0 - 3 + e - __mul24(ey, kXS);
+    const bool in = e < kXN && on_image(gy, gx);
+    const int64_t i = in ? (int64_t)gy * cols + gx : -1;
+    xi[k] = i >= 0 ? i * m : -1;
+    gv[k] = in ? d2bf((double)G[i]) << 16 : 0u;
+  }
+  T rv[kXIter];
+  auto load_r = [&](int j) {
+#pragma unroll
+    for (int k = 0; k < kXIter; ++k) rv[k] = xi[k] >= 0 ? R[xi[k] + j] : T(0);
+  };
+  auto put_x = [&](int j) {
+    const double s = a.colnorm[j] / rn, inv = s > 0.0 ? 1.0 / s : 0.0;
+#pragma unroll
+    for (int k = 0; k < kXIter; ++k) {
+      const int e = tid + k * kNetThreads;
+      const uint32_t v = xi[k] >= 0 ? (s > 0.0 ? d2bf((double)rv[k] * inv) : 0u) | gv[k] : 0u;
+      if (e < kXN) xs[e] = v;
     }
-    __syncthreads();
-    // layer 1: 2 -> 16 channels on the 32 x 32 region, K = 9 taps x 2 (padded to 32)
+  };
+  auto layer1 = [&]() {
+#pragma unroll 5
+    for (int g = wave; g < kA1G; g += kNetWaves) {
+      const int p = g * 16 + l16, pc = p < kA1N ? p : kA1N - 1;
+      const int py = div_px<kA1, kA1P>(pc), px = pc - __mul24(py, kA1);
+      const int base = __mul24(py, kXS) + px;
+      uint4_t b;
 #pragma unroll
-    for (int k = 0; k < kA1N / 16 / kNetWaves; k += 2) {
-      floatx4 acc[2];
-      int pp[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int p = (wave + kNetWaves * (k + u)) * 16 + l16, py = p >> 5, px = p & 31;
-        const int base = py * kXS + px;
-        const short4_t b0 = as_short4(xs[base + xo0], xs[base + xo1]);
-        const short4_t b1 = as_short4(q == 0 ? xs[base + xo8] : 0u, 0u);
-        floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
-        c = mfma_bf16(w1a[0], b0, c);
-        acc[u] = mfma_bf16(w1a[1], b1, c);
-        pp[u] = p;
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int p = pp[u], py = p >> 5, px = p & 31;
-        uint32_t u0 = 0, u1 = 0;
-        if (inside(y0 - 2 + py, x0 - 2 + px, a.rows, a.cols)) {
-          u0 = f2bf(relu(acc[u][0])) | (f2bf(relu(acc[u][1])) << 16);
-          u1 = f2bf(relu(acc[u][2])) | (f2bf(relu(acc[u][3])) << 16);
-        }
-        *(uint2*)&a1s[p * 16 + 4 * q] = make_uint2(u0, u1);
-      }
-    }
-    __syncthreads();
-    // layer 2 (16 -> 16 channels on the 30 x 30 region, K = 9 taps x 16) and
-    // layer 3 as 9 per-tap 1x1 products c3[tap][p] = sum_c W3[c][tap] a2[p][c]
-#pragma unroll
-    for (int k = 0; k < kA2PerWave; k += 2) {
-      int base[2];
-      bool in[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        int ch = wave + kNetWaves * (k + u);
-        ch = ch < kA2Chunks ? ch : kA2Chunks - 1;
-        const int pv = ch * 16 + l16;
-        const int p = pv < kA2N ? pv : kA2N - 1;
-        const int py = p / kA2, px = p - (p / kA2) * kA2;
-        base[u] = (py * kA1 + px) * 16 + 4 * q;
-        in[u] = inside(y0 - 1 + py, x0 - 1 + px, a.rows, a.cols);
-      }
-      floatx4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int off = ((tap / 3) * kA1 + tap % 3) * 16;
-        const uint2 bv0 = *(const uint2*)&a1s[base[0] + off];
-        const uint2 bv1 = *(const uint2*)&a1s[base[1] + off];
-        acc0 = mfma_bf16(w2a[tap], as_short4(bv0.x, bv0.y), acc0);
-        acc1 = mfma_bf16(w2a[tap], as_short4(bv1.x, bv1.y), acc1);
-      }
+      for (int i = 0; i < 4; ++i) b[i] = xs[xo[i] >= 0 ? base + xo[i] : kXN];
       const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const floatx4 acc = u == 0 ? acc0 : acc1;
-        uint32_t u0 = 0, u1 = 0;
-        if (in[u]) {
-          u0 = f2bf(relu(acc[0])) | (f2bf(relu(acc[1])) << 16);
-          u1 = f2bf(relu(acc[2])) | (f2bf(relu(acc[3])) << 16);
-        }
-        const floatx4 t = mfma_bf16(w3a, as_short4(u0, u1), zero);
-        const int ch = wave + kNetWaves * (k + u);
-        const int pv = ch * 16 + l16;
-        if (ch < kA2Chunks && pv < kA2N) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (4 * q + i < 9) c3[(4 * q + i) * kA2N + pv] = t[i];
-        }
+      const floatx4 c = mfma_bf16_k32(w1, b, zero);
+      const bool in = on_image(y0 - 2 + py, x0 - 2 + px);
+      uint2 u;
+      u.x = in ? pack2(relu(c[0]), relu(c[1])) : 0u;
+      u.y = in ? pack2(relu(c[2]), relu(c[3])) : 0u;
+      *(uint2*)(a1s + (sel * kA1P + p) * 16 + half * 8) = u;
+    }
+  };
+
+  if (tid == 0) xs[kXN] = 0u;
+  load_r(0);
+  put_x(0);
+  lds_barrier();
+  if (m > 1) load_r(1);
+  layer1();
+  lds_barrier();
+#pragma unroll 1
+  for (int j = 0; j < m; ++j) {
+    // layer 2 (16 -> 16 channels, two taps per product) and layer 3 as nine
+    // per-tap products c3[tap][p] = sum_c W3[c][tap] a2[p][c]
+#pragma unroll 4
+    for (int g = wave; g < kA2G; g += kNetWaves) {
+      const int py = g >> 1, px = (g & 1) * 16 + l16;
+      const char* b = a1s + (half * kA1P + py * kA1 + px) * 16;
+      const char* b1 = b + sel * 16;              // taps (0, 1), (4, 5), (6, 7)
+      const char* b2 = b + sel * (kA1 - 2) * 16;  // taps (2, 3)
+      floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+      c = mfma_bf16_k32(w2[0], *(const uint4_t*)b1, c);
+      c = mfma_bf16_k32(w2[1], *(const uint4_t*)(b2 + 2 * 16), c);
+      c = mfma_bf16_k32(w2[2], *(const uint4_t*)(b1 + (kA1 + 1) * 16), c);
+      c = mfma_bf16_k32(w2[3], *(const uint4_t*)(b1 + 2 * kA1 * 16), c);
+      const uint4_t zero4 = {0u, 0u, 0u, 0u};
+      const uint4_t last = *(const uint4_t*)(b + (2 * kA1 + 2) * 16);
+      c = mfma_bf16_k32(w2[4], sel ? zero4 : last, c);
+      const bool in = on_image(y0 - 1 + py, x0 - 1 + px);
+      uint2 u;
+      u.x = in ? pack2(relu(c[0]), relu(c[1])) : 0u;
+      u.y = in ? pack2(relu(c[2]), relu(c[3])) : 0u;
+      const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      const floatx4 t = mfma_bf16(w3a, __builtin_bit_cast(short4_t, u), zero);
+      float* o = c3 + 4 * q * kC3P + g * 16 + l16;
+      if (q < 3) o[0] = t[0];
+      if (q < 2) {
+        o[kC3P] = t[1];
+        o[2 * kC3P] = t[2];
+        o[3 * kC3P] = t[3];
       }
     }
-    __syncthreads();
+    if (j + 1 < m) put_x(j + 1);
+    lds_barrier();
     // output: y[o] = sum_tap c3[tap][o + off(tap)], w = s y
+    if (j + 2 < m) load_r(j + 2);
+    const double s = a.colnorm[j] / rn;
     double v[3] = {0.0, 0.0, 0.0};
-    for (int e = threadIdx.x; e < kOT * kOT; e += kNetThreads) {
-      const int oy = e / kOT, ox = e - (e / kOT) * kOT;
-      const int64_t gy = y0 + oy, gx = x0 + ox;
-      if (gy >= a.rows || gx >= a.cols) continue;
+#pragma unroll
+    for (int k = 0; k < kOIter; ++k) {
+      const int e = tid + k * kNetThreads;
+      const int oy = div_px<kOT, kOIter * kNetThreads>(e), ox = e - __mul24(oy, kOT);
+      const int gy = y0 + oy, gx = x0 + ox;
+      if (e >= kOT * kOT || (!INNER && (gy >= rows || gx >= cols))) continue;
+      const float* cp = c3 + oy * kA2 + ox;
       float yv = 0.0f;
 #pragma unroll
-      for (int tap = 0; tap < 9; ++tap) yv += c3[tap * kA2N + (oy + tap / 3) * kA2 + ox + tap % 3];
-      const int64_t i = gy * a.cols + gx;
+      for (int tap = 0; tap < 9; ++tap) yv += cp[tap * kC3P + (tap / 3) * kA2 + tap % 3];
+      const int64_t i = (int64_t)gy * cols + gx;
       const T wt = (T)(s * (double)yv);
-      Z[i * a.m + j] = wt;
+      const double r = (double)R[i * m + j];
+      Z[i * m + j] = wt;
       const double wd = (double)wt;
-      v[0] += (double)R[i * a.m + j] * wd;
+      v[0] += r * wd;
       if (sqd != nullptr) v[1] += (double)sqd[i] * yinv * wd;
       if (!__builtin_isfinite(wd)) v[2] += 1.0;
     }
-    block_sum<3>(v, red);
-    if (threadIdx.x == 0) {
-      double* pp = a.partials + ((size_t)blockIdx.x * a.m + j) * 3;
-      pp[0] = v[0];
-      pp[1] = v[1];
-      pp[2] = v[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (k == 1 && sqd == nullptr) continue;
+      const double t = wave_sum(v[k]);
+      if (lane == 0) red[(3 * j + k) * kNetWaves + wave] = t;
     }
+    if (j + 1 < m) layer1();
+    lds_barrier();
   }
+  // the waves' sums in wave order
+  if (tid < 3 * m) {
+    double t = 0.0;
+    if (sqd != nullptr || tid % 3 != 1)
+      for (int wv = 0; wv < kNetWaves; ++wv) t += red[tid * kNetWaves + wv];
+    a.partials[(size_t)blockIdx.x * 3 * m + tid] = t;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kNetThreads) __attribute__((amdgpu_waves_per_eu(4)))
+net_infer_kernel(NetInferArgs a) {
+  __shared__ NetInferShared sh;
+  if (a.st != nullptr && !a.st->active) return;
+  const int tile = xcd_tile(blockIdx.x, a.ntiles);
+  const int ty = tile / a.tiles_x, tx = tile - (tile / a.tiles_x) * a.tiles_x;
+  const int y0 = ty * kOT, x0 = tx * kOT;
+  if (y0 >= 3 && x0 >= 3 && y0 + kOT + 3 <= a.rows && x0 + kOT + 3 <= a.cols)
+    net_infer_tile<T, true>(a, sh, ty, tx);
+  else
+    net_infer_tile<T, false>(a, sh, ty, tx);
 }
 
 // LOBPCG: per column, use T(r) unless it has a non-finite entry or

@@ -488,3 +488,30 @@ def test_net_training_tiles(gsf, shape, B):
     assert nrel(grad.cpu().numpy(), ref_grad) <= NET_TOL
     again_loss, again = tr.loss_grad(idx, inp, tg)
     assert torch.equal(again, grad) and torch.equal(again_loss, loss)  # fixed-order sums
+
+
+@pytest.mark.parametrize("shape,m,prec_name", [((1, 1), 1, "f32"), ((30, 30), 3, "f32"), ((31, 29), 2, "f64"),
+                                               ((33, 36), 8, "f32"), ((60, 66), 5, "f64"), ((1, 95), 4, "f32"),
+                                               ((93, 1), 2, "f32"), ((130, 97), 6, "f32"), ((97, 160), 8, "f64")])
+def test_precond_apply_tiles(gsf, shape, m, prec_name):
+    """T(R) where the 30 x 30 tiles of the inference pass begin and end: a
+    single pixel, whole tiles, one pixel more or less, the 3-pixel halo, single
+    rows and columns, tiles whose halo lies on the image, every column count's
+    pipeline (the tolerance of the module docstring, by column); two calls
+    agree bit for bit."""
+    import torch
+    H, W = shape
+    prec = gsf.F32 if prec_name == "f32" else gsf.F64
+    dt = torch.float32 if prec == gsf.F32 else torch.float64
+    rng = np.random.default_rng(50)
+    g = rng.uniform(0.0, 1.0, (H, W)).astype(np.float32).astype(np.float64)
+    R = (rng.standard_normal((H * W, m)) * 10.0 ** rng.uniform(-3, 3, m)).astype(np.float32).astype(np.float64)
+    op = gsf.Operator("bf", (H, W), _dev(g.ravel(), dt), 2, 2.0, 0.1, prec=prec)
+    w = convnet_init(51)
+    T = gsf.Precond(op, _dev(g.ravel(), dt), _bf16_bits(w))
+    out = T.apply(_dev(R, dt))
+    assert torch.equal(T.apply(_dev(R, dt)), out)
+    out = out.cpu().numpy()
+    for j in range(m):
+        ref = cn.precond_apply(w.astype(np.float64), R[:, j].reshape(H, W), g.reshape(H, W)).ravel()
+        assert nrel(out[:, j], ref) <= NET_TOL, j
