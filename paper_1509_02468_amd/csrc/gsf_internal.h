@@ -52,9 +52,45 @@ inline int bf_num_planes(const gsf_operator_desc& d) {
 // ---------------------------------------------------------------------------
 // device helpers
 // ---------------------------------------------------------------------------
+// v of the lane that a DPP row rotation by N brings here (rows of 16 lanes)
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// v plus the other half's (ROWS = 32) or the neighbour row's (ROWS = 16) v
+template <int ROWS>
+__device__ __forceinline__ double add_swapped(double v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+  u32x2 lo, hi;
+  if constexpr (ROWS == 32) {
+    lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(l, l, false, false));
+    hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(h, h, false, false));
+  } else {
+    lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(l, l, false, false));
+    hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(h, h, false, false));
+  }
+  return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+         __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// Sum over the wave (all 64 lanes active), the same in every lane: the
+// butterfly of distances 32, 16, 8, 4, 2, 1, its exchanges in the vector unit
+// (two permlane swaps or DPP rotations of a few cycles each in place of two
+// LDS permutes of about 100; after distance 8 the values repeat, so that a
+// rotation by d meets the same partner as an exchange over d).
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  v = add_swapped<32>(v);
+  v = add_swapped<16>(v);
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
   return v;
 }
 
@@ -74,7 +110,12 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds /* NV * 1
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       double s = 0.0;
-      for (int w = 0; w < nwaves; ++w) s += lds[k * 16 + w];
+      if (nwaves == 4) {  // the streaming kernels' workgroups: reads in flight together
+#pragma unroll
+        for (int w = 0; w < 4; ++w) s += lds[k * 16 + w];
+      } else {
+        for (int w = 0; w < nwaves; ++w) s += lds[k * 16 + w];
+      }
       v[k] = s;
     }
   }
@@ -89,6 +130,7 @@ __device__ __forceinline__ void reduce_partials(const double* partials, int npar
                                                 double (&out)[NV], double* lds) {
 #pragma unroll
   for (int k = 0; k < NV; ++k) out[k] = 0.0;
+#pragma unroll 4
   for (int b = threadIdx.x; b < nparts; b += blockDim.x) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) out[k] += partials[(size_t)b * stride + k];

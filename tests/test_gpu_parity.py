@@ -445,6 +445,30 @@ def test_cg_1d_small_and_large_paths(gsf, n, prec):
     np.testing.assert_allclose(y.cpu().numpy(), c, rtol=1e-6 if prec == 0 else 1e-15)
 
 
+@pytest.mark.parametrize("offset", [0, 8])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("shape", [(3, 5), (1, 1023), (64, 64), (91, 90), (725, 725)])
+def test_cg_step_chunks(gsf, shape, prec, offset):
+    """The CG step's vector phases in 16-byte chunks: fewer points than a chunk
+    row, every remainder, several chunks per thread (above 524288 points in
+    FP32); and a workspace off the 16-byte grid, where they take elements."""
+    import torch
+    x = _round(scene_2d(*shape, 0.05, 5)[1] if min(shape) > 1 else
+               np.random.default_rng(5).uniform(0, 1, shape), prec, gsf)
+    xd = _torch(x.ravel(), prec, gsf)
+    op = gsf.Operator("bf", shape, xd, radius=1, sigma_d=2.0, sigma_r=0.2, prec=prec)
+    need = op.workspace(gsf.METHOD_CG).numel()
+    ws = torch.empty(need + 16, dtype=torch.uint8, device="cuda")[offset:offset + need]
+    dp = "f32" if prec == 0 else "f64"
+    rr = reference(lambda g: oracle.cg_filter(oracle.build_operator("bf", g.reshape(shape), 1, 2.0, 0.2), g, 8,
+                                              data_prec=dp), x.ravel())
+    y, info = op.cg_filter(xd, 8, ws=ws)
+    e = rel(y.cpu().numpy(), rr.y)
+    print(f"cg chunks {shape} prec={prec} offset={offset}: {e:.2e}")
+    assert info.status == gsf.OK and info.iters == 8
+    assert e <= (rr.gate if prec else TOL[0])
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("shape,radius", [((5, 9), 3), ((9, 5), 3), ((1, 700), 2), ((300, 1), 4), ((37, 500), 8),
                                           ((70, 131), 1), ((600,), 8), ((3,), 8), ((1,), 2)])
