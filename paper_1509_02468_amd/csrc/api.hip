@@ -30,7 +30,8 @@ void bf_set_rpt(const Operator& op, int w, int rpt);
 gsf_status launch_bf_apply_rpt(const Operator& op, int form, int m, const void* x, int64_t ldx, void* y,
                                int64_t ldy, double* dot, int* nparts, int rpt_override, hipStream_t s);
 gsf_status launch_gf_apply(const Operator& op, void* scratch, int form, int m, const void* x, int64_t ldx,
-                           void* y, int64_t ldy, hipStream_t s);
+                           void* y, int64_t ldy, double* dots, int* nparts, hipStream_t s);
+int gf_dot_parts(const Operator& op);
 int vec_blocks(int64_t n);
 int rg_bf_blocks(const Operator& op);
 gsf_status launch_rg_bf(const Operator& op, int mode, const void* g, const void* v, void* y, double* dot,
@@ -207,7 +208,15 @@ void* gf_scratch(const Operator& op) { return op.planes; }
 gsf_status apply_any(const Operator& op, int form, int m, const void* x, int64_t ldx, void* y, int64_t ldy,
                      double* dot, int* nparts, hipStream_t s) {
   if (op.desc.kind == GSF_BF) return launch_bf_apply(op, form, m, x, ldx, y, ldy, dot, nparts, s);
-  return launch_gf_apply(op, gf_scratch(op), form, m, x, ldx, y, ldy, s);
+  return launch_gf_apply(op, gf_scratch(op), form, m, x, ldx, y, ldy, dot, nparts, s);
+}
+
+// GF: the one-column apply's own x^T y partials are taken where the partials'
+// buffer (two values per vector workgroup) holds them; x and y are then not
+// read once more (4096^2, FP32: a dot launch of 52 us per CG step).
+bool gf_dots(const Operator& op) {
+  const int own = gf_dot_parts(op);
+  return own > 0 && own <= 2 * vec_blocks(op.n);
 }
 
 // Bump allocator over a caller workspace (nullptr base: size query).
@@ -747,7 +756,8 @@ struct CgRun {
   // step k (1-based): p from r (with beta from the last update's partials)
   gsf_status pre(int k) { return launch_cg_pbeta(op, w.r, w.p, w.partials2, w.st, k, s); }
   gsf_status apply() {  // q = L_sym p and the p^T q partials
-    if (op.desc.kind == GSF_BF) return apply_any(op, GSF_FORM_LSYM, 1, w.p, 1, w.q, 1, w.partials, &nparts, s);
+    if (op.desc.kind == GSF_BF || gf_dots(op))
+      return apply_any(op, GSF_FORM_LSYM, 1, w.p, 1, w.q, 1, w.partials, &nparts, s);
     GSF_TRY(apply_any(op, GSF_FORM_LSYM, 1, w.p, 1, w.q, 1, nullptr, nullptr, s));
     return launch_dot(op, w.p, w.q, w.partials, &nparts, w.st, s);
   }
@@ -1283,7 +1293,7 @@ gsf_status gsf_reguided_filter(const gsf_operator_desc* desc, int method, const 
     GSF_TRY(launch_rg_s_beta(op, w.r, w.r_old, w.s, w.partials, w.st, s));
     GSF_TRY(launch_cg_pupdate(op, w.s, w.p, w.st, s));
     int nparts = 0;
-    if (bf) {
+    if (bf || gf_dots(op)) {
       GSF_TRY(lap(w.p, w.q, w.partials, &nparts));
     } else {
       GSF_TRY(lap(w.p, w.q, nullptr, nullptr));

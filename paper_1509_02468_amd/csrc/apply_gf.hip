@@ -406,21 +406,29 @@ void gf_apply_typed(const Operator& op, void* scratch, int form, int m, const T*
 }  // namespace
 
 gsf_status launch_gf_apply_fused(const Operator& op, int form, const float* x, int64_t ldx, float* y, int64_t ldy,
-                                 hipStream_t s);
+                                 double* dots, hipStream_t s);
+int gf_fused_groups(const Operator& op);
 
 // One FP32 column: the one-pass kernel (apply_gf_fused.hip).  Blocks and FP64
 // data: the two passes above; scratch: 2 * kMaxBlock planes of n elements
-// (a, b of up to 8 columns).
+// (a, b of up to 8 columns).  dots (nullable, one FP32 column only): x^T y
+// partials, *nparts of them (gf_dot_parts).
 gsf_status launch_gf_apply(const Operator& op, void* scratch, int form, int m, const void* x, int64_t ldx,
-                           void* y, int64_t ldy, hipStream_t s) {
-  if (op.desc.prec == GSF_F32 && m == 1)
-    return launch_gf_apply_fused(op, form, (const float*)x, ldx, (float*)y, ldy, s);
+                           void* y, int64_t ldy, double* dots, int* nparts, hipStream_t s) {
+  if (op.desc.prec == GSF_F32 && m == 1) {
+    if (nparts != nullptr) *nparts = gf_fused_groups(op);
+    return launch_gf_apply_fused(op, form, (const float*)x, ldx, (float*)y, ldy, dots, s);
+  }
   if (op.desc.prec == GSF_F32)
     gf_apply_typed<float>(op, scratch, form, m, (const float*)x, ldx, (float*)y, ldy, s);
   else
     gf_apply_typed<double>(op, scratch, form, m, (const double*)x, ldx, (double*)y, ldy, s);
   return launch_status();
 }
+
+// Partials that the one-column apply can write beside its output, 0 where it
+// writes none (FP64 data).
+int gf_dot_parts(const Operator& op) { return op.desc.prec == GSF_F32 ? gf_fused_groups(op) : 0; }
 
 gsf_status launch_gf_build(const Operator& op, const void* guidance, hipStream_t s) {
   const GfGeom geo = gf_geom<2>(op);

@@ -6,59 +6,73 @@
 // per point, a pass over column pairs reads x at a stride and re-reads the
 // guidance data per pair, 3.9 ms against 1.5 ms at m = 8, 4096^2, r = 8.)
 //
-// A workgroup of 256 threads owns a strip of 256 columns (thread t = strip
-// column t, global column c0 - 2r + t) and a chunk of rows, and walks the
-// window-centre rows k_y top to bottom.  Every step is done by the column's
-// own thread; horizontal window sums are differences of a prefix sum along the
-// strip row (a wave-wide scan by DPP lane shifts, plus the totals of the
-// waves to the left), so no thread loops over a window.  Per centre row:
+// A workgroup is one wave: it owns a strip of 256 columns, four adjacent ones
+// per lane, and a chunk of rows, and walks the window-centre rows k_y top to
+// bottom.  Horizontal window sums are differences of a prefix sum along the
+// strip row (three adds in the lane, then one scan of the lanes' totals by DPP
+// shifts), so no lane loops over a window.  Per centre row:
 //   A  running FP64 vertical window sums of u = D^-1/2 x and g u over input
 //      rows k_y - r .. k_y + r (add the entering row, subtract the leaving
-//      one), scanned along the row;
-//   C  the centre's horizontal sums from two prefix values and its
+//      one), their prefix sums;
+//   C  the centres' horizontal sums from two prefix values each and their
 //      coefficients
 //        a_k = (mean(g u)_k - mu_k mean(u)_k) / (sigma_k^2 + eps),
 //        b_k = mean(u)_k - a_k mu_k
 //      (mu_k and 1/(sigma_k^2 + eps) from the operator build), rounded to
-//      FP32 as the two-pass path stores them, pushed into the column's
-//      LDS ring of the last 2r + 1 centre rows and added to running FP64
-//      vertical sums of (a, b), scanned along the row;
-//   E  the output point of row k_y - r in this column: horizontal sums of
-//      (a, b) from two prefix values and the output form
+//      FP32 as the two-pass path stores them, added to running FP64 vertical
+//      sums of (a, b), their prefix sums;
+//   E  the output points of row k_y - r: horizontal sums of (a, b) from two
+//      prefix values and the output form
 //        GF(u)_i = (g_i sum a + sum b) / N_i,  N x = D^1/2 GF(D^-1/2 x), ...;
-//      then the oldest ring row leaves the (a, b) sums.
-// Two barriers per row order the two prefix rows in LDS (LDS-only fences).  The strip's
-// 256 - 4r output columns carry a 2r halo on each side (r for each box); a
-// chunk of rb output rows walks rb + 2r centre rows.  Loads run D centre
-// rows ahead in a register ring (entering and leaving input rows, the centre
-// row's statistics, the output row's g and x).  HBM traffic per point is
-// Algorithm 1's own: x, g, mu, 1/(var + eps) in and y out (the rows re-read
-// for the leaving sums and the epilogue hit L2).  Counts and 1/sqrt(d) come
-// from the border-truncated window sizes with the same expressions as the
-// operator build (interior values computed once), so u equals the
-// stored-diagonal product bit for bit.  A 1D signal is one row with no
-// vertical window.
+//      then row k_y - 2r leaves the (a, b) sums and row k_y takes its place in
+//      the LDS ring of 2r rows.
+// One wave needs no barriers: LDS operations of a wave complete in order, and
+// the prefix rows of both stages share one buffer.  Step A of the next row
+// runs between the requests for the (a, b) prefix values and their use.
+//
+// One column per thread (256 threads, four scans and sets of addresses per
+// row, two barriers) took four times the vector instructions; now about 330
+// per 256 points and row, 40% of the cycles of the one wave per SIMD that the
+// ring's LDS allows at r = 8.  4096^2, r = 8: 167 us (2.4 TB/s of the 20 B per
+// point), 282 before; a CG filter of 10 steps on 128^2 1.8 (r = 8) to 2.9
+// (r = 1) times as fast, on 1024^2 1.6 to 2.2 times.
+// The strip's 256 - 4r (to a multiple of 8) output columns carry a halo on
+// each side (r for each box); a chunk of rb output rows walks rb + 2r centre
+// rows.  Loads run two centre rows ahead in registers (the entering input row,
+// the centre row's statistics, the output row's g and x, which is also the
+// next centre row's leaving input row).  HBM
+// traffic per point is Algorithm 1's own: x, g, mu, 1/(var + eps) in and y out
+// (the rows read again for the epilogue hit L2).  Counts and
+// 1/sqrt(d) come from the border-truncated window sizes with the same
+// expressions as the operator build (interior values computed once), so u
+// equals the stored-diagonal product bit for bit.  A 1D signal is one row with
+// no vertical window.
 #include <cmath>
+#include <type_traits>
 
 #include "gsf_internal.h"
 
 namespace gsf {
 namespace {
 
-constexpr int kFT = 256;  // threads per workgroup = columns per strip
+constexpr int kFW = 256;  // columns per strip, four per lane
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 struct FusedArgs {
   const float* x;
-  int ldx;
+  int64_t ldx;
   const float* g;
   const float* mu;
   const float* inv;
   float* y;
-  int ldy;
+  int64_t ldy;
   int rows, cols;
   int rb;       // output rows per workgroup
   int form;
   double omega;  // |w| = (2r+1)^ndim
+  double* dots;  // nullable: x^T y partials, one per workgroup
 };
 
 __device__ __forceinline__ int fcount(int v, int len, int r) {
@@ -72,246 +86,437 @@ __device__ __forceinline__ int fcount(int v, int len, int r) {
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ double dpp0(double v) {
   const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWMASK, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWMASK, 0xf, false);
+  constexpr bool zero_fill = ROWMASK == 0xf;
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWMASK, 0xf, zero_fill);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWMASK, 0xf, zero_fill);
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// inclusive prefix sum over the 64 lanes of a wave: shifts by 1, 2, 4, 8
-// within rows of 16 lanes, then the row totals broadcast to the rows above
-__device__ __forceinline__ double wave_scan(double v) {
-  v += dpp0<0x111, 0xf>(v);
-  v += dpp0<0x112, 0xf>(v);
-  v += dpp0<0x114, 0xf>(v);
-  v += dpp0<0x118, 0xf>(v);
-  v += dpp0<0x142, 0xa>(v);
-  v += dpp0<0x143, 0xc>(v);
-  return v;
+// inclusive prefix sums over the 64 lanes of a wave: shifts by 1, 2, 4, 8
+// within rows of 16 lanes, then the row totals broadcast to the rows above;
+// two at a time, each filling the other's latency
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ void scan_step(double& v, double& w) {
+  const double a = dpp0<CTRL, ROWMASK>(v), b = dpp0<CTRL, ROWMASK>(w);
+  v += a;
+  w += b;
+}
+__device__ __forceinline__ void wave_scan2(double& v, double& w) {
+  scan_step<0x111, 0xf>(v, w);
+  scan_step<0x112, 0xf>(v, w);
+  scan_step<0x114, 0xf>(v, w);
+  scan_step<0x118, 0xf>(v, w);
+  scan_step<0x142, 0xa>(v, w);
+  scan_step<0x143, 0xc>(v, w);
 }
 
-// Workgroup barrier that orders LDS only: the fences name the local address
-// space, so the loads of rows ahead stay in flight across it (a plain
-// __syncthreads also waits for every outstanding global load).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+// Keeps the order of the wave's LDS accesses (other lanes read what a lane
+// wrote); the unit itself completes them in order.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-// window sum over strip columns t - R .. t + R from the per-wave inclusive
-// scans P and the wave totals T: the two ends are at most one wave apart
-// (R < 64), so the sum is P[hi] - P[lo - 1] plus the total of lo - 1's wave
-// when it is not hi's wave (lo - 1 = -1: the empty prefix)
-template <int R>
-__device__ __forceinline__ double box_sum(const double* P, const double* T, int t) {
-  const int hi = t + R, lo = t - R - 1;
-  double v = P[hi];
-  if (lo >= 0) {
-    v -= P[lo];
-    if ((lo >> 6) != (hi >> 6)) v += T[lo >> 6];
-  }
-  return v;
-}
+template <int R, int RV>
+struct FusedShape {
+  static constexpr int HL = (2 * R + 3) & ~3;        // strip columns left (and right) of the outputs
+  static constexpr int NOUT = kFW - 2 * HL;
+  static constexpr int PL = (R + 4) / 4, PR = (R + 3) / 4;  // lanes of zeros beside the prefix rows
+  static constexpr int PW = 64 + PL + PR;
+  static constexpr int NR = RV > 0 ? 2 * RV : 1;
+};
 
-// R: window radius; RV: vertical radius (R for images, 0 for a 1D signal);
-// M: columns of the block (1 or 2); D: rows of loads in flight.
-template <int R, int RV, int M, int D>
-__global__ void __launch_bounds__(kFT) gf_fused_kernel(FusedArgs a) {
-  constexpr int NC = 2 * M;            // channels per point: (u_j, g u_j), later (a_j, b_j)
-  constexpr int NOUT = kFT - 4 * R;    // outputs per strip row (strip columns 2R .. 255 - 2R)
-  constexpr int NR = 2 * RV + 1;       // rows of the (a, b) ring
-  constexpr int NW = kFT / 64;
-  __shared__ double P1[NC][kFT];
-  __shared__ double P2[NC][kFT];
-  __shared__ double T1[NC][NW];
-  __shared__ double T2[NC][NW];
-  __shared__ float ring[NR][NC][kFT];  // this column's (a, b) of the last NR centre rows
+template <int R, int RV>
+struct FusedShared {
+  typedef FusedShape<R, RV> S;
+  double P[2][4][S::PW];   // prefix rows of two channels, by column modulo 4
+  f4 ring[S::NR][2][64];   // (a, b) of the last 2 RV centre rows
+};
 
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+enum FusedMode {
+  kInner,    // every column of the strip is on the grid, x and y contiguous
+  kEdge,     // some are not; contiguous, a multiple of four columns
+  kRagged,   // the same, any count of at least four columns
+  kGeneral,  // any strides and widths, element by element
+};
+
+// R: window radius; RV: vertical radius (R for images, 0 for a 1D signal).
+template <int R, int RV, FusedMode MODE>
+__device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R, RV>& sh) {
+  typedef FusedShape<R, RV> Shape;
+  constexpr int HL = Shape::HL, NOUT = Shape::NOUT, PL = Shape::PL, PW = Shape::PW, NR = Shape::NR;
+  auto& P = sh.P;
+  auto& ring = sh.ring;
+
+  const int lane = threadIdx.x;
   const int rows = a.rows, cols = a.cols;
-  const int c0 = (int)blockIdx.x * NOUT;
+  const int col = (int)blockIdx.x * NOUT - HL + 4 * lane;  // the lane's first column (a multiple of 4)
   const int y0 = (int)blockIdx.y * a.rb;
   const int y1 = y0 + a.rb < rows ? y0 + a.rb : rows;
   const bool scale = a.form == GSF_FORM_N || a.form == GSF_FORM_LSYM;
-  const int col = c0 - 2 * R + t;
-  const bool cin = col >= 0 && col < cols;
-  const int colc = cin ? col : 0;
-  const bool centre_col = cin && t >= R && t < kFT - R;
-  const bool out_col = cin && t >= 2 * R && t < kFT - 2 * R;
-  const double rh = 1.0 / (double)fcount(colc, cols, R);
-  const double srh = sqrt(rh);
+  const bool lap = a.form == GSF_FORM_LSYM || a.form == GSF_FORM_L;
+  // contiguous rows: four columns from cb, in the row, moved left by skip to
+  // stand at col (4 or more: all off the grid)
+  const int cb = MODE == kInner ? col : (col < 0 ? 0 : (col + 4 > cols ? cols - 4 : col));
+  const int skip = col < 0 ? 4 : col - cb;
+  const bool whole = MODE == kInner || (col >= 0 && col + 4 <= cols);
   const double sro = 1.0 / sqrt(a.omega);
   // vertical window sizes: 2RV + 1 away from the top and bottom RV rows
   const double rv_in = 1.0 / (double)(2 * RV + 1 < rows ? 2 * RV + 1 : rows);
-  const double srv_in = sqrt(rv_in);
   auto interior = [&](int v) { return v >= RV && v < rows - RV; };
   auto rv_of = [&](int v) { return interior(v) ? rv_in : 1.0 / (double)fcount(v, rows, RV); };
+  // per column 1 / (horizontal window size), 0 off the grid (its u, a and b are zeros)
+  auto rh_of = [&](int e) {
+    const int c = col + e;
+    return MODE == kInner || (c >= 0 && c < cols) ? 1.0 / (double)fcount(c, cols, R) : 0.0;
+  };
   // 1/sqrt(d) with d = N / |w|, as the operator build computes and stores it
-  auto dinv_of_rv = [&](double rv) {
-    const double d = 1.0 / ((rv * rh) * a.omega);
+  auto dinv_of_rv = [&](double rv, int e) {
+    const double d = 1.0 / ((rv * rh_of(e)) * a.omega);
     return (double)(float)(1.0 / sqrt(d));
   };
-  const double dinv_in = dinv_of_rv(rv_in);
-  auto dinv_at = [&](int v) { return interior(v) ? dinv_in : dinv_of_rv(1.0 / (double)fcount(v, rows, RV)); };
+  // away from the top and bottom rows: 1/sqrt(d), 1 / N, and the output's
+  // factor c in N x = c GF(u), c = sqrt(1 / N) / sqrt(|w|) (c = 1 / N for the
+  // unscaled forms)
+  double dinv_in[4], rc_in[4], c_in[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const double rh = rh_of(e);
+    rc_in[e] = rv_in * rh;
+    dinv_in[e] = scale ? dinv_of_rv(rv_in, e) : 1.0;
+    c_in[e] = scale ? (sqrt(rv_in) * sqrt(rh)) * sro : rc_in[e];
+  }
   auto clamp_row = [&](int v) { return v < 0 ? 0 : (v >= rows ? rows - 1 : v); };
 
-  struct Slot {
-    float xin[M], gin, xl[M], gl, mu, inv, eg, ex[M];
-  };
-  auto fill = [&](Slot& s, int k) {
-    const size_t pin = (size_t)clamp_row(k + RV) * cols + colc, pl = (size_t)clamp_row(k - RV - 1) * cols + colc;
-    const size_t pk = (size_t)clamp_row(k) * cols + colc, po = (size_t)clamp_row(k - RV) * cols + colc;
+  // the lane's four values of a row of x (or a plane), zeros off the grid
+  auto row_ld = [&](const float* plane, int v, int64_t ld) {
+    const float* p = plane + (size_t)clamp_row(v) * cols * (MODE == kGeneral ? ld : 1);
+    f4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (MODE == kGeneral) {
 #pragma unroll
-    for (int j = 0; j < M; ++j) {
-      s.xin[j] = a.x[pin * a.ldx + j];
-      s.xl[j] = a.x[pl * a.ldx + j];
-      s.ex[j] = a.x[po * a.ldx + j];
+      for (int e = 0; e < 4; ++e)
+        if (col + e >= 0 && col + e < cols) o[e] = p[(col + e) * ld];
+    } else {
+      o = *(const f4u*)(p + cb);
+      if constexpr (MODE == kRagged) {
+        o = skip & 1 ? f4{o[1], o[2], o[3], 0.0f} : o;
+        o = skip & 2 ? f4{o[2], o[3], 0.0f, 0.0f} : o;
+      }
+      if constexpr (MODE != kInner) o = skip >= 4 ? f4{0.0f, 0.0f, 0.0f, 0.0f} : o;
     }
-    s.gin = a.g[pin];
-    s.gl = a.g[pl];
-    s.mu = a.mu[pk];
-    s.inv = a.inv[pk];
-    s.eg = a.g[po];
+    return o;
   };
+  auto row_x = [&](int v) { return row_ld(a.x, v, a.ldx); };
+  auto row_of = [&](const float* plane, int v) { return row_ld(plane, v, 1); };
 
-  // stage A warm-up: input rows y0 - 2RV .. y0 - 1 of the first centre row's window
-  double sA[NC];
+  // A: the vertical sums of u and g u
+  double su[4], sg[4];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) sA[c] = 0.0;
-  const int wlo = y0 - 2 * RV < 0 ? 0 : y0 - 2 * RV;
-  if (cin) {
-    for (int yy = wlo; yy < y0 && yy < rows; ++yy) {
-      const size_t p = (size_t)yy * cols + colc;
-      const double di = scale ? dinv_at(yy) : 1.0;
-      const double gv = (double)a.g[p];
+  for (int e = 0; e < 4; ++e) su[e] = sg[e] = 0.0;
+  auto take_row = [&](const f4& xv, const f4& gv, int v, bool add, bool inside) {
+    double di[4];
 #pragma unroll
-      for (int j = 0; j < M; ++j) {
-        const double u = (double)a.x[p * a.ldx + j] * di;
-        sA[2 * j] += u;
-        sA[2 * j + 1] += gv * u;
+    for (int e = 0; e < 4; ++e) di[e] = dinv_in[e];
+    if (!inside && scale && !interior(v)) {
+      const double rv = rv_of(v);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) di[e] = dinv_of_rv(rv, e);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double u = (double)xv[e] * di[e];
+      if (add) {
+        su[e] += u;
+        sg[e] += (double)gv[e] * u;
+      } else {
+        su[e] -= u;
+        sg[e] -= (double)gv[e] * u;
       }
     }
+  };
+  // the four prefix values of a lane's columns, of two channels
+  auto prefix = [&](const double (&v)[4], const double (&w)[4], double (&p)[4], double (&q)[4]) {
+    p[0] = v[0];
+    q[0] = w[0];
+#pragma unroll
+    for (int e = 1; e < 4; ++e) {
+      p[e] = p[e - 1] + v[e];
+      q[e] = q[e - 1] + w[e];
+    }
+    double tp = p[3], tq = q[3];
+    wave_scan2(tp, tq);
+    const double lp = tp - p[3], lq = tq - q[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      p[e] += lp;
+      q[e] += lq;
+    }
+    p[3] = tp;
+    q[3] = tq;
+  };
+  auto put = [&](const double (&p0)[4], const double (&p1)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      P[0][e][PL + lane] = p0[e];
+      P[1][e][PL + lane] = p1[e];
+    }
+  };
+  // the prefix values at the ends of the windows c - R .. c + R of the lane's columns c
+  struct Ends {
+    double hi[2][4], lo[2][4];
+  };
+  auto get = [&](Ends& w) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        w.hi[ch][e] = P[ch][(e + R) & 3][PL + lane + ((e + R) >> 2)];
+        w.lo[ch][e] = P[ch][(e - R - 1) & 3][PL + lane + ((e - R - 1) >> 2)];
+      }
+    }
+  };
+
+  for (int e = lane; e < 8 * PW; e += 64) (&P[0][0][0])[e] = 0.0;
+  if constexpr (RV > 0) {
+    const f4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int q = 0; q < NR; ++q) ring[q][0][lane] = ring[q][1][lane] = z;
   }
-  for (int q = 0; q < NR; ++q)
+  double Sa[4], Sb[4];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) ring[q][c][t] = 0.0f;
-  double S[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) S[c] = 0.0;
+  for (int e = 0; e < 4; ++e) Sa[e] = Sb[e] = 0.0;
+  double dot = 0.0;
 
   const int ks = y0 - RV, ke = y1 + RV;  // centre rows of this chunk
-  Slot slot[D];
+  const int wlo = y0 - 2 * RV < 0 ? 0 : y0 - 2 * RV;
+  struct In {
+    f4 x, g;
+  };
+  struct Out {
+    f4 mu, inv, eg, ex;
+  };
+  auto fill_in = [&](int k) { return In{row_x(k + RV), row_of(a.g, k + RV)}; };
+  auto fill_out = [&](int k) {
+    return Out{row_of(a.mu, k), row_of(a.inv, k), row_of(a.g, k - RV), row_x(k - RV)};
+  };
+  // row k: the entering row, and the leaving one, which is row k - 1's output
+  // row.  steady: both are in range and away from the image's borders.
+  Ends wa;
+  auto stage_a = [&](const In& in, const f4& xl, const f4& gl, int k, bool steady) {
+    const int yin = k + RV, yl = k - RV - 1;
+    if (steady || (yin >= 0 && yin < rows)) take_row(in.x, in.g, yin, true, steady);
+    if (steady || (yl >= wlo && yl < rows)) take_row(xl, gl, yl, false, steady);
+    double p0[4], p1[4];
+    prefix(su, sg, p0, p1);
+    wave_lds_order();
+    put(p0, p1);
+    wave_lds_order();
+    get(wa);
+  };
+
+  In in[2];
+  Out ou[2];
+  in[0] = fill_in(ks);
+  in[1] = fill_in(ks + 1);
+  ou[0] = fill_out(ks);
+  ou[1] = fill_out(ks + 1);
+  __asm__ volatile("" ::: "memory");  // these are the oldest loads of the first pass too
+  // input rows y0 - 2RV .. y0 - 1 of the first centre row's window
+  if constexpr (RV > 0) {
+    int yy = wlo;
+    for (; yy + 4 <= y0 && yy + 4 <= rows; yy += 4) {
+      f4 xv[4], gv[4];
 #pragma unroll
-  for (int u = 0; u < D; ++u) fill(slot[u], ks + u);
-  for (int kb = ks; kb < ke; kb += D) {
+      for (int q = 0; q < 4; ++q) {
+        xv[q] = row_x(yy + q);
+        gv[q] = row_of(a.g, yy + q);
+      }
 #pragma unroll
-    for (int u = 0; u < D; ++u) {
-      const int k = kb + u;
-      const Slot cur = slot[u];
-      fill(slot[u], k + D);
-      if (k < ke) {  // uniform over the workgroup
-        // A: the column's vertical sums for centre row k, scanned along the row
-        const int yin = k + RV, yl = k - RV - 1;
-        const bool ain = cin && yin >= 0 && yin < rows;
-        const bool lin = cin && yl >= wlo && yl < rows;
-        const double din = scale ? dinv_at(yin) : 1.0;
-        const double dl = scale ? dinv_at(yl) : 1.0;
+      for (int q = 0; q < 4; ++q) take_row(xv[q], gv[q], yy + q, true, false);
+    }
+    for (; yy < y0 && yy < rows; ++yy) take_row(row_x(yy), row_of(a.g, yy), yy, true, false);
+  }
+  stage_a(in[0], ou[0].ex, ou[0].eg, ks, false);  // no row leaves yet
+  in[0] = fill_in(ks + 2);
+  __asm__ volatile("" ::: "memory");
+
+  int slot = 0;
+  auto step = [&](int k, Out& cur, In& in_next, auto steady_t) {
+    constexpr bool steady = decltype(steady_t)::value;
+    // C: the centres' (a, b)
+    f4 av = {0.0f, 0.0f, 0.0f, 0.0f}, bv = av;
+    if (steady || (k >= 0 && k < rows)) {
+      double rc[4];
 #pragma unroll
-        for (int j = 0; j < M; ++j) {
-          const double ui = (double)cur.xin[j] * din, ul = (double)cur.xl[j] * dl;
-          sA[2 * j] += (ain ? ui : 0.0) - (lin ? ul : 0.0);
-          sA[2 * j + 1] += (ain ? (double)cur.gin * ui : 0.0) - (lin ? (double)cur.gl * ul : 0.0);
-        }
+      for (int e = 0; e < 4; ++e) rc[e] = rc_in[e];
+      if (!steady && !interior(k)) {
+        const double rv = rv_of(k);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const double p = wave_scan(cin ? sA[c] : 0.0);
-          P1[c][t] = p;
-          if (lane == 63) T1[c][wave] = p;
-        }
-        lds_barrier();
-        // C: the centre's (a, b), into the ring and the vertical (a, b) sums
-        float abn[NC];
+        for (int e = 0; e < 4; ++e) rc[e] = rv * rh_of(e);
+      }
 #pragma unroll
-        for (int c = 0; c < NC; ++c) abn[c] = 0.0f;
-        if (centre_col && k >= 0 && k < rows) {
-          const double rc = rv_of(k) * rh;
-          const double mk = (double)cur.mu, ik = (double)cur.inv;
-#pragma unroll
-          for (int j = 0; j < M; ++j) {
-            const double su = box_sum<R>(P1[2 * j], T1[2 * j], t);
-            const double sgu = box_sum<R>(P1[2 * j + 1], T1[2 * j + 1], t);
-            const double mean_u = su * rc, mean_gu = sgu * rc;
-            const double av = (mean_gu - mk * mean_u) * ik;
-            abn[2 * j] = (float)av;
-            abn[2 * j + 1] = (float)(mean_u - av * mk);
-          }
-        }
-        // slot of centre row k: it held row k - NR, which already left the sums
-        const int slot_k = ((k % NR) + NR) % NR;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          ring[slot_k][c][t] = abn[c];
-          S[c] += (double)abn[c];
-          const double p = wave_scan(S[c]);
-          P2[c][t] = p;
-          if (lane == 63) T2[c][wave] = p;
-        }
-        lds_barrier();
-        // E: the output point of row k - RV in this column
-        const int yo = k - RV;
-        if (out_col && yo >= y0 && yo < y1) {
-          const double rvo = rv_of(yo);
-          const double rc = rvo * rh, src = (interior(yo) ? srv_in : sqrt(rvo)) * srh;
-          const double gi = (double)cur.eg;
-#pragma unroll
-          for (int j = 0; j < M; ++j) {
-            const double sa = box_sum<R>(P2[2 * j], T2[2 * j], t);
-            const double sb = box_sum<R>(P2[2 * j + 1], T2[2 * j + 1], t);
-            const double gfu = gi * sa + sb;
-            const double xi = (double)cur.ex[j];
-            double out;
-            if (a.form == GSF_FORM_RW) {
-              out = gfu * rc;
-            } else if (a.form == GSF_FORM_L) {
-              out = (xi - gfu * rc) * (sro * sro / rc);
-            } else {
-              const double nx = gfu * (src * sro);
-              out = a.form == GSF_FORM_LSYM ? xi - nx : nx;
-            }
-            a.y[((size_t)yo * cols + col) * a.ldy + j] = (float)out;
-          }
-        }
-        // the oldest centre row, k - 2RV, leaves the (a, b) sums
-        const int slot_o = (((k - 2 * RV) % NR) + NR) % NR;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) S[c] -= (double)ring[slot_o][c][t];
+      for (int e = 0; e < 4; ++e) {
+        const double mean_u = (wa.hi[0][e] - wa.lo[0][e]) * rc[e], mean_gu = (wa.hi[1][e] - wa.lo[1][e]) * rc[e];
+        const double mk = (double)cur.mu[e], ik = (double)cur.inv[e];
+        const double ak = (mean_gu - mk * mean_u) * ik;
+        av[e] = (float)ak;
+        bv[e] = (float)(mean_u - ak * mk);
       }
     }
+    double p0[4], p1[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      Sa[e] += (double)av[e];
+      Sb[e] += (double)bv[e];
+    }
+    prefix(Sa, Sb, p0, p1);
+    wave_lds_order();
+    put(p0, p1);
+    wave_lds_order();
+    Ends w;
+    get(w);
+    f4 oa = av, ob = bv;  // the oldest centre row, k - 2RV
+    if constexpr (RV > 0) {
+      oa = ring[slot][0][lane];
+      ob = ring[slot][1][lane];
+      wave_lds_order();
+      ring[slot][0][lane] = av;
+      ring[slot][1][lane] = bv;
+      slot = slot + 1 == NR ? 0 : slot + 1;
+    }
+    // A of the next row, while the prefix values arrive
+    stage_a(in_next, cur.ex, cur.eg, k + 1, steady);
+    in_next = fill_in(k + 3);
+    // E: the output points of row k - RV
+    const int yo = k - RV;
+    if (steady || (yo >= y0 && yo < y1)) {
+      double c[4], nx[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[e] = c_in[e];
+      if (!steady && !interior(yo)) {
+        const double rvo = rv_of(yo), srv = sqrt(rvo);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double rh = rh_of(e);
+          c[e] = scale ? (srv * sqrt(rh)) * sro : rvo * rh;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double sa = w.hi[0][e] - w.lo[0][e], sb = w.hi[1][e] - w.lo[1][e];
+        nx[e] = ((double)cur.eg[e] * sa + sb) * c[e];
+      }
+      if (lap) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nx[e] = (double)cur.ex[e] - nx[e];
+      }
+      if (a.form == GSF_FORM_L) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nx[e] *= sro * sro / c[e];
+      }
+      f4 out;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = (float)nx[e];
+      if (lane >= HL / 4 && lane < 64 - HL / 4) {
+        float* yp = a.y + ((int64_t)yo * cols + col) * a.ldy;
+        if (MODE != kGeneral && whole) {
+          *(f4u*)yp = out;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (whole || col + e < cols) yp[e * a.ldy] = out[e];
+        }
+        if (a.dots != nullptr) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (whole || col + e < cols) dot += (double)cur.ex[e] * (double)out[e];
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      Sa[e] -= (double)oa[e];
+      Sb[e] -= (double)ob[e];
+    }
+    // after the last use of the old values: the loads land in their registers
+    // (asked for earlier they need copies, which wait for them, every row)
+    cur = fill_out(k + 2);
+  };
+  // Two rows per pass, each with its own registers.  The pass has one way
+  // through (an odd count's last row is past the outputs, and writes nothing):
+  // with an exit between the rows every wait allowed for a pass that had
+  // skipped the younger loads, and drained them all.  Rows whose windows and
+  // outputs are all away from the borders take straight-line code.
+  const int sk0 = (y0 > RV ? y0 : RV) + RV, sk1 = y1 + RV < rows - 2 * RV - 1 ? y1 + RV : rows - 2 * RV - 1;
+  for (int k = ks; k < ke; k += 2) {
+    if (RV > 0 && k >= sk0 && k + 1 < sk1) {
+      step(k, ou[0], in[1], std::true_type{});
+      step(k + 1, ou[1], in[0], std::true_type{});
+    } else {
+      step(k, ou[0], in[1], std::false_type{});
+      step(k + 1, ou[1], in[0], std::false_type{});
+    }
+  }
+  if (a.dots != nullptr) {
+    dot = wave_sum(dot);
+    if (lane == 0) a.dots[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = dot;
   }
 }
 
-template <int R, int RV, int M>
-void launch_fused_rm(const FusedArgs& a0, hipStream_t s) {
-  constexpr int D = 2;
-  constexpr int NOUT = kFT - 4 * R;
-  FusedArgs a = a0;
-  const int strips = (a.cols + NOUT - 1) / NOUT;
-  // rows per workgroup: about 1024 workgroups (four per CU), at least 32 rows
-  // so that the 2r extra centre rows of a chunk stay a modest share
-  int rb = (int)(((int64_t)a.rows * strips + 1023) / 1024);
-  rb = rb < 32 ? 32 : (rb > 256 ? 256 : rb);
-  if (RV == 0) rb = 1;
-  a.rb = rb;
-  const dim3 grid((unsigned)strips, (unsigned)((a.rows + rb - 1) / rb));
-  gf_fused_kernel<R, RV, M, D><<<grid, kFT, 0, s>>>(a);
+template <int R, int RV, FusedMode FORM>
+__global__ void __launch_bounds__(64) gf_fused_kernel(FusedArgs a) {
+  __shared__ FusedShared<R, RV> sh;
+  typedef FusedShape<R, RV> Shape;
+  if constexpr (FORM == kGeneral) {
+    gf_fused_strip<R, RV, kGeneral>(a, sh);
+  } else {
+    const int first = (int)blockIdx.x * Shape::NOUT - Shape::HL;
+    if (first >= 0 && first + kFW <= a.cols)
+      gf_fused_strip<R, RV, kInner>(a, sh);
+    else
+      gf_fused_strip<R, RV, FORM == kRagged ? kRagged : kEdge>(a, sh);
+  }
 }
 
-template <int M>
-void launch_fused_m(const FusedArgs& a, int r, bool two_d, hipStream_t s) {
-#define GSF_FUSED_CASE(RR)                                        \
-  case RR:                                                        \
-    if (two_d) launch_fused_rm<RR, RR, M>(a, s);                   \
-    else launch_fused_rm<RR, 0, M>(a, s);                          \
+// Workgroups of one call: as many as the chip holds at once at r = 8 (37 KB of
+// LDS: four per CU), so that no second round is left nearly empty; more, of at
+// most 256 rows, only where the strips alone exceed that.  Short chunks walk
+// 2r rows beside their own but leave no CU idle.
+struct FusedGrid {
+  int strips, chunks, rb;
+};
+
+FusedGrid fused_grid(int rows, int cols, int r, bool two_d) {
+  constexpr int kGroups = 1024, kMinRows = 4, kMaxRows = 256;
+  FusedGrid g;
+  const int nout = kFW - 2 * ((2 * r + 3) & ~3);
+  g.strips = (cols + nout - 1) / nout;
+  const int chunks = g.strips < kGroups ? kGroups / g.strips : 1;
+  g.rb = (rows + chunks - 1) / chunks;
+  g.rb = g.rb < kMinRows ? kMinRows : (g.rb > kMaxRows ? kMaxRows : g.rb);
+  if (!two_d) g.rb = 1;
+  g.chunks = (rows + g.rb - 1) / g.rb;
+  return g;
+}
+
+template <int R, int RV>
+void launch_fused_r(FusedArgs a, const FusedGrid& g, hipStream_t s) {
+  a.rb = g.rb;
+  const dim3 grid((unsigned)g.strips, (unsigned)g.chunks);
+  if (a.ldx != 1 || a.ldy != 1 || a.cols < 4)
+    gf_fused_kernel<R, RV, kGeneral><<<grid, 64, 0, s>>>(a);
+  else if (a.cols % 4 != 0)
+    gf_fused_kernel<R, RV, kRagged><<<grid, 64, 0, s>>>(a);
+  else
+    gf_fused_kernel<R, RV, kEdge><<<grid, 64, 0, s>>>(a);
+}
+
+void launch_fused(const FusedArgs& a, int r, bool two_d, hipStream_t s) {
+  const FusedGrid g = fused_grid(a.rows, a.cols, r, two_d);
+#define GSF_FUSED_CASE(RR)                              \
+  case RR:                                              \
+    if (two_d) launch_fused_r<RR, RR>(a, g, s);          \
+    else launch_fused_r<RR, 0>(a, g, s);                 \
     break;
   switch (r) {
     GSF_FUSED_CASE(1)
@@ -328,23 +533,30 @@ void launch_fused_m(const FusedArgs& a, int r, bool two_d, hipStream_t s) {
 
 }  // namespace
 
-// One-pass GF apply of one FP32 column.
+int gf_fused_groups(const Operator& op) {
+  const FusedGrid g = fused_grid((int)op.rows, (int)op.cols, op.desc.radius, op.desc.ndim == 2);
+  return g.strips * g.chunks;
+}
+
+// One-pass GF apply of one FP32 column; dots (nullable): x^T y partials, one
+// per workgroup (gf_fused_groups).
 gsf_status launch_gf_apply_fused(const Operator& op, int form, const float* x, int64_t ldx, float* y, int64_t ldy,
-                                 hipStream_t s) {
+                                 double* dots, hipStream_t s) {
   FusedArgs a{};
   a.x = x;
   a.y = y;
   a.g = (const float*)op.g;
   a.mu = (const float*)op.mu;
   a.inv = (const float*)op.inv;
-  a.ldx = (int)ldx;
-  a.ldy = (int)ldy;
+  a.ldx = ldx;
+  a.ldy = ldy;
   a.rows = (int)op.rows;
   a.cols = (int)op.cols;
   a.form = form;
+  a.dots = dots;
   const double w = 2.0 * op.desc.radius + 1.0;
   a.omega = op.desc.ndim == 1 ? w : w * w;
-  launch_fused_m<1>(a, op.desc.radius, op.desc.ndim == 2, s);
+  launch_fused(a, op.desc.radius, op.desc.ndim == 2, s);
   return launch_status();
 }
 

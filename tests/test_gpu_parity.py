@@ -500,6 +500,37 @@ def test_gf_one_column_all_forms_edges(gsf, shape, radius, prec):
         assert not yw[:, 0].any() and not yw[:, 1].any()
 
 
+@pytest.mark.parametrize("radius", [1, 3, 6, 8])
+@pytest.mark.parametrize("shape", [(3, 4), (9, 7), (40, 223), (33, 224), (21, 225), (17, 226), (50, 240), (8, 449),
+                                   (130, 500), (1030, 12), (700,), (1793,)])
+def test_gf_one_column_strips(gsf, shape, radius):
+    """The one-pass GF apply on contiguous columns where its strips and chunks
+    begin and end: widths of one strip's outputs and one column more or less,
+    every remainder by the four columns of a lane, strips off the grid on one
+    or both sides, odd chunk heights, rows too few for the straight-line part;
+    all four forms, and the CG filter (whose p^T q the apply sums), against the
+    oracle, and against the element-by-element form (strided columns)."""
+    import torch
+    rng = np.random.default_rng(70 + radius)
+    g = _round(rng.uniform(0.0, 1.0, shape), gsf.F32, gsf)
+    op = gsf.Operator("gf", shape, _torch(g.ravel(), gsf.F32, gsf), radius=radius, eps=1e-2, prec=gsf.F32)
+    ref = oracle.build_operator("gf", g, radius, eps=1e-2)
+    x = _round(rng.standard_normal(op.n), gsf.F32, gsf)
+    xd = _torch(x, gsf.F32, gsf)
+    wide = torch.zeros((op.n, 2), device="cuda")
+    wide[:, 0] = xd
+    for form in (gsf.FORM_N, gsf.FORM_LSYM, gsf.FORM_RW, gsf.FORM_L):
+        y = op.apply(xd.reshape(-1, 1), form).ravel()
+        assert torch.equal(op.apply(wide[:, 0:1], form).ravel(), y)
+        r = ref.apply(form, x)
+        e = np.linalg.norm(y.cpu().numpy() - r) / max(np.linalg.norm(r), np.linalg.norm(x))
+        assert e <= TOL[gsf.F32], (form, e)
+    y, info = op.cg_filter(_torch(g.ravel(), gsf.F32, gsf), 5)
+    r, rinfo = oracle.cg_filter(ref, g.ravel(), 5, data_prec="f32")
+    e = rel(y.cpu().numpy(), r)
+    assert info.iters == rinfo.iters and e <= TOL[gsf.F32], e
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 def test_lobpcg_soft_locking_parity(gsf, prec):
     """LOBPCG to a tolerance, where columns reach it at different steps and
