@@ -445,6 +445,28 @@ def test_cg_1d_small_and_large_paths(gsf, n, prec):
     np.testing.assert_allclose(y.cpu().numpy(), c, rtol=1e-6 if prec == 0 else 1e-15)
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("radius", [1, 2, 3, 5, 6, 8])
+@pytest.mark.parametrize("n", [2, 63, 65, 1024, 1025, 2048, 2049, 4096, 4097, 8191])
+def test_cg_1d_one_workgroup_forms(gsf, n, radius, prec):
+    """The one-workgroup CG where its forms meet: one wave or less, the lengths
+    at which a thread takes one, two, four or eight points, radii whose weights
+    stay in registers and radii whose do not, windows wider than the signal;
+    the same steps as the oracle, twice the same bits."""
+    import torch
+    x = _round(piecewise_constant_1d(n, 0.1, 11)[1] if n > 2 else np.array([0.2, 0.7]), prec, gsf)
+    op = gsf.Operator("bf", (n,), _torch(x, prec, gsf), radius=radius, sigma_d=3.0, sigma_r=0.2, prec=prec)
+    dp = "f32" if prec == 0 else "f64"
+    kmax = 1 if n == 2 else 8
+    rr = reference(lambda g: oracle.cg_filter(oracle.build_operator("bf", g, radius, 3.0, 0.2), g, kmax, data_prec=dp),
+                   x)
+    y, info = op.cg_filter(_torch(x, prec, gsf), kmax)
+    e = rel(y.cpu().numpy(), rr.y)
+    assert info.iters == rr.extra.iters == kmax
+    assert e <= (rr.gate if prec else TOL[0]), e
+    assert torch.equal(op.cg_filter(_torch(x, prec, gsf), kmax)[0], y)
+
+
 @pytest.mark.parametrize("offset", [0, 8])
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("shape", [(3, 5), (1, 1023), (64, 64), (91, 90), (725, 725)])
