@@ -358,6 +358,293 @@ struct GfCpl {
   static constexpr int v = M == 1 ? 2 : 1;
 };
 
+// ---------------------------------------------------------------------------
+// contiguous blocks of 4 or 8 columns
+// ---------------------------------------------------------------------------
+// The two passes of the apply for a point-major block whose M columns are all
+// of it: a row is one run of memory, read in 16-byte pieces by consecutive
+// threads, each of which keeps the FP64 vertical window sums of its pieces
+// whatever column they belong to.  (One grid column per lane, the kernel above,
+// spreads every load over 64 lines and, in groups of 4 FP64 columns of 8, uses
+// half of each.)  Four waves own a strip of 256 columns, 2r of them halo, and
+// rb rows; per row they add the entering row, put their sums into an LDS row,
+// and after one barrier (the rows alternate between two buffers) take the
+// horizontal window sums as (run of consecutive columns, block column) with a
+// sliding sum.  Per apply, r = 8: 1531 x 2047, FP64, m = 8 514 us (2.9 TB/s of
+// the two passes' least traffic), 794 as two groups of 4 columns of the kernel
+// above; FP32, m = 8 236 us, 335; 256 x 256, FP32, m = 4 27 us, 32.
+constexpr int kGfBlkThreads = 256;
+constexpr int kGfBlkCols = 256;  // halo columns of a strip
+
+template <typename T, int M>
+struct GfBlkShared {
+  static constexpr int kPitch = 2 * M + 2;  // doubles per column: runs of columns spread over the banks
+  double vs[2][kGfBlkCols * kPitch];
+  double2 rh[kGfBlkCols];                   // 1 / (points of the horizontal window) and its root
+};
+
+struct GfBlkArgs {
+  const void* in;    // stage 1: x; stage 2: (a, b)
+  const void* x;     // stage 2: x (L_sym and L forms)
+  int64_t ldx, ldy;  // elements between consecutive points of x and y
+  const void* g;
+  const void* dinv;  // stage 1: 1/sqrt(d), or nullptr (u = x)
+  const void* mu;
+  const void* inv;
+  void* out;         // stage 1: (a, b); stage 2: y
+  int rows, cols, r, rb;
+  int form;
+  double sromega;    // 1 / sqrt(|w|)
+};
+
+// DENSE: the pieces of `in` are aligned runs (else x has a row stride or
+// address of its own and is read by elements; the same sums).
+template <typename T, int M, int STAGE, bool SCALE, bool DENSE>
+__global__ void __launch_bounds__(kGfBlkThreads) gf_block_kernel(GfBlkArgs a) {
+  constexpr int V = 16 / (int)sizeof(T);      // elements of a piece
+  constexpr int K = STAGE == 1 ? M : 2 * M;   // elements of a point's row
+  constexpr int NP = K / V;                   // pieces per thread
+  constexpr int NC = STAGE == 1 ? 2 : 1;      // sums per element
+  constexpr int R = kGfBlkThreads / M;        // runs
+  constexpr int NO = (kGfBlkCols + R - 1) / R;  // most outputs of a run
+  constexpr int PITCH = GfBlkShared<T, M>::kPitch;
+  typedef T piece_t __attribute__((ext_vector_type(V)));
+  __shared__ GfBlkShared<T, M> sh;
+  const int t = threadIdx.x, r = a.r, ow = kGfBlkCols - 2 * r;
+  const int c0 = (int)blockIdx.x * ow, y0 = (int)blockIdx.y * a.rb;
+  const int y1 = y0 + a.rb < a.rows ? y0 + a.rb : a.rows;
+  const T* __restrict__ in = (const T*)a.in;
+  const T* __restrict__ g = (const T*)a.g;
+  const T* __restrict__ dinv = (const T*)a.dinv;
+
+  // piece role: strip column, element of its row, offset in an image row
+  int pcol[NP], pel[NP], goff[NP];
+  bool ok[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int e = (p * kGfBlkThreads + t) * V;
+    pcol[p] = e / K;
+    pel[p] = e % K;
+    const int gc = c0 - r + pcol[p];
+    ok[p] = gc >= 0 && gc < a.cols;
+    goff[p] = ok[p] ? gc : 0;
+  }
+  struct Row {
+    piece_t v[NP];
+    T g[NP], d[NP];
+  };
+  auto clamp_row = [&](int y) { return y < 0 ? 0 : (y >= a.rows ? a.rows - 1 : y); };
+  auto fetch = [&](int y) {
+    Row w;
+    const size_t base = (size_t)clamp_row(y) * a.cols;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if constexpr (DENSE) {
+        w.v[p] = *(const piece_t*)(in + base * K + ((size_t)goff[p] * K + pel[p]));
+      } else {
+#pragma unroll
+        for (int i = 0; i < V; ++i) w.v[p][i] = in[(base + goff[p]) * a.ldx + pel[p] + i];
+      }
+      if constexpr (STAGE == 1) {
+        w.g[p] = g[base + goff[p]];
+        if constexpr (SCALE) w.d[p] = dinv[base + goff[p]];
+      }
+    }
+    return w;
+  };
+  double s[NP][V][NC];
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s[p][i][c] = 0.0;
+  auto add_row = [&](const Row& w, bool sub) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        double u = (double)w.v[p][i];
+        if constexpr (STAGE == 1 && SCALE) u *= (double)w.d[p];
+        u = ok[p] ? u : 0.0;
+        s[p][i][0] += sub ? -u : u;
+        if constexpr (STAGE == 1) {
+          const double gu = ok[p] ? (double)w.g[p] * u : 0.0;
+          s[p][i][NC - 1] += sub ? -gu : gu;
+        }
+      }
+    }
+  };
+
+  // run role: block column j, output columns [cb, cb + nout) of the strip
+  const int L = (ow + R - 1) / R, j = t % M, cb = (t / M) * L;
+  int nout = ow - cb < L ? ow - cb : L;
+  if (c0 + cb + nout > a.cols) nout = a.cols - c0 - cb;
+  struct Epi {
+    T p[NO], q[NO];  // stage 1: mu, inv; stage 2: g, x
+  };
+  const bool need_x = a.form == GSF_FORM_LSYM || a.form == GSF_FORM_L;
+  auto pre = [&](int y) {
+    Epi e;
+    const size_t base = (size_t)clamp_row(y) * a.cols + c0 + cb;
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+      e.p[o] = e.q[o] = T(0);
+      if (o < nout) {
+        if constexpr (STAGE == 1) {
+          e.p[o] = ((const T*)a.mu)[base + o];
+          e.q[o] = ((const T*)a.inv)[base + o];
+        } else {
+          e.p[o] = g[base + o];
+          if (need_x) e.q[o] = ((const T*)a.x)[(base + o) * a.ldx + j];
+        }
+      }
+    }
+    return e;
+  };
+
+  {
+    const int c = c0 + t;  // output column t of the strip
+    const double rh = c < a.cols ? 1.0 / (double)win_count(c, a.cols, r) : 0.0;
+    sh.rh[t] = make_double2(rh, sqrt(rh));
+  }
+  // the window rows of the first output row, without its last
+  const int w0 = y0 - r < 0 ? 0 : y0 - r;
+  const int w1 = y0 + r - 1 < a.rows - 1 ? y0 + r - 1 : a.rows - 1;
+  Row enter = fetch(y0 + r), leave = fetch(y0 - r);
+  Epi epi = pre(y0);
+  for (int yy = w0; yy <= w1; yy += 2) {
+    const Row p = fetch(yy), q = fetch(yy + 1);
+    add_row(p, false);
+    if (yy + 1 <= w1) add_row(q, false);
+  }
+  for (int yo = y0; yo < y1; ++yo) {
+    const int ya = yo + r, yd = yo - r;
+    if (ya < a.rows) add_row(enter, false);
+    enter = fetch(ya + 1);
+    double* vs = sh.vs[(yo - y0) & 1];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if constexpr (STAGE == 1) {
+        double2* w = (double2*)(vs + pcol[p] * PITCH + 2 * pel[p]);
+#pragma unroll
+        for (int i = 0; i < V; ++i) w[i] = make_double2(s[p][i][0], s[p][i][NC - 1]);
+      } else {
+        double2* w = (double2*)(vs + pcol[p] * PITCH + pel[p]);
+#pragma unroll
+        for (int i = 0; i < V; i += 2) w[i / 2] = make_double2(s[p][i][0], s[p][i + 1][0]);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (nout > 0) {
+      const int vc = (ya < a.rows ? ya : a.rows - 1) - (yd < 0 ? 0 : yd) + 1;
+      const double rv = 1.0 / (double)vc, srv = sqrt(rv);
+      const double* v = vs + cb * PITCH + 2 * j;
+      double a0 = 0.0, a1 = 0.0;
+#pragma unroll 4
+      for (int h = 0; h < 2 * r; ++h) {
+        const double2 w = *(const double2*)(v + h * PITCH);
+        a0 += w.x;
+        a1 += w.y;
+      }
+      const double* vr = v + 2 * r * PITCH;
+      const size_t base = (size_t)yo * a.cols + c0 + cb;
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        if (o < nout) {
+          const double2 w = *(const double2*)(vr + o * PITCH);
+          a0 += w.x;
+          a1 += w.y;
+          const double2 h = sh.rh[cb + o];
+          const double rc = rv * h.x;
+          if constexpr (STAGE == 1) {
+            const double mk = (double)epi.p[o];
+            const double mean_u = a0 * rc, mean_gu = a1 * rc;
+            const double av = (mean_gu - mk * mean_u) * (double)epi.q[o];
+            typedef T pair_t __attribute__((ext_vector_type(2)));
+            ((pair_t*)a.out)[(base + o) * M + j] = pair_t{(T)av, (T)(mean_u - av * mk)};
+          } else {
+            const double gfu = (double)epi.p[o] * a0 + a1, xi = (double)epi.q[o];
+            double out;
+            if (a.form == GSF_FORM_RW) {
+              out = gfu * rc;
+            } else if (a.form == GSF_FORM_L) {
+              out = (xi - gfu * rc) * (a.sromega * a.sromega / rc);  // d (x - GF(x)), d = N/|w|
+            } else {
+              const double nx = gfu * ((srv * h.y) * a.sromega);  // (g sum a + sum b) / sqrt(N_i |w|)
+              out = a.form == GSF_FORM_LSYM ? xi - nx : nx;
+            }
+            ((T*)a.out)[(base + o) * a.ldy + j] = (T)out;
+          }
+          const double2 l = *(const double2*)(v + o * PITCH);
+          a0 -= l.x;
+          a1 -= l.y;
+        }
+      }
+    }
+    epi = pre(yo + 1);
+    if (yd >= 0) add_row(leave, true);
+    leave = fetch(yd + 1);
+  }
+}
+
+// Rows per workgroup: the strips and chunks fill the chip's workgroup slots
+// (two per CU by registers and LDS) once, down to 4 rows.
+template <typename T, int M>
+void gf_apply_block(const Operator& op, T* ab, int form, const T* x, int64_t ldx, T* y, int64_t ldy,
+                    hipStream_t s) {
+  constexpr int kGroups = 512, kMinRows = 4;
+  GfBlkArgs a{};
+  a.rows = (int)op.rows;
+  a.cols = (int)op.cols;
+  a.r = op.desc.radius;
+  a.form = form;
+  const double w = 2.0 * op.desc.radius + 1.0;
+  a.sromega = 1.0 / sqrt(op.desc.ndim == 1 ? w : w * w);
+  const int ow = kGfBlkCols - 2 * a.r, strips = (a.cols + ow - 1) / ow;
+  const int chunks = strips < kGroups ? kGroups / strips : 1;
+  a.rb = (a.rows + chunks - 1) / chunks;
+  if (a.rb < kMinRows) a.rb = kMinRows;
+  const dim3 grid((unsigned)strips, (unsigned)((a.rows + a.rb - 1) / a.rb));
+  a.g = op.g;
+  a.mu = op.mu;
+  a.inv = op.inv;
+  a.x = x;
+  a.in = x;
+  a.out = ab;
+  a.ldx = ldx;
+  a.ldy = ldy;
+  const bool dense = ldx == M && (uintptr_t)x % 16 == 0;
+  if (form == GSF_FORM_RW || form == GSF_FORM_L) {
+    if (dense) gf_block_kernel<T, M, 1, false, true><<<grid, kGfBlkThreads, 0, s>>>(a);
+    else gf_block_kernel<T, M, 1, false, false><<<grid, kGfBlkThreads, 0, s>>>(a);
+  } else {
+    a.dinv = op.diag;
+    if (dense) gf_block_kernel<T, M, 1, true, true><<<grid, kGfBlkThreads, 0, s>>>(a);
+    else gf_block_kernel<T, M, 1, true, false><<<grid, kGfBlkThreads, 0, s>>>(a);
+  }
+  a.in = ab;
+  a.out = y;
+  gf_block_kernel<T, M, 2, false, true><<<grid, kGfBlkThreads, 0, s>>>(a);
+}
+
+// Blocks of 4 and 8 columns take gf_block_kernel, other sizes gf_box_kernel.
+// So do tall images that fill less than half of a strip (8192 x 64, FP32,
+// m = 4 / 8, r = 8: 48 / 79 us against 69 / 103; at 96 x 96, where latency and
+// not the idle columns counts, 31 / 43 against 25 / 34) and short signals
+// (4096 samples, FP64, m = 4: 10.3 against 10.9 us; 200000: 30 against 19).
+// Eight FP64 columns, two calls of the other kernel, always take this one
+// (8192 x 64: 169 against 116 us, 4096 samples 16.7 against 12.0).
+template <typename T>
+bool gf_block_pays(const Operator& op, int m) {
+  if (m != 4 && m != 8) return false;
+  if (sizeof(T) == 8 && m == 8) return true;
+  if (op.desc.ndim == 1) return op.n >= 65536;
+  return op.cols >= kGfBlkCols / 2 || op.n < (1 << 17);
+}
+
 double gf_omega(const Operator& op) {
   const double w = 2.0 * op.desc.radius + 1.0;
   return op.desc.ndim == 1 ? w : w * w;
@@ -384,6 +671,11 @@ template <typename T>
 void gf_apply_typed(const Operator& op, void* scratch, int form, int m, const T* x, int64_t ldx, T* y, int64_t ldy,
                     hipStream_t s) {
   T* ab = (T*)scratch;
+  if (gf_block_pays<T>(op, m)) {
+    if (m == 8) gf_apply_block<T, 8>(op, ab, form, x, ldx, y, ldy, s);
+    else gf_apply_block<T, 4>(op, ab, form, x, ldx, y, ldy, s);
+    return;
+  }
   int c = 0;
   while (c < m) {
     const int left = m - c;

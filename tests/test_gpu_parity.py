@@ -554,6 +554,38 @@ def test_gf_one_column_strips(gsf, shape, radius):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("m", [4, 8])
+@pytest.mark.parametrize("shape,radius", [((3, 2), 8), ((9, 239), 8), ((40, 240), 8), ((33, 241), 3), ((70, 255), 1),
+                                          ((21, 513), 6), ((2100, 64), 2), ((66000,), 5), ((500,), 8), ((1, 300), 4)])
+def test_gf_block_strips(gsf, shape, radius, m, prec):
+    """The GF apply of a block of 4 or 8 columns where its strips and chunks
+    begin and end: a strip's 256 - 2r output columns and one more or less, a
+    grid smaller than the window, several strips, tall narrow images and
+    signals on both sides of the choice of kernel; all four forms against the
+    oracle, and bit for bit against columns of a wider array."""
+    import torch
+    rng = np.random.default_rng(90 + radius)
+    g = _round(rng.uniform(0.0, 1.0, shape), prec, gsf)
+    op = gsf.Operator("gf", shape, _torch(g.ravel(), prec, gsf), radius=radius, eps=1e-2, prec=prec)
+    ref = oracle.build_operator("gf", g, radius, eps=1e-2)
+    x = _round(rng.standard_normal((op.n, m)), prec, gsf)
+    xd = _torch(x, prec, gsf)
+    wide = torch.zeros((op.n, m + 3), dtype=xd.dtype, device="cuda")
+    wide[:, 1:1 + m] = xd
+    for form in (gsf.FORM_N, gsf.FORM_LSYM, gsf.FORM_RW, gsf.FORM_L):
+        y = op.apply(xd, form)
+        out = torch.zeros_like(wide)
+        op.apply(wide[:, 1:1 + m], form, out=out[:, 2:2 + m])
+        assert torch.equal(out[:, 2:2 + m], y)
+        assert not out[:, :2].any() and not out[:, 2 + m:].any()
+        y = y.cpu().numpy()
+        for j in (0, m - 1):
+            r = ref.apply(form, x[:, j])
+            e = np.linalg.norm(y[:, j] - r) / max(np.linalg.norm(r), np.linalg.norm(x[:, j]))
+            assert e <= TOL[prec], (form, j, e)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 def test_lobpcg_soft_locking_parity(gsf, prec):
     """LOBPCG to a tolerance, where columns reach it at different steps and
     are soft-locked (their W columns count as zero): the GPU stops at the
