@@ -38,7 +38,7 @@ gsf_status launch_rg_bf(const Operator& op, int mode, const void* g, const void*
                         int* nparts, hipStream_t s);
 gsf_status launch_bscale(const Operator& op, int m, const void* in, void* out, int divide, hipStream_t s);
 gsf_status launch_bcg(int kind, const Operator& op, int m, void* z, void* r, void* p, void* q, double* partials,
-                      BlockCgState* st, hipStream_t s);
+                      BlockCgState* st, int k, hipStream_t s);
 gsf_status launch_bcg_state_init(BlockCgState* st, const BlockCgState& v, hipStream_t s);
 gsf_status launch_srgb_to_lab(int prec, int64_t n, const void* rgb, void* lab, hipStream_t s);
 bool launch_bf_apply_joint(const Operator& op, int form, int m, const void* x, int64_t ldx, void* y, int64_t ldy,
@@ -691,15 +691,18 @@ gsf_status gsf_cg_filter_block(const gsf_operator* h, int m, const void* x0, voi
   GSF_TRY(launch_bcg_state_init(w.st, init, s));
   GSF_TRY(launch_bscale(op, m, x0, w.z, 0, s));
   GSF_TRY(apply_any(op, GSF_FORM_LSYM, m, w.z, m, w.r, m, nullptr, nullptr, s));
-  GSF_TRY(launch_bcg(0, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, s));
+  GSF_TRY(launch_bcg(0, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, 0, s));
   Poller poll(s, &w.st->active, info != nullptr && tol > 0.0);
+  int steps = 0;
   for (int k = 1; k <= kmax; ++k) {
     if (!poll.keep_going(k - 1)) break;
-    GSF_TRY(launch_bcg(1, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, s));
+    GSF_TRY(launch_bcg(1, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, k, s));
     GSF_TRY(apply_any(op, GSF_FORM_LSYM, m, w.p, m, w.q, m, nullptr, nullptr, s));
-    GSF_TRY(launch_bcg(2, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, s));
-    GSF_TRY(launch_bcg(3, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, s));
+    GSF_TRY(launch_bcg(2, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, k, s));
+    GSF_TRY(launch_bcg(3, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, k, s));
+    steps = k;
   }
+  if (steps > 0) GSF_TRY(launch_bcg(4, op, m, w.z, w.r, w.p, w.q, w.partials, w.st, steps, s));
   GSF_TRY(launch_bscale(op, m, w.z, x_out, 1, s));
   if (info == nullptr) return GSF_OK;
   BlockCgState host{};

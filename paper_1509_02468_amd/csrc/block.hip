@@ -9,6 +9,7 @@
 // workgroup order by a one-workgroup kernel.
 #include <cmath>
 
+#include "cg_step.h"
 #include "gsf_internal.h"
 #include "solver_state.h"
 
@@ -76,6 +77,7 @@ __global__ void __launch_bounds__(kThreads) bcg_init_final_kernel(const double* 
       const double rho = t[2 * c];
       s.rho = rho;
       s.rho0 = rho;
+      s.rhob[1] = rho;
       s.res0 = sqrt(rho > 0.0 ? rho : 0.0);
       s.floor = s.tau * s.tau * t[2 * c + 1];
       s.tol2 = s.tol > 0.0 ? s.tol * s.tol * rho : -1.0;
@@ -95,25 +97,111 @@ __global__ void __launch_bounds__(kThreads) bcg_init_final_kernel(const double* 
   }
 }
 
-// p_c = r_c (first step of column c) or r_c + beta_c p_c; stopped columns keep p
+// Groups of whole 16-byte chunks that hold whole points: element e of a group
+// belongs to column e % M.
 template <typename T, int M>
-__global__ void __launch_bounds__(kThreads) bcg_pupdate_kernel(const T* __restrict__ r, T* __restrict__ p, int64_t n,
-                                                               const BlockCgState* st) {
+struct PointGroup {
+  typedef typename Chunk<T>::type V;
+  static constexpr int vn = Chunk<T>::n;
+  static constexpr int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
+  static constexpr int nv = M / gcd(M, vn);  // chunks per group
+  static constexpr int elems = nv * vn;
+  static constexpr int points = elems / M;
+  static __device__ __forceinline__ void load(const T* p, int64_t g, T (&e)[elems]) {
+    const V* c = (const V*)p + g * nv;
+#pragma unroll
+    for (int v = 0; v < nv; ++v) {
+      const V w = c[v];
+#pragma unroll
+      for (int i = 0; i < vn; ++i) e[v * vn + i] = w[i];
+    }
+  }
+  static __device__ __forceinline__ void store(T* p, int64_t g, const T (&e)[elems]) {
+    V* c = (V*)p + g * nv;
+#pragma unroll
+    for (int v = 0; v < nv; ++v) {
+      V w;
+#pragma unroll
+      for (int i = 0; i < vn; ++i) w[i] = e[v * vn + i];
+      c[v] = w;
+    }
+  }
+};
+
+// The three vector phases of a step, bound by HBM (or the last-level cache):
+// they take groups of 16-byte chunks where the vectors are aligned and single
+// points where not and for the remainder, and every workgroup sums the partials
+// that it needs itself, in a fixed order, so that no launch of one workgroup
+// stands between them (as the single-column step does; workgroup 0 records the
+// scalars, r^T r by step parity, and a column's stop is the same decision in
+// all).  1024^2, m = 3, FP32: direction, product and update with their scalars
+// 36 us per step in three launches, 46 in five that took the elements one by
+// one.
+
+// step k: per active column k = 1: p = r; k > 1: rho and r^T r_old from the
+// last update's partials, the tests before step k, beta = (rho - r^T r_old) /
+// rho_old, p = r + beta p; stopped columns keep p
+template <typename T, int M>
+__global__ void __launch_bounds__(kThreads) bcg_pbeta_kernel(const T* __restrict__ r, T* __restrict__ p, int64_t n,
+                                                             const double* __restrict__ upd, int nupd,
+                                                             BlockCgState* st, int k) {
+  __shared__ double red[2 * M * 16];
+  __shared__ double bc[2 * M];
+  typedef PointGroup<T, M> G;
   if (!st->active) return;
   T beta[M];
-  bool on[M], first[M];
+  bool on[M];
 #pragma unroll
   for (int c = 0; c < M; ++c) {
     on[c] = st->col[c].active != 0;
-    first[c] = st->col[c].k == 1;
-    beta[c] = (T)st->col[c].beta;
+    beta[c] = T(0);
   }
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+  if (k > 1) {
+    double t[2 * M];
+    reduce_all<2 * M>(upd, nupd, t, red, bc);
 #pragma unroll
     for (int c = 0; c < M; ++c) {
       if (!on[c]) continue;
-      p[i * M + c] = first[c] ? r[i * M + c] : r[i * M + c] + beta[c] * p[i * M + c];
+      CgState& s = st->col[c];
+      const double rho = t[2 * c];
+      const bool stop_bd = !(__builtin_isfinite(rho) && rho > s.floor);
+      const bool stop_tol = !stop_bd && s.tol2 > 0.0 && rho <= s.tol2;
+      const double b = (rho - t[2 * c + 1]) / s.rhob[(k - 1) & 1];
+      on[c] = !(stop_bd || stop_tol);
+      beta[c] = (T)b;
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        s.rho = rho;
+        s.rhob[k & 1] = rho;
+        s.beta = b;
+        if (stop_bd) s.status = GSF_EBREAKDOWN;
+        if (!on[c]) s.active = 0;
+      }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) any_active(st, M);
+  }
+  bool some = false;
+#pragma unroll
+  for (int c = 0; c < M; ++c) some = some || on[c];
+  if (!some) return;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t ng = chunk_aligned(r, p) ? n / G::points : 0;
+  for (int64_t g = t0; g < ng; g += stride) {
+    T re[G::elems], pe[G::elems];
+    G::load(r, g, re);
+    G::load(p, g, pe);
+#pragma unroll
+    for (int e = 0; e < G::elems; ++e) {
+      const int c = e % M;
+      const T v = k == 1 ? re[e] : re[e] + beta[c] * pe[e];
+      pe[e] = on[c] ? v : pe[e];
+    }
+    G::store(p, g, pe);
+  }
+  for (int64_t i = ng * G::points + t0; i < n; i += stride) {
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+      if (!on[c]) continue;
+      p[i * M + c] = k == 1 ? r[i * M + c] : r[i * M + c] + beta[c] * p[i * M + c];
     }
   }
 }
@@ -123,12 +211,21 @@ template <typename T, int M>
 __global__ void __launch_bounds__(kThreads) bdot_kernel(const T* __restrict__ p, const T* __restrict__ q, int64_t n,
                                                         double* __restrict__ partials, const BlockCgState* st) {
   __shared__ double red[M * 16];
+  typedef PointGroup<T, M> G;
   if (!st->active) return;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[M];
 #pragma unroll
   for (int c = 0; c < M; ++c) v[c] = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+  const int64_t ng = chunk_aligned(p, q) ? n / G::points : 0;
+  for (int64_t g = t0; g < ng; g += stride) {
+    T pe[G::elems], qe[G::elems];
+    G::load(p, g, pe);
+    G::load(q, g, qe);
+#pragma unroll
+    for (int e = 0; e < G::elems; ++e) v[e % M] += (double)pe[e] * (double)qe[e];
+  }
+  for (int64_t i = ng * G::points + t0; i < n; i += stride) {
 #pragma unroll
     for (int c = 0; c < M; ++c) v[c] += (double)p[i * M + c] * (double)q[i * M + c];
   }
@@ -139,52 +236,70 @@ __global__ void __launch_bounds__(kThreads) bdot_kernel(const T* __restrict__ p,
   }
 }
 
-// one workgroup: per active column p^T q, alpha = rho / p^T q, breakdown test
-template <int M>
-__global__ void __launch_bounds__(kThreads) bcg_alpha_kernel(const double* __restrict__ partials, int nparts,
-                                                             BlockCgState* st) {
-  __shared__ double red[M * 16];
-  if (!st->active) return;
-  double t[M];
-  reduce_partials<M>(partials, nparts, M, t, red);
-  if (threadIdx.x == 0) {
-    for (int c = 0; c < M; ++c) {
-      CgState& s = st->col[c];
-      if (!s.active) continue;
-      const double pq = t[c];
-      s.pq = pq;
-      if (!(__builtin_isfinite(pq) && pq > 0.0)) {
-        s.status = GSF_EBREAKDOWN;
-        s.active = 0;
-      } else {
-        s.alpha = s.rho / pq;
-      }
-    }
-    any_active(st, M);
-  }
-}
-
-// active columns: z += alpha p; r -= alpha q; partials of r_new^T r_new and
-// r_new^T r_old
+// step k: per active column p^T q from the partials, the breakdown test,
+// alpha = rho / p^T q, z += alpha p, r -= alpha q; partials of r_new^T r_new
+// and r_new^T r_old into upd (not the buffer that dots is read from)
 template <typename T, int M>
 __global__ void __launch_bounds__(kThreads) bcg_update_kernel(T* __restrict__ z, T* __restrict__ r,
                                                               const T* __restrict__ p, const T* __restrict__ q,
-                                                              int64_t n, double* __restrict__ partials,
-                                                              const BlockCgState* st) {
+                                                              int64_t n, const double* __restrict__ dots, int ndots,
+                                                              double* __restrict__ upd, BlockCgState* st, int k) {
   __shared__ double red[2 * M * 16];
+  __shared__ double bc[M];
+  typedef PointGroup<T, M> G;
   if (!st->active) return;
   T alpha[M];
   bool on[M];
 #pragma unroll
+  for (int c = 0; c < M; ++c) on[c] = st->col[c].active != 0;
+  double t[M];
+  reduce_all<M>(dots, ndots, t, red, bc);
+#pragma unroll
   for (int c = 0; c < M; ++c) {
-    on[c] = st->col[c].active != 0;
-    alpha[c] = (T)st->col[c].alpha;
+    alpha[c] = T(0);
+    if (!on[c]) continue;
+    CgState& s = st->col[c];
+    const double pq = t[c];
+    on[c] = __builtin_isfinite(pq) && pq > 0.0;
+    const double a = s.rhob[k & 1] / pq;
+    alpha[c] = (T)a;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      s.pq = pq;
+      if (on[c]) {
+        s.alpha = a;
+        s.iters = k;
+        s.k = k + 1;
+      } else {
+        s.status = GSF_EBREAKDOWN;
+        s.active = 0;
+      }
+    }
   }
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  if (blockIdx.x == 0 && threadIdx.x == 0) any_active(st, M);
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[2 * M];
 #pragma unroll
-  for (int k = 0; k < 2 * M; ++k) v[k] = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+  for (int c = 0; c < 2 * M; ++c) v[c] = 0.0;
+  const int64_t ng = chunk_aligned(z, r, p, q) ? n / G::points : 0;
+  for (int64_t g = t0; g < ng; g += stride) {
+    T ze[G::elems], re[G::elems], pe[G::elems], qe[G::elems];
+    G::load(z, g, ze);
+    G::load(p, g, pe);
+    G::load(r, g, re);
+    G::load(q, g, qe);
+#pragma unroll
+    for (int e = 0; e < G::elems; ++e) {
+      const int c = e % M;
+      const T zn = ze[e] + alpha[c] * pe[e], ro = re[e], rn = ro - alpha[c] * qe[e];
+      ze[e] = on[c] ? zn : ze[e];
+      re[e] = on[c] ? rn : ro;
+      v[2 * c] += (double)re[e] * (double)re[e];
+      v[2 * c + 1] += (double)re[e] * (double)ro;
+    }
+    G::store(z, g, ze);
+    G::store(r, g, re);
+  }
+  for (int64_t i = ng * G::points + t0; i < n; i += stride) {
 #pragma unroll
     for (int c = 0; c < M; ++c) {
       if (!on[c]) continue;
@@ -199,29 +314,24 @@ __global__ void __launch_bounds__(kThreads) bcg_update_kernel(T* __restrict__ z,
   block_sum<2 * M>(v, red);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < 2 * M; ++k) partials[(size_t)blockIdx.x * 2 * M + k] = v[k];
+    for (int c = 0; c < 2 * M; ++c) upd[(size_t)blockIdx.x * 2 * M + c] = v[c];
   }
 }
 
-// one workgroup: per active column rho_new, beta = (rho_new - r_new.r_old) /
-// rho_old, the step count and the tests that precede the next step
+// one workgroup after the last step: the final residuals and their tests
 template <int M>
-__global__ void __launch_bounds__(kThreads) bcg_beta_kernel(const double* __restrict__ partials, int nparts,
-                                                            BlockCgState* st) {
+__global__ void __launch_bounds__(kThreads) bcg_close_kernel(const double* __restrict__ upd, int nupd,
+                                                             BlockCgState* st) {
   __shared__ double red[2 * M * 16];
   if (!st->active) return;
   double t[2 * M];
-  reduce_partials<2 * M>(partials, nparts, 2 * M, t, red);
+  reduce_partials<2 * M>(upd, nupd, 2 * M, t, red);
   if (threadIdx.x == 0) {
     for (int c = 0; c < M; ++c) {
       CgState& s = st->col[c];
       if (!s.active) continue;
-      const double rho_old = s.rho;
       const double rho = t[2 * c];
-      s.beta = (rho - t[2 * c + 1]) / rho_old;
       s.rho = rho;
-      s.iters = s.k;
-      s.k = s.k + 1;
       if (!(__builtin_isfinite(rho) && rho > s.floor)) {
         s.status = GSF_EBREAKDOWN;
         s.active = 0;
@@ -304,42 +414,55 @@ LabParams lab_params() {
   return p;
 }
 
+// The partials' buffer holds 2m values per vector workgroup (and is a multiple
+// of 32 values): the product's workgroups, m values each, take its first
+// quarter, the update's, 2m each, the rest.
+struct BcgGrid {
+  int nb, ndot, nupd;
+};
+BcgGrid bcg_grid(int64_t n) {
+  const int nb = vec_blocks(n), nd = nb > 1 ? nb / 2 : 1;
+  return BcgGrid{nb, nd, nb > 1 ? (2 * nb - nd) / 2 : 1};
+}
+
 template <typename T, int M>
-void launch_bcg_m(int kind, const Operator& op, void* z, void* r, void* p, void* q, double* partials, int nparts,
-                  BlockCgState* st, hipStream_t s) {
-  const int nb = vec_blocks(op.n);
+void launch_bcg_m(int kind, const Operator& op, void* z, void* r, void* p, void* q, double* partials,
+                  BlockCgState* st, int k, hipStream_t s) {
+  const BcgGrid g = bcg_grid(op.n);
+  double* upd = partials + (size_t)g.ndot * M;
   switch (kind) {
     case 0:
-      bcg_init_kernel<T, M><<<nb, kThreads, 0, s>>>((const T*)z, (T*)r, op.n, partials);
-      bcg_init_final_kernel<M><<<1, kThreads, 0, s>>>(partials, nb, st);
+      bcg_init_kernel<T, M><<<g.nb, kThreads, 0, s>>>((const T*)z, (T*)r, op.n, partials);
+      bcg_init_final_kernel<M><<<1, kThreads, 0, s>>>(partials, g.nb, st);
       break;
     case 1:
-      bcg_pupdate_kernel<T, M><<<nb, kThreads, 0, s>>>((const T*)r, (T*)p, op.n, st);
+      bcg_pbeta_kernel<T, M><<<g.nb, kThreads, 0, s>>>((const T*)r, (T*)p, op.n, upd, g.nupd, st, k);
       break;
     case 2:
-      bdot_kernel<T, M><<<nb, kThreads, 0, s>>>((const T*)p, (const T*)q, op.n, partials, st);
-      bcg_alpha_kernel<M><<<1, kThreads, 0, s>>>(partials, nb, st);
+      bdot_kernel<T, M><<<g.ndot, kThreads, 0, s>>>((const T*)p, (const T*)q, op.n, partials, st);
+      break;
+    case 3:
+      bcg_update_kernel<T, M><<<g.nupd, kThreads, 0, s>>>((T*)z, (T*)r, (const T*)p, (const T*)q, op.n, partials,
+                                                          g.ndot, upd, st, k);
       break;
     default:
-      bcg_update_kernel<T, M><<<nb, kThreads, 0, s>>>((T*)z, (T*)r, (const T*)p, (const T*)q, op.n, partials, st);
-      bcg_beta_kernel<M><<<1, kThreads, 0, s>>>(partials, nb, st);
+      bcg_close_kernel<M><<<1, kThreads, 0, s>>>(upd, g.nupd, st);
       break;
   }
-  (void)nparts;
 }
 
 template <typename T>
 void launch_bcg_t(int kind, const Operator& op, int m, void* z, void* r, void* p, void* q, double* partials,
-                  BlockCgState* st, hipStream_t s) {
+                  BlockCgState* st, int k, hipStream_t s) {
   switch (m) {
-    case 1: launch_bcg_m<T, 1>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    case 2: launch_bcg_m<T, 2>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    case 3: launch_bcg_m<T, 3>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    case 4: launch_bcg_m<T, 4>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    case 5: launch_bcg_m<T, 5>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    case 6: launch_bcg_m<T, 6>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    case 7: launch_bcg_m<T, 7>(kind, op, z, r, p, q, partials, 0, st, s); break;
-    default: launch_bcg_m<T, 8>(kind, op, z, r, p, q, partials, 0, st, s); break;
+    case 1: launch_bcg_m<T, 1>(kind, op, z, r, p, q, partials, st, k, s); break;
+    case 2: launch_bcg_m<T, 2>(kind, op, z, r, p, q, partials, st, k, s); break;
+    case 3: launch_bcg_m<T, 3>(kind, op, z, r, p, q, partials, st, k, s); break;
+    case 4: launch_bcg_m<T, 4>(kind, op, z, r, p, q, partials, st, k, s); break;
+    case 5: launch_bcg_m<T, 5>(kind, op, z, r, p, q, partials, st, k, s); break;
+    case 6: launch_bcg_m<T, 6>(kind, op, z, r, p, q, partials, st, k, s); break;
+    case 7: launch_bcg_m<T, 7>(kind, op, z, r, p, q, partials, st, k, s); break;
+    default: launch_bcg_m<T, 8>(kind, op, z, r, p, q, partials, st, k, s); break;
   }
 }
 
@@ -369,14 +492,14 @@ gsf_status launch_bscale(const Operator& op, int m, const void* in, void* out, i
   return launch_status();
 }
 
-// kind: 0 init (r <- -r, per-column rho0 and floor), 1 p update, 2 p^T q and
-// alpha, 3 z / r update and beta
+// kind: 0 init (r <- -r, per-column rho0 and floor); of step k: 1 beta and the
+// p update, 2 p^T q, 3 alpha and the z / r update; 4 after the last step
 gsf_status launch_bcg(int kind, const Operator& op, int m, void* z, void* r, void* p, void* q, double* partials,
-                      BlockCgState* st, hipStream_t s) {
+                      BlockCgState* st, int k, hipStream_t s) {
   if (op.desc.prec == GSF_F32)
-    launch_bcg_t<float>(kind, op, m, z, r, p, q, partials, st, s);
+    launch_bcg_t<float>(kind, op, m, z, r, p, q, partials, st, k, s);
   else
-    launch_bcg_t<double>(kind, op, m, z, r, p, q, partials, st, s);
+    launch_bcg_t<double>(kind, op, m, z, r, p, q, partials, st, k, s);
   return launch_status();
 }
 

@@ -251,3 +251,27 @@ def test_block_filters_on_gf_operator(gsf, prec):
     print(f"GF block CG prec={prec}: {e:.2e} (band {rr.band:.1e})")
     assert e <= (rr.gate if prec == gsf.F64 else 1e-5)
     assert all(i.iters == 12 for i in infos)
+
+
+@pytest.mark.parametrize("offset", [0, 8])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n", [3, 255, 257, 511, 1030])
+def test_block_cg_groups(gsf, n, prec, offset):
+    """The block CG's vector phases in groups of whole 16-byte chunks: every
+    block width with every remainder, one and two workgroups of partials, a
+    workspace off the 16-byte grid; each column against the single-column
+    filter (the same steps; FP64 1e-12 as above, FP32 1e-5)."""
+    import torch
+    rng = np.random.default_rng(n)
+    g = rng.uniform(0.0, 1.0, n)
+    op = gsf.Operator("bf", (n,), _dev(g, prec, gsf), 1, 2.0, 0.2, prec=prec)
+    for m in range(1, 9):
+        X = _dev(rng.standard_normal((n, m)), prec, gsf)
+        kmax = 1 if n == 3 else 6
+        need = op.workspace(gsf.METHOD_CG, m).numel()
+        ws = torch.empty(need + 16, dtype=torch.uint8, device="cuda")[offset:offset + need]
+        Y, infos = op.cg_filter_block(X, kmax, ws=ws)
+        for c in range(m):
+            y, info = op.cg_filter(X[:, c].contiguous(), kmax)
+            assert infos[c].iters == info.iters == kmax and infos[c].status == info.status
+            assert rel(Y[:, c].cpu().numpy(), y.cpu().numpy()) <= (1e-12 if prec else 1e-5), (m, c)
