@@ -320,6 +320,21 @@ def test_lobpcg_filter_parity(gsf, prec, case, m, k, constraint):
     check_lobpcg(info, y.cpu().numpy(), ref, m, prec, f"{case} m={m} k={k} c={constraint}")
 
 
+@pytest.mark.parametrize("prec,m", [(0, 1), (0, 2), (1, 1)])
+@pytest.mark.parametrize("shape", [(23, 45), (46, 29), (25, 41), (33, 31)])
+@pytest.mark.parametrize("constraint", [False, True])
+def test_lobpcg_narrow_block_groups(gsf, shape, prec, m, constraint):
+    """LOBPCG with rows of less than 16 bytes, whose update takes several points
+    at a time: every remainder of the point count, all three basis widths
+    (first, second and later steps), and the projection of narrow rows."""
+    x = _round(scene_2d(*shape, 0.05, 9)[1], prec, gsf)
+    p = dict(radius=2, sigma_d=2.0, sigma_r=0.2)
+    op = gsf.Operator("bf", shape, _torch(x.ravel(), prec, gsf), prec=prec, **p)
+    y, info = op.lobpcg_filter(_torch(x.ravel(), prec, gsf), m, 6, constraint=constraint)
+    ref = lobpcg_reference("bf", p, x, shape, m, 6, prec, constraint=constraint)
+    check_lobpcg(info, y.cpu().numpy(), ref, m, prec, f"{shape} m={m} c={constraint}")
+
+
 def test_lobpcg_identity_at_zero_steps(gsf):
     op, ref, x = _build(gsf, ("bf", (67, 130), 3), 1)
     y, info = op.lobpcg_filter(_torch(x, 1, gsf), 4, 0)
