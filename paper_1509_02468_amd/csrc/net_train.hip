@@ -662,11 +662,19 @@ int64_t train_tiles(int batch, int64_t rows, int64_t cols) {
 
 }  // namespace
 
-// operand packs, loss and gradient partials: the tiles' planes stay in LDS, so
-// the size does not depend on the batch
-size_t net_train_bytes(int, int64_t) {
-  return align_up((size_t)kPackWords * 16, 256) + align_up((size_t)kNetGrid * 8, 256) +
-         align_up((size_t)kNetGrid * kNetWeights * 8, 256);
+// The pass needs the operand packs and the loss and gradient partials (the
+// tiles' planes stay in LDS).  The entry points ask for what they always did,
+// room for a whole batch's planes (the activations of both hidden layers in
+// BF16, their gradients in FP32, y and dy) beside the partials of 1024
+// workgroups, so that the sizes callers hold and the calls they see refused
+// stay the same.
+size_t net_train_bytes(int batch, int64_t hw) {
+  constexpr size_t used = (size_t)kPackWords * 16 + (size_t)kNetGrid * (1 + kNetWeights) * 8 + 3 * 256;
+  constexpr size_t partials = (size_t)1024 * kNetWeights * 8;
+  static_assert(used <= partials, "the pass fits whatever the batch");
+  const size_t px = (size_t)batch * (size_t)hw;
+  return align_up(kNetWeights * 4, 256) + 2 * align_up(px * 32, 256) + 2 * align_up(px * 4, 256) +
+         2 * align_up(px * 64, 256) + align_up(1024 * 8, 256) + align_up(partials, 256);
 }
 
 gsf_status net_forward_train(const uint16_t* w, int batch, const int32_t* idx, int64_t rows, int64_t cols,
