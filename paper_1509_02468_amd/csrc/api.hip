@@ -59,11 +59,10 @@ gsf_status launch_cg_aupdate(const Operator& op, void* z, void* r, const void* p
                              int ndots, double* upd, CgState* st, int k, hipStream_t s);
 gsf_status launch_cg_close(const Operator& op, const double* upd, CgState* st, hipStream_t s);
 gsf_status launch_rg_init(const Operator& op, const void* x, void* r, double* partials, CgState* st, hipStream_t s);
-gsf_status launch_rg_s_beta(const Operator& op, const void* r, const void* r_old, void* sv, double* partials,
-                            CgState* st, hipStream_t s);
-gsf_status launch_rg_alpha(const double* partials, int nparts, CgState* st, hipStream_t s);
+gsf_status launch_rg_direction(const Operator& op, const void* r, const void* r_old, void* sv, void* p,
+                               double* partials, CgState* st, int k, hipStream_t s);
 gsf_status launch_rg_update(const Operator& op, void* x, void* r, void* r_old, const void* p, const void* q,
-                            const CgState* st, hipStream_t s);
+                            const double* partials, int nparts, CgState* st, int k, hipStream_t s);
 gsf_status launch_cg_update(const Operator& op, void* z, void* r, const void* p, const void* q, double* partials,
                             CgState* st, hipStream_t s);
 
@@ -1293,8 +1292,7 @@ gsf_status gsf_reguided_filter(const gsf_operator_desc* desc, int method, const 
   for (int k = 1; k <= kmax; ++k) {
     if (!poll.keep_going(k - 1)) break;
     if (k > 1) GSF_TRY(rebuild());
-    GSF_TRY(launch_rg_s_beta(op, w.r, w.r_old, w.s, w.partials, w.st, s));
-    GSF_TRY(launch_cg_pupdate(op, w.s, w.p, w.st, s));
+    GSF_TRY(launch_rg_direction(op, w.r, w.r_old, w.s, w.p, w.partials, w.st, k, s));
     int nparts = 0;
     if (bf || gf_dots(op)) {
       GSF_TRY(lap(w.p, w.q, w.partials, &nparts));
@@ -1302,8 +1300,7 @@ gsf_status gsf_reguided_filter(const gsf_operator_desc* desc, int method, const 
       GSF_TRY(lap(w.p, w.q, nullptr, nullptr));
       GSF_TRY(launch_dot(op, w.p, w.q, w.partials, &nparts, w.st, s));
     }
-    GSF_TRY(launch_rg_alpha(w.partials, nparts, w.st, s));
-    GSF_TRY(launch_rg_update(op, x_out, w.r, w.r_old, w.p, w.q, w.st, s));
+    GSF_TRY(launch_rg_update(op, x_out, w.r, w.r_old, w.p, w.q, w.partials, nparts, w.st, k, s));
   }
   if (info == nullptr) return GSF_OK;
   CgState host{};

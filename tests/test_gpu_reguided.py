@@ -304,3 +304,27 @@ def test_reguided_bf_tiny_grids(gsf, shape):
     print(f"re-guided BF tiny {shape}: status {info.status} vs {rinfo.status}, iters {info.iters} vs {rinfo.iters}")
     assert info.status == st and info.iters == rinfo.iters
     assert rel(y.cpu().numpy(), ref) <= rr.gate
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("kind", ["bf", "gf"])
+@pytest.mark.parametrize("shape", [(3, 5), (9, 31), (23, 45), (46, 29), (60, 64)])
+def test_reguided_cg_chunks(gsf, shape, kind, prec, shift):
+    """The re-guided CG's vector phases in 16-byte chunks: fewer points than a
+    workgroup, every remainder, and an output off the 16-byte grid (which they
+    take by elements); against the oracle with the bounds stated at the top."""
+    import torch
+    x0 = np.random.default_rng(3).uniform(0.0, 1.0, shape).ravel()
+    if prec == gsf.F32:
+        x0 = x0.astype(np.float32).astype(np.float64)
+    dp = "f32" if prec == gsf.F32 else "f64"
+    gp = dict(radius=2, sigma_d=2.0, sigma_r=0.2) if kind == "bf" else dict(radius=2, eps=1e-2)
+    op_ = dict(radius=2, sigma_s=2.0, sigma_r=0.2) if kind == "bf" else dict(radius=2, eps=1e-2)
+    xd = _dev(x0, prec, gsf)
+    out = torch.empty(xd.numel() + 2, dtype=xd.dtype, device="cuda")[shift:shift + xd.numel()]
+    y, info = gsf.reguided_filter(kind, shape, xd, gsf.METHOD_CG, 4, **gp, prec=prec, out=out)
+    rr = _rg_cg(kind, x0, shape, 4, **op_, data_prec=dp)
+    e = rel(y.cpu().numpy(), rr.y)
+    print(f"re-guided CG chunks {kind} {shape} prec={prec} shift={shift}: {e:.2e} (band {rr.band:.1e})")
+    assert info.iters == rr.extra.iters and e <= (rr.gate if prec == gsf.F64 else 1e-5)
