@@ -164,7 +164,11 @@ __global__ void __launch_bounds__(kSmallThreads) cg1d_small_kernel(const T* __re
         const int i = tid + j * nt;
         T acc = T(0);
         if (i < n) {
-          const T ui = v[j] * is[j];
+          // the rounded u_i that the neighbours read: contracted into the
+          // differences the product would keep its low bits, and u_i - u_j no
+          // longer be the negative of u_j - u_i (FP32 errors twice as large)
+          T ui = v[j] * is[j];
+          __asm__ volatile("" : "+v"(ui));
 #pragma unroll
           for (int o = 1; o <= RW; ++o) {
             if (o > r) break;
