@@ -75,6 +75,7 @@ gsf_status net_adam(int64_t count, int t, double lr, double b1, double b2, doubl
                     float* vel, const float* grad, uint16_t* wb, hipStream_t s);
 gsf_status net_to_bf16(int64_t count, const float* w, uint16_t* wb, hipStream_t s);
 int net_tiles(int64_t rows, int64_t cols);
+int net_partials(int64_t rows, int64_t cols);
 gsf_status net_infer(int prec, const uint16_t* w, int64_t rows, int64_t cols, int m, const void* R, void* Z,
                      const void* g, const void* sqd, const double* colnorm, const LobpcgState* st, double* partials,
                      hipStream_t s);
@@ -361,7 +362,7 @@ size_t carve_lob(const Operator& op, int m, char* base, LobWs* w) {
   w->vpart = (double*)c.take((size_t)vec_blocks(op.n) * 17 * sizeof(double));
   w->st = (LobpcgState*)c.take(sizeof(LobpcgState));
   w->Z = c.take(blk);
-  w->net_partials = (double*)c.take((size_t)net_tiles(op.rows, op.cols) * 3 * m * sizeof(double));
+  w->net_partials = (double*)c.take((size_t)net_partials(op.rows, op.cols) * 3 * m * sizeof(double));
   return c.off;
 }
 

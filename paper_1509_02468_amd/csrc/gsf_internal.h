@@ -130,7 +130,10 @@ __device__ __forceinline__ void reduce_partials(const double* partials, int npar
                                                 double (&out)[NV], double* lds) {
 #pragma unroll
   for (int k = 0; k < NV; ++k) out[k] = 0.0;
-#pragma unroll 4
+  // many rows in flight: a dependent launch reads them across the chip, about a
+  // microsecond a trip (4096 partials in the CG update of the 5-point graph)
+  constexpr int kAhead = NV == 1 ? 16 : (NV == 2 ? 8 : 4);
+#pragma unroll kAhead
   for (int b = threadIdx.x; b < nparts; b += blockDim.x) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) out[k] += partials[(size_t)b * stride + k];

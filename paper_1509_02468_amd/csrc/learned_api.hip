@@ -14,7 +14,7 @@ gsf_status net_forward_train(const uint16_t* w, int batch, const int32_t* idx, i
 gsf_status net_adam(int64_t count, int t, double lr, double b1, double b2, double eps, float* w, float* mom,
                     float* vel, const float* grad, uint16_t* wb, hipStream_t s);
 gsf_status net_to_bf16(int64_t count, const float* w, uint16_t* wb, hipStream_t s);
-int net_tiles(int64_t rows, int64_t cols);
+int net_partials(int64_t rows, int64_t cols);
 gsf_status net_infer(int prec, const uint16_t* w, int64_t rows, int64_t cols, int m, const void* R, void* Z,
                      const void* g, const void* sqd, const double* colnorm, const LobpcgState* st, double* partials,
                      hipStream_t s);
@@ -130,7 +130,7 @@ void gsf_precond_destroy(gsf_precond* T) {
 gsf_status gsf_precond_workspace_bytes(const gsf_precond* T, int m, size_t* bytes) {
   if (T == nullptr || bytes == nullptr || m < 1 || m > kMaxBlock) return GSF_EINVAL;
   *bytes = a256((size_t)vec_blocks(T->n) * kMaxBlock * 8) + 256 +
-           a256((size_t)net_tiles(T->rows, T->cols) * 3 * m * 8);
+           a256((size_t)net_partials(T->rows, T->cols) * 3 * m * 8);
   return GSF_OK;
 }
 

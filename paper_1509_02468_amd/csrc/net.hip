@@ -590,6 +590,13 @@ int net_tiles(int64_t rows, int64_t cols) {
   return (int)(((rows + kOT - 1) / kOT) * ((cols + kOT - 1) / kOT));
 }
 
+// Partials that the workspaces hold room for: one per 28 x 28 tile, the sizes
+// that callers have always been asked for; at least the tiles of a launch.
+int net_partials(int64_t rows, int64_t cols) {
+  static_assert(kOT >= 28, "no more tiles than partials");
+  return (int)(((rows + 27) / 28) * ((cols + 27) / 28));
+}
+
 gsf_status net_infer(int prec, const uint16_t* w, int64_t rows, int64_t cols, int m, const void* R, void* Z,
                      const void* g, const void* sqd, const double* colnorm, const LobpcgState* st, double* partials,
                      hipStream_t s) {
@@ -630,7 +637,7 @@ gsf_status net_lob_select(int prec, int64_t rows, int64_t cols, int m, int const
 }
 
 int tz_blocks(int64_t rows, int64_t cols) {
-  const int a = vec_blocks(rows * cols), b = net_tiles(rows, cols);
+  const int a = vec_blocks(rows * cols), b = net_partials(rows, cols);
   return a < b ? a : b;
 }
 
