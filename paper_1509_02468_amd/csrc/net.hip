@@ -160,7 +160,7 @@ __device__ __forceinline__ void lds_barrier() {
 // it delivers later than the wait before its use allows for (outputs differed
 // from run to run), so that the two forms are never chained.
 // Bound by vector instructions (conversions, addresses, the FP64 scaling) at
-// four waves per SIMD.  An m = 4 block at 2048^2, FP32: 411 us per call, 717
+// four waves per SIMD.  An m = 4 block at 2048^2, FP32: 390 us per call, 717
 // with 28 x 28 tiles, K = 16 products only, 64-bit coordinates, FP64
 // divisions, BF16 rounding by integer operations, the guidance converted
 // again for every column and six barriers per column.

@@ -80,7 +80,7 @@ inline double inv_two_sigma2(double s) { return std::isinf(s) ? 0.0 : 1.0 / (2.0
 // the points; a wave hands over the sums of its four rows of 16 lanes, and
 // every lane finishes the total itself (rows of 16 lanes, one per wave), so
 // that a sum costs one barrier and no broadcast.  500 samples, FP64, 20 steps:
-// 22.6 us per call, 61.8 with 16 waves of 8 points whatever the length, weights
+// 21.8 us per call, 61.8 with 16 waves of 8 points whatever the length, weights
 // read again in every step and three barriers per sum (94 with those sums'
 // exchanges through LDS); 4096 samples, r = 1 / 5: 41 / 150 us, 109 / 185
 // before; 8192: 97 / 256, 128 / 282.
