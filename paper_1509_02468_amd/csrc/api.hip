@@ -45,7 +45,8 @@ bool launch_bf_apply_joint(const Operator& op, int form, int m, const void* x, i
                            const void* x2, int64_t ldx2, void* y2, int64_t ldy2, double* dot, int* nparts,
                            hipStream_t s);
 bool launch_rg_power_small(const gsf_operator_desc& d, const void* x0, void* x_out, int kmax, hipStream_t s);
-bool launch_cg_small(const Operator& op, const void* x0, void* x_out, int kmax, CgState* st, hipStream_t s);
+bool launch_cg_small(const Operator& op, const void* x0, void* x_out, int kmax, const CgState& init, CgState* st,
+                     hipStream_t s);
 gsf_status launch_scale(const Operator& op, const void* in, void* out, int divide, hipStream_t s);
 gsf_status launch_cg_init(const Operator& op, const void* z, void* r, double* partials, CgState* st,
                           hipStream_t s);
@@ -1025,12 +1026,9 @@ gsf_status cg_filter_run(const Operator& op, const void* x0, void* x_out, int km
     CgState init{};
     init.tol = tol;
     init.tau = breakdown_tau(op.desc.prec);
-    if (op.desc.kind == GSF_BF && op.desc.ndim == 1 && op.n <= 8192) {
-      GSF_TRY(launch_cg_state_init(cg.w.st, init, cg.s));
-      if (launch_cg_small(op, x0, x_out, kmax, cg.w.st, cg.s)) {
-        GSF_TRY(hip_ok(hipGetLastError()));
-        return cg.report(tol, info);
-      }
+    if (launch_cg_small(op, x0, x_out, kmax, init, cg.w.st, cg.s)) {
+      GSF_TRY(hip_ok(hipGetLastError()));
+      return cg.report(tol, info);
     }
   }
   GSF_TRY(cg.begin(x0, tol));

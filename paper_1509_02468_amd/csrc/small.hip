@@ -80,7 +80,7 @@ inline double inv_two_sigma2(double s) { return std::isinf(s) ? 0.0 : 1.0 / (2.0
 // the points; a wave hands over the sums of its four rows of 16 lanes, and
 // every lane finishes the total itself (rows of 16 lanes, one per wave), so
 // that a sum costs one barrier and no broadcast.  500 samples, FP64, 20 steps:
-// 21.8 us per call, 61.8 with 16 waves of 8 points whatever the length, weights
+// 21.5 us per call, 61.8 with 16 waves of 8 points whatever the length, weights
 // read again in every step and three barriers per sum (94 with those sums'
 // exchanges through LDS); 4096 samples, r = 1 / 5: 41 / 150 us, 109 / 185
 // before; 8192: 97 / 256, 128 / 282.
@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(kSmallThreads) cg1d_small_kernel(const T* __re
                                                                    int64_t ppad, int r, const T* __restrict__ isqd,
                                                                    const T* __restrict__ sqd,
                                                                    const T* __restrict__ x0, T* __restrict__ xout,
-                                                                   int n, int kmax, CgState* st) {
+                                                                   int n, int kmax, CgState init, CgState* st) {
   __shared__ T ubuf[kSmallThreads * PTS + 2 * kCgPad];
   __shared__ T zb[PTS < 8 ? 1 : kSmallThreads * PTS];  // z where the registers have no room for it
   __shared__ __align__(16) double part_q[1][kSmallWaves][4], part_r[2][kSmallWaves][4];
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(kSmallThreads) cg1d_small_kernel(const T* __re
     }
     zz += (double)p[j] * (double)p[j];
   }
-  const double tol = st->tol, tau = st->tau;
+  const double tol = init.tol, tau = init.tau;
   apply(p);
 #pragma unroll
   for (int j = 0; j < PTS; ++j) {
@@ -308,45 +308,48 @@ __global__ void __launch_bounds__(kSmallThreads) cg1d_small_kernel(const T* __re
     if (i < n) xout[i] = zr(j) / sqd[i];
   }
   if (tid == 0) {
-    st->rho = rho;
-    st->rho0 = rho0;
-    st->res0 = sqrt(rho0 > 0.0 ? rho0 : 0.0);
-    st->floor = floor;
-    st->tol2 = tol2;
-    st->iters = iters;
-    st->k = iters + 1;
-    st->status = status;
-    st->active = active;
+    init.rho = rho;
+    init.rho0 = rho0;
+    init.res0 = sqrt(rho0 > 0.0 ? rho0 : 0.0);
+    init.floor = floor;
+    init.tol2 = tol2;
+    init.iters = iters;
+    init.k = iters + 1;
+    init.status = status;
+    init.active = active;
+    *st = init;
   }
 }
 
 template <typename T, int PTS, int RW>
-void launch_cg1d(const Operator& op, const void* x0, void* x_out, int kmax, CgState* st, hipStream_t s) {
+void launch_cg1d(const Operator& op, const void* x0, void* x_out, int kmax, const CgState& init, CgState* st,
+                 hipStream_t s) {
   const int per = (int)((op.n + PTS - 1) / PTS), threads = (per + 63) / 64 * 64;
   cg1d_small_kernel<T, PTS, RW><<<1, threads, 0, s>>>((const T*)op.planes, op.pstride, op.ppad, op.desc.radius,
                                                       (const T*)op.diag, (const T*)op.sqd, (const T*)x0,
-                                                      (T*)x_out, (int)op.n, kmax, st);
+                                                      (T*)x_out, (int)op.n, kmax, init, st);
 }
 
 // The fewest points per thread that 1024 threads hold; the weights in
 // registers as long as 16 waves' registers have room for them (2048 samples,
 // FP64: r = 5 in registers 44 us, r = 8 read in every step 118).
 template <typename T>
-void launch_cg1d_t(const Operator& op, const void* x0, void* x_out, int kmax, CgState* st, hipStream_t s) {
+void launch_cg1d_t(const Operator& op, const void* x0, void* x_out, int kmax, const CgState& init, CgState* st,
+                   hipStream_t s) {
   const int r = op.desc.radius;
   const int64_t per = (op.n + kSmallThreads - 1) / kSmallThreads;
   if (per <= 1) {
-    if (r <= 2) launch_cg1d<T, 1, 2>(op, x0, x_out, kmax, st, s);
-    else launch_cg1d<T, 1, 8>(op, x0, x_out, kmax, st, s);
+    if (r <= 2) launch_cg1d<T, 1, 2>(op, x0, x_out, kmax, init, st, s);
+    else launch_cg1d<T, 1, 8>(op, x0, x_out, kmax, init, st, s);
   } else if (per <= 2) {
-    if (r <= 2) launch_cg1d<T, 2, 2>(op, x0, x_out, kmax, st, s);
-    else if (r <= 5) launch_cg1d<T, 2, 5>(op, x0, x_out, kmax, st, s);
-    else launch_cg1d<T, 2, 0>(op, x0, x_out, kmax, st, s);
+    if (r <= 2) launch_cg1d<T, 2, 2>(op, x0, x_out, kmax, init, st, s);
+    else if (r <= 5) launch_cg1d<T, 2, 5>(op, x0, x_out, kmax, init, st, s);
+    else launch_cg1d<T, 2, 0>(op, x0, x_out, kmax, init, st, s);
   } else if (per <= 4) {
-    if (r <= 2) launch_cg1d<T, 4, 2>(op, x0, x_out, kmax, st, s);
-    else launch_cg1d<T, 4, 0>(op, x0, x_out, kmax, st, s);
+    if (r <= 2) launch_cg1d<T, 4, 2>(op, x0, x_out, kmax, init, st, s);
+    else launch_cg1d<T, 4, 0>(op, x0, x_out, kmax, init, st, s);
   } else {
-    launch_cg1d<T, 8, 0>(op, x0, x_out, kmax, st, s);
+    launch_cg1d<T, 8, 0>(op, x0, x_out, kmax, init, st, s);
   }
 }
 
@@ -372,14 +375,16 @@ bool launch_rg_power_small(const gsf_operator_desc& d, const void* x0, void* x_o
 }
 
 // One-launch CG filter of a built 1D BF operator whose signal fits in one
-// workgroup (n <= 8192); false (nothing launched) otherwise.  The state must
-// hold tol and tau (as after launch_cg_state_init).
-bool launch_cg_small(const Operator& op, const void* x0, void* x_out, int kmax, CgState* st, hipStream_t s) {
+// workgroup (n <= 8192); false (nothing launched) otherwise.  init: the state
+// with tol and tau; the kernel writes *st whole, so that no launch sets it first
+// (500 samples, 20 steps: 21.5 us per call, 21.8 with one).
+bool launch_cg_small(const Operator& op, const void* x0, void* x_out, int kmax, const CgState& init, CgState* st,
+                     hipStream_t s) {
   if (op.desc.kind != GSF_BF || op.desc.ndim != 1 || op.n > kCgSmallMax) return false;
   if (op.desc.prec == GSF_F32)
-    launch_cg1d_t<float>(op, x0, x_out, kmax, st, s);
+    launch_cg1d_t<float>(op, x0, x_out, kmax, init, st, s);
   else
-    launch_cg1d_t<double>(op, x0, x_out, kmax, st, s);
+    launch_cg1d_t<double>(op, x0, x_out, kmax, init, st, s);
   return true;
 }
 
