@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(kThreads) bcg_pbeta_kernel(const T* __restrict
   __shared__ double red[2 * M * 16];
   __shared__ double bc[2 * M];
   typedef PointGroup<T, M> G;
-  if (!st->active) return;
+  if (!group_active(&st->active)) return;
   T beta[M];
   bool on[M];
 #pragma unroll
@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(kThreads) bcg_update_kernel(T* __restrict__ z,
   __shared__ double red[2 * M * 16];
   __shared__ double bc[M];
   typedef PointGroup<T, M> G;
-  if (!st->active) return;
+  if (!group_active(&st->active)) return;
   T alpha[M];
   bool on[M];
 #pragma unroll

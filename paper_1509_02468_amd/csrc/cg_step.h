@@ -51,6 +51,18 @@ __device__ __forceinline__ bool chunk_aligned(P... ptrs) {
   return (((uintptr_t)ptrs | ...) & 15) == 0;
 }
 
+// The state's `active` flag, read once per workgroup: workgroup 0 of a phase may
+// clear it while other workgroups of the same launch are still starting, and a
+// workgroup whose waves read it for themselves could lose some of them before
+// its barriers and sums.  Read this way it leaves as a whole (the stop is the
+// decision that it would have taken from the same sums) or not at all.
+__device__ __forceinline__ bool group_active(const int32_t* flag) {
+  __shared__ int32_t on;
+  if (threadIdx.x == 0) on = *flag;
+  __syncthreads();
+  return on != 0;
+}
+
 // all threads get the fixed-order sum of NV partials per workgroup
 template <int NV>
 __device__ __forceinline__ void reduce_all(const double* partials, int nparts, double (&t)[NV], double* red,
@@ -74,7 +86,7 @@ __device__ __forceinline__ void cg_pbeta_body(const T* __restrict__ r, T* __rest
                                               int bid, int nblk) {
   __shared__ double red[32];
   __shared__ double bc[2];
-  if (!st->active) return;
+  if (!group_active(&st->active)) return;
   typedef typename Chunk<T>::type V;
   const int64_t stride = (int64_t)nblk * blockDim.x, c0 = (int64_t)bid * blockDim.x + threadIdx.x;
   const int64_t nc = chunk_aligned(r, p) ? n / Chunk<T>::n : 0;
@@ -130,7 +142,7 @@ __device__ __forceinline__ void cg_aupdate_body(T* __restrict__ z, T* __restrict
                                                 int nblk) {
   __shared__ double red[32];
   __shared__ double bc[2];
-  if (!st->active) return;
+  if (!group_active(&st->active)) return;
   typedef typename Chunk<T>::type V;
   const int64_t stride = (int64_t)nblk * blockDim.x, c0 = (int64_t)bid * blockDim.x + threadIdx.x;
   const int64_t nc = chunk_aligned(z, r, p, q) ? n / Chunk<T>::n : 0;

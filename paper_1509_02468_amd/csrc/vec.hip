@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(kThreads) rg_pbeta_kernel(const T* __restrict_
                                                             CgState* st, int k) {
   __shared__ double red[32];
   __shared__ double bc[2];
-  if (!st->active) return;
+  if (!group_active(&st->active)) return;
   typedef typename Chunk<T>::type V;
   constexpr int C = Chunk<T>::n;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x, c0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -360,7 +360,7 @@ __global__ void __launch_bounds__(kThreads) rg_aupdate_kernel(T* __restrict__ x,
                                                               CgState* st, int k) {
   __shared__ double red[16];
   __shared__ double bc[1];
-  if (!st->active) return;
+  if (!group_active(&st->active)) return;
   typedef typename Chunk<T>::type V;
   constexpr int C = Chunk<T>::n;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x, c0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
