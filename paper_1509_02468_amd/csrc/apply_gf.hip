@@ -16,6 +16,7 @@
 // (a, b) -> output for up to 8 columns at once; the build is one kernel on
 // (g, g^2).  A 1D signal is one row.
 #include <cmath>
+#include <type_traits>
 
 #include "gsf_internal.h"
 
@@ -369,17 +370,30 @@ struct GfCpl {
 // half of each.)  Four waves own a strip of 256 columns, 2r of them halo, and
 // rb rows; per row they add the entering row, put their sums into an LDS row,
 // and after one barrier (the rows alternate between two buffers) take the
-// horizontal window sums as (run of consecutive columns, block column) with a
-// sliding sum.  Per apply, r = 8: 1531 x 2047, FP64, m = 8 514 us (2.9 TB/s of
-// the two passes' least traffic), 794 as two groups of 4 columns of the kernel
-// above; FP32, m = 8 236 us, 335; 256 x 256, FP32, m = 4 27 us, 32.
+// horizontal window sums as (run of consecutive columns, block column).  Per
+// apply, r = 8: 1531 x 2047, FP64, m = 8 514 us (2.9 TB/s of the two passes'
+// least traffic), 794 as two groups of 4 columns of the kernel above; FP32,
+// m = 8 236 us, 335; 256 x 256, FP32, m = 4 23 us, 32.
+//
+// Rounding.  A horizontal sum takes additions only (a sliding one over runs of
+// 8 columns was less exact than the kernel above, whose runs are shorter).  A
+// vertical sum gathers a rounding with every row that enters or leaves, and
+// keeps a huge or non-finite value after its row has left; chunks of more than
+// kGfRowsMax rows, the kernel above's most, therefore renew their sums every
+// 2r + 1 rows (RENEW) from a second set that only adds the rows that enter.
+// L_sym x of uniform data, FP64, m = 8, r = 8, relative to long double:
+// 3.5e-16 at 1531 x 2047 and 3.3e-16 at 4096^2 (147 rows a chunk), 4.2e-16 and
+// 4.1e-16 by the kernel above; with sliding sums never renewed 4.7e-16 and
+// 6.2e-16.  Renewing costs 1% at 4096^2 (2426 us, 2401 without; 4140 above).
 constexpr int kGfBlkThreads = 256;
 constexpr int kGfBlkCols = 256;  // halo columns of a strip
 
 template <typename T, int M>
 struct GfBlkShared {
   static constexpr int kPitch = 2 * M + 2;  // doubles per column: runs of columns spread over the banks
-  double vs[2][kGfBlkCols * kPitch];
+  // most outputs of a run; a strip's last run may read that many columns past its row
+  static constexpr int kRun = (kGfBlkCols * M + kGfBlkThreads - 1) / kGfBlkThreads;
+  double vs[(2 * kGfBlkCols + kRun) * kPitch];  // two rows
   double2 rh[kGfBlkCols];                   // 1 / (points of the horizontal window) and its root
 };
 
@@ -398,15 +412,15 @@ struct GfBlkArgs {
 };
 
 // DENSE: the pieces of `in` are aligned runs (else x has a row stride or
-// address of its own and is read by elements; the same sums).
-template <typename T, int M, int STAGE, bool SCALE, bool DENSE>
-__global__ void __launch_bounds__(kGfBlkThreads) gf_block_kernel(GfBlkArgs a) {
+// address of its own and is read by elements; the same sums).  RENEW: see above.
+template <typename T, int M, int STAGE, bool SCALE, bool DENSE, bool RENEW>
+__global__ void __launch_bounds__(kGfBlkThreads, 2) gf_block_kernel(GfBlkArgs a) {
   constexpr int V = 16 / (int)sizeof(T);      // elements of a piece
   constexpr int K = STAGE == 1 ? M : 2 * M;   // elements of a point's row
   constexpr int NP = K / V;                   // pieces per thread
   constexpr int NC = STAGE == 1 ? 2 : 1;      // sums per element
   constexpr int R = kGfBlkThreads / M;        // runs
-  constexpr int NO = (kGfBlkCols + R - 1) / R;  // most outputs of a run
+  constexpr int NO = GfBlkShared<T, M>::kRun;
   constexpr int PITCH = GfBlkShared<T, M>::kPitch;
   typedef T piece_t __attribute__((ext_vector_type(V)));
   __shared__ GfBlkShared<T, M> sh;
@@ -452,25 +466,29 @@ __global__ void __launch_bounds__(kGfBlkThreads) gf_block_kernel(GfBlkArgs a) {
     }
     return w;
   };
-  double s[NP][V][NC];
+  // the running sums, and their successors: from zero, the entering rows alone
+  double s[NP][V][NC], f[NP][V][NC];
 #pragma unroll
   for (int p = 0; p < NP; ++p)
 #pragma unroll
     for (int i = 0; i < V; ++i)
 #pragma unroll
-      for (int c = 0; c < NC; ++c) s[p][i][c] = 0.0;
-  auto add_row = [&](const Row& w, bool sub) {
+      for (int c = 0; c < NC; ++c) s[p][i][c] = f[p][i][c] = 0.0;
+  enum { kWarm, kEnter, kLeave };
+  auto add_row = [&](const Row& w, int what, bool live = true) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
 #pragma unroll
       for (int i = 0; i < V; ++i) {
-        double u = (double)w.v[p][i];
-        if constexpr (STAGE == 1 && SCALE) u *= (double)w.d[p];
-        u = ok[p] ? u : 0.0;
-        s[p][i][0] += sub ? -u : u;
-        if constexpr (STAGE == 1) {
-          const double gu = ok[p] ? (double)w.g[p] * u : 0.0;
-          s[p][i][NC - 1] += sub ? -gu : gu;
+        double u[NC];
+        u[0] = (double)w.v[p][i];
+        if constexpr (STAGE == 1 && SCALE) u[0] *= (double)w.d[p];
+        u[0] = ok[p] && live ? u[0] : 0.0;
+        if constexpr (STAGE == 1) u[NC - 1] = ok[p] && live ? (double)w.g[p] * u[0] : 0.0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          s[p][i][c] += what == kLeave ? -u[c] : u[c];
+          if (RENEW && what == kEnter) f[p][i][c] += u[c];
         }
       }
     }
@@ -515,14 +533,27 @@ __global__ void __launch_bounds__(kGfBlkThreads) gf_block_kernel(GfBlkArgs a) {
   Epi epi = pre(y0);
   for (int yy = w0; yy <= w1; yy += 2) {
     const Row p = fetch(yy), q = fetch(yy + 1);
-    add_row(p, false);
-    if (yy + 1 <= w1) add_row(q, false);
+    add_row(p, kWarm);
+    add_row(q, kWarm, yy + 1 <= w1);  // (not under a branch: the compiler then moves the loads there too)
   }
+  int age = 0;
   for (int yo = y0; yo < y1; ++yo) {
     const int ya = yo + r, yd = yo - r;
-    if (ya < a.rows) add_row(enter, false);
+    if (ya < a.rows) add_row(enter, kEnter);
     enter = fetch(ya + 1);
-    double* vs = sh.vs[(yo - y0) & 1];
+    if (RENEW && ++age == 2 * r + 1) {  // the successors hold the whole window
+      age = 0;
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            s[p][i][c] = f[p][i][c];
+            f[p][i][c] = 0.0;
+          }
+    }
+    double* vs = sh.vs + ((yo - y0) & 1) * (kGfBlkCols * PITCH);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       if constexpr (STAGE == 1) {
@@ -542,21 +573,57 @@ __global__ void __launch_bounds__(kGfBlkThreads) gf_block_kernel(GfBlkArgs a) {
       const int vc = (ya < a.rows ? ya : a.rows - 1) - (yd < 0 ? 0 : yd) + 1;
       const double rv = 1.0 / (double)vc, srv = sqrt(rv);
       const double* v = vs + cb * PITCH + 2 * j;
-      double a0 = 0.0, a1 = 0.0;
+      // window sums of the run, by additions only: of G outputs at a time
+      // (2r >= G), what their windows share plus the columns left and right of
+      // it that each has; left and right one after the other (both at once
+      // spilled at eight FP64 columns)
+      double2 sum[NO];
+      auto window_sums = [&](auto group) {
+        constexpr int G = decltype(group)::value < NO ? decltype(group)::value : NO;
+#pragma unroll
+        for (int b = 0; b < NO; b += G) {
+          const double* vb = v + b * PITCH;
+          double2 side[G], core = *(const double2*)(vb + G * PITCH);
+#pragma unroll
+          for (int o = 0; o < G; ++o) side[o] = *(const double2*)(vb + o * PITCH);
 #pragma unroll 4
-      for (int h = 0; h < 2 * r; ++h) {
-        const double2 w = *(const double2*)(v + h * PITCH);
-        a0 += w.x;
-        a1 += w.y;
-      }
-      const double* vr = v + 2 * r * PITCH;
+          for (int h = G + 1; h <= 2 * r; ++h) {
+            const double2 w = *(const double2*)(vb + h * PITCH);
+            core.x += w.x;
+            core.y += w.y;
+          }
+          core.x += side[G - 1].x;
+          core.y += side[G - 1].y;
+          sum[b + G - 1] = core;
+          double2 t = {0.0, 0.0};
+#pragma unroll
+          for (int o = G - 2; o >= 0; --o) {
+            t.x += side[o].x;
+            t.y += side[o].y;
+            sum[b + o] = make_double2(core.x + t.x, core.y + t.y);
+          }
+          if constexpr (RENEW && M * sizeof(T) == 64) __builtin_amdgcn_sched_barrier(0);
+          vb += 2 * r * PITCH;
+#pragma unroll
+          for (int o = 1; o < G; ++o) side[o] = *(const double2*)(vb + o * PITCH);
+          t = {0.0, 0.0};
+#pragma unroll
+          for (int o = 1; o < G; ++o) {
+            t.x += side[o].x;
+            t.y += side[o].y;
+            sum[b + o].x += t.x;
+            sum[b + o].y += t.y;
+          }
+        }
+      };
+      if (r >= 4) window_sums(std::integral_constant<int, 8>{});
+      else if (r >= 2) window_sums(std::integral_constant<int, 4>{});
+      else window_sums(std::integral_constant<int, 2>{});
       const size_t base = (size_t)yo * a.cols + c0 + cb;
 #pragma unroll
       for (int o = 0; o < NO; ++o) {
         if (o < nout) {
-          const double2 w = *(const double2*)(vr + o * PITCH);
-          a0 += w.x;
-          a1 += w.y;
+          const double a0 = sum[o].x, a1 = sum[o].y;
           const double2 h = sh.rh[cb + o];
           const double rc = rv * h.x;
           if constexpr (STAGE == 1) {
@@ -578,14 +645,11 @@ __global__ void __launch_bounds__(kGfBlkThreads) gf_block_kernel(GfBlkArgs a) {
             }
             ((T*)a.out)[(base + o) * a.ldy + j] = (T)out;
           }
-          const double2 l = *(const double2*)(v + o * PITCH);
-          a0 -= l.x;
-          a1 -= l.y;
         }
       }
     }
     epi = pre(yo + 1);
-    if (yd >= 0) add_row(leave, true);
+    if (yd >= 0) add_row(leave, kLeave);
     leave = fetch(yd + 1);
   }
 }
@@ -617,17 +681,23 @@ void gf_apply_block(const Operator& op, T* ab, int form, const T* x, int64_t ldx
   a.ldx = ldx;
   a.ldy = ldy;
   const bool dense = ldx == M && (uintptr_t)x % 16 == 0;
-  if (form == GSF_FORM_RW || form == GSF_FORM_L) {
-    if (dense) gf_block_kernel<T, M, 1, false, true><<<grid, kGfBlkThreads, 0, s>>>(a);
-    else gf_block_kernel<T, M, 1, false, false><<<grid, kGfBlkThreads, 0, s>>>(a);
-  } else {
-    a.dinv = op.diag;
-    if (dense) gf_block_kernel<T, M, 1, true, true><<<grid, kGfBlkThreads, 0, s>>>(a);
-    else gf_block_kernel<T, M, 1, true, false><<<grid, kGfBlkThreads, 0, s>>>(a);
-  }
-  a.in = ab;
-  a.out = y;
-  gf_block_kernel<T, M, 2, false, true><<<grid, kGfBlkThreads, 0, s>>>(a);
+  const bool scale = form != GSF_FORM_RW && form != GSF_FORM_L;
+  if (scale) a.dinv = op.diag;
+  auto passes = [&](auto renew) {
+    constexpr bool N = decltype(renew)::value;
+    if (!scale) {
+      if (dense) gf_block_kernel<T, M, 1, false, true, N><<<grid, kGfBlkThreads, 0, s>>>(a);
+      else gf_block_kernel<T, M, 1, false, false, N><<<grid, kGfBlkThreads, 0, s>>>(a);
+    } else {
+      if (dense) gf_block_kernel<T, M, 1, true, true, N><<<grid, kGfBlkThreads, 0, s>>>(a);
+      else gf_block_kernel<T, M, 1, true, false, N><<<grid, kGfBlkThreads, 0, s>>>(a);
+    }
+    a.in = ab;
+    a.out = y;
+    gf_block_kernel<T, M, 2, false, true, N><<<grid, kGfBlkThreads, 0, s>>>(a);
+  };
+  if (a.rb > kGfRowsMax) passes(std::true_type{});
+  else passes(std::false_type{});
 }
 
 // Blocks of 4 and 8 columns take gf_block_kernel, other sizes gf_box_kernel.

@@ -600,6 +600,49 @@ def test_gf_block_strips(gsf, shape, radius, m, prec):
             assert e <= TOL[prec], (form, j, e)
 
 
+@pytest.mark.parametrize("prec,m", [(0, 4), (0, 8), (1, 4), (1, 8)])
+@pytest.mark.parametrize("shape,radius", [((2500, 2300), 8), ((9000, 64), 8), ((40000, 240), 1)])
+def test_gf_block_rows_start_afresh(gsf, shape, radius, m, prec):
+    """The running window sums of a block's apply start afresh at least every
+    32 rows, whatever the image's height: what a row holds reaches (beside the
+    window's r rows, in each of the two passes) the 31 rows after it at most.
+    Exact: a perturbed row 0 leaves every output from row 2 (31 + r) + 1 on as
+    it was, to the bit; a large value first (it would take digits off the sums
+    below it), then a NaN."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    dt = torch.float32 if prec == gsf.F32 else torch.float64
+    g = torch.rand(shape[0] * shape[1], device="cuda", dtype=dt, generator=gen)
+    x = torch.rand((g.numel(), m), device="cuda", dtype=dt, generator=gen)
+    op = gsf.Operator("gf", shape, g, radius=radius, eps=1e-2, prec=prec)
+    y = op.apply(x, gsf.FORM_N)
+    first = (2 * (31 + radius) + 1) * shape[1]
+    for v in (1e6, float("nan")):
+        x[:shape[1]] = v
+        assert torch.equal(op.apply(x, gsf.FORM_N)[first:], y[first:]), v
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("rows,radius", [(33, 8), (34, 1), (40, 2), (47, 3), (51, 4), (52, 8), (70, 5)])
+def test_gf_block_renewed_sums(gsf, rows, radius, prec):
+    """Chunks of more than 32 rows, whose sums are renewed every 2r + 1 rows:
+    chunk heights on both sides of a renewal, against the pairs of columns that
+    the kernel for other block sizes takes.  Both sum at most a few hundred
+    terms in FP64: within 1e-13 (FP64 data), or one unit of the last place of
+    the stored coefficients and outputs (FP32)."""
+    import torch
+    cols = 512 * 254
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    dt = torch.float32 if prec == gsf.F32 else torch.float64
+    g = torch.rand(rows * cols, device="cuda", dtype=dt, generator=gen)
+    x = torch.rand((g.numel(), 4), device="cuda", dtype=dt, generator=gen)
+    op = gsf.Operator("gf", (rows, cols), g, radius=radius, eps=1e-2, prec=prec)
+    y = op.apply(x, gsf.FORM_N)
+    for c in (0, 2):
+        ref = op.apply(x[:, c:c + 2].contiguous(), gsf.FORM_N)
+        assert (y[:, c:c + 2] - ref).abs().max() <= (1e-13 if prec else 1e-6) * ref.abs().max()
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 def test_lobpcg_soft_locking_parity(gsf, prec):
     """LOBPCG to a tolerance, where columns reach it at different steps and
