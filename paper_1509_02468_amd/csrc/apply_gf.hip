@@ -654,12 +654,25 @@ __global__ void __launch_bounds__(kGfBlkThreads, 2) gf_block_kernel(GfBlkArgs a)
   }
 }
 
-// Rows per workgroup: the strips and chunks fill the chip's workgroup slots
-// (two per CU by registers and LDS) once, down to 4 rows.
+// Strips of a row, and rows per workgroup: the strips and chunks fill the
+// chip's workgroup slots (two per CU by registers and LDS) once, down to 4 rows.
+struct GfBlkGrid {
+  int ow, strips, rb;
+};
+GfBlkGrid gf_block_grid(const Operator& op) {
+  constexpr int kGroups = 512, kMinRows = 4;
+  GfBlkGrid g;
+  g.ow = kGfBlkCols - 2 * op.desc.radius;
+  g.strips = ((int)op.cols + g.ow - 1) / g.ow;
+  const int chunks = g.strips < kGroups ? kGroups / g.strips : 1;
+  g.rb = ((int)op.rows + chunks - 1) / chunks;
+  if (g.rb < kMinRows) g.rb = kMinRows;
+  return g;
+}
+
 template <typename T, int M>
 void gf_apply_block(const Operator& op, T* ab, int form, const T* x, int64_t ldx, T* y, int64_t ldy,
                     hipStream_t s) {
-  constexpr int kGroups = 512, kMinRows = 4;
   GfBlkArgs a{};
   a.rows = (int)op.rows;
   a.cols = (int)op.cols;
@@ -667,11 +680,9 @@ void gf_apply_block(const Operator& op, T* ab, int form, const T* x, int64_t ldx
   a.form = form;
   const double w = 2.0 * op.desc.radius + 1.0;
   a.sromega = 1.0 / sqrt(op.desc.ndim == 1 ? w : w * w);
-  const int ow = kGfBlkCols - 2 * a.r, strips = (a.cols + ow - 1) / ow;
-  const int chunks = strips < kGroups ? kGroups / strips : 1;
-  a.rb = (a.rows + chunks - 1) / chunks;
-  if (a.rb < kMinRows) a.rb = kMinRows;
-  const dim3 grid((unsigned)strips, (unsigned)((a.rows + a.rb - 1) / a.rb));
+  const GfBlkGrid geo = gf_block_grid(op);
+  a.rb = geo.rb;
+  const dim3 grid((unsigned)geo.strips, (unsigned)((a.rows + a.rb - 1) / a.rb));
   a.g = op.g;
   a.mu = op.mu;
   a.inv = op.inv;
@@ -700,19 +711,38 @@ void gf_apply_block(const Operator& op, T* ab, int form, const T* x, int64_t ldx
   else passes(std::false_type{});
 }
 
-// Blocks of 4 and 8 columns take gf_block_kernel, other sizes gf_box_kernel.
-// So do tall images that fill less than half of a strip (8192 x 64, FP32,
-// m = 4 / 8, r = 8: 48 / 79 us against 69 / 103; at 96 x 96, where latency and
-// not the idle columns counts, 31 / 43 against 25 / 34) and short signals
-// (4096 samples, FP64, m = 4: 10.3 against 10.9 us; 200000: 30 against 19).
-// Eight FP64 columns, two calls of the other kernel, always take this one
-// (8192 x 64: 169 against 116 us, 4096 samples 16.7 against 12.0).
+// Blocks of 4 and 8 columns take gf_block_kernel where it is the faster one,
+// else, as other sizes do, gf_box_kernel (in groups of up to 4 columns, FP32 8).
+// The strips' idle columns cost gf_block_kernel as much as those in use, so the
+// lines lie at parts of the strips in use.  Its time over the other's, r = 2 and
+// 8, 4 to 770 columns, 60 to 120000 rows:
+// - up to 5 rows per workgroup, where latency bounds both: 0.45 to 1.04 at any
+//   width; 7 rows: 0.68 to 1.0 at a quarter or more in use, 0.9 to 1.2 below;
+//   10 rows: 0.53 to 1.0 from 0.55 on, up to 1.1 at 0.5, 1.4 at 0.03;
+// - more rows, FP32, m = 4: one strip 0.76 to 1.01 from 0.7 on and up to 1.36 at
+//   0.5, several 0.71 to 1.05 from 0.78 on and up to 1.5 at 0.5;
+// - FP32, m = 8: one strip 0.7 to 1.04 from 0.5 on and up to 1.3 at 0.45, several
+//   0.63 to 1.0 from 0.66 on and up to 1.2 at 0.5;
+// - FP64, m = 4: one strip 0.73 to 0.99 from 0.45 on and up to 1.25 at 0.25,
+//   several 0.8 to 1.08 from 0.7 on and up to 1.33 at 0.5;
+// - FP64, m = 8 (two calls of the other kernel): 0.5 to 0.95 from 0.25 on, 1.1
+//   to 2.6 below 0.2;
+// - signals: 0.4 to 0.94 from 65536 samples on, about 1.0 below (FP64, m = 8:
+//   0.5 to 0.75 at any length).
 template <typename T>
 bool gf_block_pays(const Operator& op, int m) {
   if (m != 4 && m != 8) return false;
-  if (sizeof(T) == 8 && m == 8) return true;
-  if (op.desc.ndim == 1) return op.n >= 65536;
-  return op.cols >= kGfBlkCols / 2 || op.n < (1 << 17);
+  const bool f64 = sizeof(T) == 8;
+  if (op.desc.ndim == 1) return op.n >= 65536 || (f64 && m == 8);
+  const GfBlkGrid g = gf_block_grid(op);
+  if (g.rb <= 5) return true;
+  const bool one = g.strips == 1;
+  double least;
+  if (m == 8) least = f64 ? 0.25 : (one ? 0.5 : 0.66);
+  else least = f64 ? (one ? 0.45 : 0.7) : (one ? 0.7 : 0.78);
+  if (g.rb <= 10 && least > 0.55) least = 0.55;
+  if (g.rb <= 7) least = 0.25;
+  return (double)op.cols >= least * ((double)g.strips * g.ow);
 }
 
 double gf_omega(const Operator& op) {

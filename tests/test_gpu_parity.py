@@ -643,6 +643,26 @@ def test_gf_block_renewed_sums(gsf, rows, radius, prec):
         assert (y[:, c:c + 2] - ref).abs().max() <= (1e-13 if prec else 1e-6) * ref.abs().max()
 
 
+@pytest.mark.parametrize("prec,m", [(0, 4), (0, 8), (1, 4), (1, 8)])
+@pytest.mark.parametrize("shape,radius", [((2560, 31), 8), ((2561, 31), 8), ((5200, 60), 8), ((5200, 59), 8),
+                                          ((5200, 136), 8), ((5200, 164), 8), ((5200, 193), 8), ((2600, 300), 2),
+                                          ((2600, 390), 8), ((20000, 3), 1)])
+def test_gf_block_either_kernel(gsf, shape, radius, m, prec):
+    """Heights and widths on both sides of the choice of kernel for blocks of 4
+    and 8 columns, against the apply of column pairs, whose kernel never
+    changes; bounds as above."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    dt = torch.float32 if prec == gsf.F32 else torch.float64
+    g = torch.rand(shape[0] * shape[1], device="cuda", dtype=dt, generator=gen)
+    x = torch.rand((g.numel(), m), device="cuda", dtype=dt, generator=gen)
+    op = gsf.Operator("gf", shape, g, radius=radius, eps=1e-2, prec=prec)
+    y = op.apply(x, gsf.FORM_N)
+    for c in range(0, m, 2):
+        ref = op.apply(x[:, c:c + 2].contiguous(), gsf.FORM_N)
+        assert (y[:, c:c + 2] - ref).abs().max() <= (1e-13 if prec else 1e-6) * ref.abs().max()
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 def test_lobpcg_soft_locking_parity(gsf, prec):
     """LOBPCG to a tolerance, where columns reach it at different steps and
