@@ -330,7 +330,9 @@ __device__ __forceinline__ void wave_fence() { __asm__ volatile("" ::: "memory")
 
 // Reciprocal square root and reciprocal: the hardware approximation (a relative
 // error e below 2^-20) and one step of third order, r (1 + e/2 + 3 e^2/8) and
-// r (1 + e + e^2): an ulp or two.
+// r (1 + e + e^2).  The product x r of the first is rounded: within 1 ulp, 0.27
+// in the mean (the correctly rounded root and quotient of 1 / sqrt(x): 1.5 and
+// 0.33); the second is correctly rounded but for ties (0.51 ulp).
 __device__ __forceinline__ double rsq_nr(double x) {
   const double r = __builtin_amdgcn_rsq(x);
   const double e = fma(-x * r, r, 1.0);
@@ -608,7 +610,7 @@ __device__ __forceinline__ void rr_tridiagonalize(RRShared& sh, double (&a)[RRGr
 // Eigenvalues t = wave (and wave + 4 for m > 4) of T into sh.ev[t], their
 // eigenvectors into sh.Y[t], every wave its own: multisection bisection of the
 // Sturm count (the wave's 64 lanes, 32 for m > 4, evaluate it at evenly spaced
-// shifts of the bracket, which shrinks by 65 (33) per round, down to 2^-54 of
+// shifts of the bracket, which shrinks by 65 (33) per round, down to 2^-60 of
 // the Gershgorin interval), then two steps of inverse iteration from a fixed
 // start vector (Gaussian elimination with partial pivoting of T - lambda I in
 // registers).  Rows past K are padded with a diagonal far above the spectrum.
@@ -634,7 +636,7 @@ __device__ __forceinline__ void rr_eig_pairs(RRShared& sh, int K, int m) {
   }
   const int half = m > 4 ? 1 : 0;            // two eigenvalues per wave
   const int G = half ? 32 : 64;              // lanes per eigenvalue
-  const int rounds = half ? 11 : 9;          // 33^11, 65^9 > 2^54
+  const int rounds = half ? 12 : 10;         // 33^12, 65^10 > 2^60
   const int sub = half ? (lane >> 5) : 0;
   const int t = wave + 4 * sub;              // this lane's eigenvalue (t >= m: idle copy)
   const int tc = t < m ? t : m - 1;

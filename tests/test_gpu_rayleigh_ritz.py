@@ -74,3 +74,16 @@ def test_dropped_columns(gsf, ns, m, drop):
     G1 = np.ones((ns, ns))
     th, C, kept, nk = gsf.rayleigh_ritz(G1, G1, m, 1e-10, 1e-13)
     assert nk == 1 and kept[0] and not kept[1:].any()
+
+
+@pytest.mark.parametrize("ns,m", [(3, 1), (4, 2), (9, 3), (12, 4), (16, 5), (24, 8)])
+def test_small_ritz_values_of_a_diagonal_pencil(gsf, ns, m):
+    """The bisection ends at 2^-60 of the Gershgorin interval (below 3 wide).  On
+    a diagonal matrix the counts are exact, so a Ritz value is within half of
+    that bracket, 1.3e-18, and the roundings of the bracket's ends, an ulp."""
+    rng = np.random.default_rng(ns)
+    for small in (1e-2, 1e-3, 1e-4):
+        lam = np.concatenate([small * (1.0 + np.arange(m) + 0.3 * rng.uniform(size=m)), rng.uniform(0.5, 2.0, ns - m)])
+        th = gsf.rayleigh_ritz(np.diag(lam), np.eye(ns), m, 1e-10, 1e-13)[0]
+        ref = np.sort(lam)[:m]
+        assert np.all(np.abs(th - ref) <= 1.3e-18 + 2 * np.spacing(ref))
