@@ -1331,13 +1331,14 @@ __global__ void __launch_bounds__(kThreads) lob_update_kernel(LobArgs a, int fir
       v[M + t] += yi * rt;
     }
   };
-  // rows of less than 16 bytes go GP points at a time, 16 bytes per block
-  // (m = 1, FP32, 1024^2: 11.6 us per launch, 13.8 a point at a time)
+  // rows of less than 16 bytes go GP points at a time, 16 bytes per block where
+  // the blocks are aligned to that (m = 1, FP32, 1024^2: 11.6 us per launch, 13.8
+  // a point at a time, as in a workspace off the 16-byte grid)
   constexpr int GP = sizeof(T) * M < 16 && 16 % (sizeof(T) * M) == 0 ? (int)(16 / (sizeof(T) * M)) : 1;
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t done = 0;
   if constexpr (GP > 1) {
-    const int64_t ng = a.n / GP;
+    const int64_t ng = chunk_aligned(X, W, P, AX, AW, AP) ? a.n / GP : 0;
     done = ng * GP;
     for (int64_t g = t0; g < ng; g += stride) {
       constexpr int E = GP * M;

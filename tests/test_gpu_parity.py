@@ -663,6 +663,23 @@ def test_gf_block_either_kernel(gsf, shape, radius, m, prec):
         assert (y[:, c:c + 2] - ref).abs().max() <= (1e-13 if prec else 1e-6) * ref.abs().max()
 
 
+@pytest.mark.parametrize("prec,m", [(0, 1), (0, 2), (1, 1)])
+@pytest.mark.parametrize("constraint", [False, True])
+def test_lobpcg_narrow_block_off_grid(gsf, prec, m, constraint):
+    """LOBPCG with rows of less than 16 bytes in a workspace off the 16-byte
+    grid, where the update takes a point at a time."""
+    import torch
+    shape = (25, 41)
+    x = _round(scene_2d(*shape, 0.05, 9)[1], prec, gsf)
+    p = dict(radius=2, sigma_d=2.0, sigma_r=0.2)
+    op = gsf.Operator("bf", shape, _torch(x.ravel(), prec, gsf), prec=prec, **p)
+    need = op.workspace(gsf.METHOD_LOBPCG, m).numel()
+    ws = torch.empty(need + 16, dtype=torch.uint8, device="cuda")[8:8 + need]
+    y, info = op.lobpcg_filter(_torch(x.ravel(), prec, gsf), m, 6, constraint=constraint, ws=ws)
+    ref = lobpcg_reference("bf", p, x, shape, m, 6, prec, constraint=constraint)
+    check_lobpcg(info, y.cpu().numpy(), ref, m, prec, f"off grid m={m} c={constraint}")
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 def test_lobpcg_soft_locking_parity(gsf, prec):
     """LOBPCG to a tolerance, where columns reach it at different steps and
