@@ -771,7 +771,9 @@ template <typename T>
 void gf_apply_typed(const Operator& op, void* scratch, int form, int m, const T* x, int64_t ldx, T* y, int64_t ldy,
                     hipStream_t s) {
   T* ab = (T*)scratch;
-  if (gf_block_pays<T>(op, m)) {
+  // (gf_block_kernel takes the coefficients in 16-byte pieces: not in an
+  // operator workspace off the 16-byte grid)
+  if ((uintptr_t)ab % 16 == 0 && gf_block_pays<T>(op, m)) {
     if (m == 8) gf_apply_block<T, 8>(op, ab, form, x, ldx, y, ldy, s);
     else gf_apply_block<T, 4>(op, ab, form, x, ldx, y, ldy, s);
     return;

@@ -681,6 +681,29 @@ def test_lobpcg_narrow_block_off_grid(gsf, prec, m, constraint):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("m", [4, 8])
+def test_gf_block_operator_off_grid(gsf, m, prec):
+    """The GF apply of 4 and 8 columns with the operator's workspace (which holds
+    the coefficients between the two passes) off the 16-byte grid."""
+    import torch
+    shape, radius = (70, 255), 3
+    rng = np.random.default_rng(m)
+    g = _round(rng.uniform(0.0, 1.0, shape), prec, gsf)
+    x = _round(rng.standard_normal((g.size, m)), prec, gsf)
+    need = gsf.Operator("gf", shape, _torch(g.ravel(), prec, gsf), radius=radius, eps=1e-2, prec=prec).ws.numel()
+    ws = torch.empty(need + 16, dtype=torch.uint8, device="cuda")[8:8 + need]
+    op = gsf.Operator("gf", shape, _torch(g.ravel(), prec, gsf), radius=radius, eps=1e-2, prec=prec, ws=ws)
+    assert op.ws.data_ptr() == ws.data_ptr()
+    ref = oracle.build_operator("gf", g, radius, eps=1e-2)
+    for form in (gsf.FORM_N, gsf.FORM_LSYM, gsf.FORM_RW, gsf.FORM_L):
+        y = op.apply(_torch(x, prec, gsf), form).cpu().numpy()
+        for j in (0, m - 1):
+            r = ref.apply(form, x[:, j])
+            e = np.linalg.norm(y[:, j] - r) / max(np.linalg.norm(r), np.linalg.norm(x[:, j]))
+            assert e <= TOL[prec], (form, j, e)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 def test_lobpcg_soft_locking_parity(gsf, prec):
     """LOBPCG to a tolerance, where columns reach it at different steps and
     are soft-locked (their W columns count as zero): the GPU stops at the
