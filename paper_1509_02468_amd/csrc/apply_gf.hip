@@ -566,9 +566,7 @@ __global__ void __launch_bounds__(kGfBlkThreads, 2) gf_block_kernel(GfBlkArgs a)
         for (int i = 0; i < V; i += 2) w[i / 2] = make_double2(s[p][i][0], s[p][i + 1][0]);
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_barrier();
     if (nout > 0) {
       const int vc = (ya < a.rows ? ya : a.rows - 1) - (yd < 0 ? 0 : yd) + 1;
       const double rv = 1.0 / (double)vc, srv = sqrt(rv);

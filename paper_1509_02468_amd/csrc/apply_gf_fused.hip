@@ -81,23 +81,12 @@ __device__ __forceinline__ int fcount(int v, int len, int r) {
   return hi - lo + 1;
 }
 
-// DPP lane move of a double, 0 where the source lane is outside the row or
-// the destination row is masked off
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ double dpp0(double v) {
-  const long long b = __double_as_longlong(v);
-  constexpr bool zero_fill = ROWMASK == 0xf;
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWMASK, 0xf, zero_fill);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWMASK, 0xf, zero_fill);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // inclusive prefix sums over the 64 lanes of a wave: shifts by 1, 2, 4, 8
 // within rows of 16 lanes, then the row totals broadcast to the rows above;
 // two at a time, each filling the other's latency
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ void scan_step(double& v, double& w) {
-  const double a = dpp0<CTRL, ROWMASK>(v), b = dpp0<CTRL, ROWMASK>(w);
+  const double a = dpp_move<CTRL, ROWMASK>(v), b = dpp_move<CTRL, ROWMASK>(w);
   v += a;
   w += b;
 }

@@ -52,13 +52,27 @@ inline int bf_num_planes(const gsf_operator_desc& d) {
 // ---------------------------------------------------------------------------
 // device helpers
 // ---------------------------------------------------------------------------
-// v of the lane that a DPP row rotation by N brings here (rows of 16 lanes)
+// v of the lane that a DPP control (rows of 16 lanes) brings here; 0 where that
+// lane is outside the row or this lane's row is masked off
+template <int CTRL, int ROWMASK = 0xf>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  constexpr bool zero_fill = ROWMASK == 0xf;
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWMASK, 0xf, zero_fill);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWMASK, 0xf, zero_fill);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 template <int N>
 __device__ __forceinline__ double row_rotate(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xf, 0xf, false);
-  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, false);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  return dpp_move<0x120 + N>(v);
+}
+
+// Workgroup barrier that orders LDS only: loads and stores of global memory
+// stay in flight across it (a plain __syncthreads waits for all of them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // v plus the other half's (ROWS = 32) or the neighbour row's (ROWS = 16) v

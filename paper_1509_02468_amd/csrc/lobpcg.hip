@@ -359,12 +359,6 @@ struct RRShared {
   double C[8][KMAX];       // the Ritz coefficients, before their signs
 };
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
 __device__ __forceinline__ double readlane_d(double v, int l) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
@@ -372,26 +366,20 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
 }
 // Sum (maximum) over each row of 16 lanes, in every lane of the row.
 __device__ __forceinline__ double row_sum(double v) {
-  v += dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v += dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v += dpp_d<0x141>(v);  // row_half_mirror: the other quad of the half row
-  v += dpp_d<0x140>(v);  // row_mirror: the other half of the row
+  v += dpp_move<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_move<0x141>(v);  // row_half_mirror: the other quad of the half row
+  v += dpp_move<0x140>(v);  // row_mirror: the other half of the row
   return v;
 }
 __device__ __forceinline__ double row_max(double v) {
-  v = fmax(v, dpp_d<0xB1>(v));
-  v = fmax(v, dpp_d<0x4E>(v));
-  v = fmax(v, dpp_d<0x141>(v));
-  return fmax(v, dpp_d<0x140>(v));
+  v = fmax(v, dpp_move<0xB1>(v));
+  v = fmax(v, dpp_move<0x4E>(v));
+  v = fmax(v, dpp_move<0x141>(v));
+  return fmax(v, dpp_move<0x140>(v));
 }
-// The same over the wave's first KB lanes, in every lane; the lanes from KB to
-// 31 must hold 0 (or a value already counted, for the maximum).
-template <int KB>
-__device__ __forceinline__ double sum_rows(double v) {
-  v = row_sum(v);
-  if constexpr (KB <= 16) return readlane_d(v, 0);
-  return readlane_d(v, 0) + readlane_d(v, 16);
-}
+// The maximum over the wave's first KB lanes, in every lane; the lanes past the
+// matrix, up to 31, repeat one of its rows.
 template <int KB>
 __device__ __forceinline__ double max_rows(double v) {
   v = row_max(v);

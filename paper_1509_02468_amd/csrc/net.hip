@@ -7,29 +7,21 @@
 // (offset 0), W2[o][c][ky][kx] (offset 288), W3[c][ky][kx] (offset 2592).
 //
 // Training (loss and weight gradient) is in net_train.hip, Adam here;
-// inference inside LOBPCG runs on one fused kernel per 30x30 output tile that keeps the whole receptive field in
-// LDS and does the three convolutions as implicit GEMMs on bf16 MFMA
-// (v_mfma_f32_16x16x16bf16_1k: 16 output channels x 16 pixels per
-// instruction; layer 3 as 9 per-tap 1x1 products summed over the taps).
+// inference inside LOBPCG runs on one fused kernel per 30x30 output tile that
+// keeps the whole receptive field in LDS and does the three convolutions as
+// implicit GEMMs on bf16 MFMA, 16 output channels x 16 pixels per instruction
+// (layers 1 and 2 v_mfma_f32_16x16x32_bf16; layer 3 v_mfma_f32_16x16x16bf16_1k,
+// as 9 per-tap 1x1 products summed over the taps).
 #include <cmath>
 
-#include "gsf_internal.h"
+#include "net_common.h"
 #include "solver_state.h"
 
 namespace gsf {
 
 int vec_blocks(int64_t n);
 
-constexpr int kOffW1 = 0, kOffW2 = 288, kOffW3 = 2592;
-
 namespace {
-
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx2_t __attribute__((ext_vector_type(2)));
 
 // FP32 -> BF16, round to nearest, ties to even (NaN stays NaN).
 __device__ __forceinline__ uint32_t f2bf(float f) {
@@ -48,10 +40,6 @@ __device__ __forceinline__ uint32_t d2bf(double d) {
     u = fabs(d) > fabs((double)f) ? u + 1u : u - 1u;
   return f2bf(__uint_as_float(u));
 }
-
-// ReLU that keeps NaN (so a NaN inside the network reaches the output and
-// triggers the T = I fallback).
-__device__ __forceinline__ float relu(float v) { return __builtin_elementwise_maximum(v, 0.0f); }
 
 // ---------------------------------------------------------------------------
 // optimiser (the training pass is in net_train.hip)
@@ -113,42 +101,14 @@ struct NetInferArgs {
   double* partials;        // [tile][3m]: r_j.w_j, y.w_j, non-finite count
 };
 
-__device__ __forceinline__ floatx4 mfma_bf16(short4_t a, short4_t b, floatx4 c) {
+__device__ __forceinline__ floatx4_t mfma_bf16(short4_t a, short4_t b, floatx4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ floatx4 mfma_bf16_k32(uint4_t a, uint4_t b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
-                                                 0, 0, 0);
-}
-// two FP32 values rounded to BF16 (nearest even), the first in the low half
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  const floatx2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
 constexpr int kNetThreads = 512;    // 8 waves per tile
 constexpr int kNetWaves = kNetThreads / 64;
 constexpr int kXIter = (kXN + kNetThreads - 1) / kNetThreads;
 constexpr int kOIter = (kOT * kOT + kNetThreads - 1) / kNetThreads;
-
-// i / D for 0 <= i < N by one 24-bit product
-constexpr bool div_exact(int d, int n) {
-  for (int i = 0; i < n; ++i)
-    if (i / d != (i * ((65536 + d - 1) / d)) >> 16) return false;
-  return true;
-}
-template <int D, int N>
-__device__ __forceinline__ int div_px(int i) {
-  static_assert(div_exact(D, N), "the reciprocal is exact over the range");
-  return __mul24(i, (65536 + D - 1) / D) >> 16;
-}
-
-// Workgroup barrier that orders LDS only (the next column's loads stay in flight)
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // One tile of all m columns.  Per column two phases, with one barrier between:
 //   layer 2 of column j (a1 -> c3, the layer-3 products) and the input of
@@ -261,8 +221,8 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
       uint4_t b;
 #pragma unroll
       for (int i = 0; i < 4; ++i) b[i] = xs[xo[i] >= 0 ? base + xo[i] : kXN];
-      const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-      const floatx4 c = mfma_bf16_k32(w1, b, zero);
+      const floatx4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      const floatx4_t c = mfma_bf16_k32(w1, b, zero);
       const bool in = on_image(y0 - 2 + py, x0 - 2 + px);
       uint2 u;
       u.x = in ? pack2(relu(c[0]), relu(c[1])) : 0u;
@@ -288,7 +248,7 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
       const char* b = a1s + (half * kA1P + py * kA1 + px) * 16;
       const char* b1 = b + sel * 16;              // taps (0, 1), (4, 5), (6, 7)
       const char* b2 = b + sel * (kA1 - 2) * 16;  // taps (2, 3)
-      floatx4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+      floatx4_t c = {0.0f, 0.0f, 0.0f, 0.0f};
       c = mfma_bf16_k32(w2[0], *(const uint4_t*)b1, c);
       c = mfma_bf16_k32(w2[1], *(const uint4_t*)(b2 + 2 * 16), c);
       c = mfma_bf16_k32(w2[2], *(const uint4_t*)(b1 + (kA1 + 1) * 16), c);
@@ -300,8 +260,8 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
       uint2 u;
       u.x = in ? pack2(relu(c[0]), relu(c[1])) : 0u;
       u.y = in ? pack2(relu(c[2]), relu(c[3])) : 0u;
-      const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-      const floatx4 t = mfma_bf16(w3a, __builtin_bit_cast(short4_t, u), zero);
+      const floatx4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      const floatx4_t t = mfma_bf16(w3a, __builtin_bit_cast(short4_t, u), zero);
       float* o = c3 + 4 * q * kC3P + g * 16 + l16;
       if (q < 3) o[0] = t[0];
       if (q < 2) {

@@ -31,21 +31,10 @@
 // channel 4i + q: the four values lane group q feeds to one tap's products).
 #include <cmath>
 
-#include "gsf_internal.h"
+#include "net_common.h"
 
 namespace gsf {
-
-constexpr int kNetWeights = 2736;
-constexpr int kOffW2 = 288, kOffW3 = 2592;
-
 namespace {
-
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx2_t __attribute__((ext_vector_type(2)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 512;               // threads: 8 waves
 constexpr int kWaves = kT / 64;
@@ -91,27 +80,8 @@ struct NetTrainArgs {
   int64_t ntiles;
 };
 
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // round to nearest even
-  const floatx2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-// ReLU that keeps NaN
-__device__ __forceinline__ float relu(float v) { return __builtin_elementwise_maximum(v, 0.0f); }
-
-// i / D for the small pixel indexes of a tile (0 <= i < N): one 24-bit product
-// and a shift (a general division by a constant takes a 64-bit product)
-constexpr bool div_exact(int d, int n) {
-  for (int i = 0; i < n; ++i)
-    if (i / d != (i * ((65536 + d - 1) / d)) >> 16) return false;
-  return true;
-}
-template <int D, int N>
-__device__ __forceinline__ int div_px(int i) {
-  static_assert(div_exact(D, N), "the reciprocal is exact over the range");
-  return __mul24(i, (65536 + D - 1) / D) >> 16;
-}
 
 // f = h + m + l exactly, each part's bits the upper half of a word: the two
 // remainders of a truncation to 8 significant bits are exact (16, then 8 bits)
@@ -129,10 +99,6 @@ __device__ __forceinline__ Split split3(float f) {
 }
 // two BF16 values (upper halves of a and b) as one word, a first
 __device__ __forceinline__ uint32_t join(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
-__device__ __forceinline__ floatx4_t mfma32(uint4_t a, uint4_t b, floatx4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
-                                                 0, 0, 0);
-}
 
 // Transposing LDS read: lane i of a group of 16 gets channel i of four
 // consecutive pixels (lane i's address: pixel i / 4, channels 4 (i % 4)..).
@@ -143,15 +109,6 @@ __device__ __forceinline__ uint2 read_tr(const char* p) {
 __device__ __forceinline__ uint4_t read_tr8(const char* p) {  // pixels p..p+3 and p+4..p+7
   const uint2 a = read_tr(p), b = read_tr(p + 4 * 16);
   return uint4_t{a.x, a.y, b.x, b.y};
-}
-
-// Workgroup barrier that orders LDS only: the operand packs and the next
-// tile's input, loaded ahead, stay in flight across it (a plain __syncthreads
-// waits for every outstanding load).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // MFMA operand packs of the BF16 weights (one thread per lane and pack)
@@ -450,7 +407,7 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
         const float* d = dys + __mul24(py, YW) + px;
         const Split s0 = split3(d[o0]), s1 = split3(d[o1]), s8 = split3(d[0]);
         const floatx4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
-        const floatx4_t c = mfma32(w, uint4_t{join(s0.h, s0.m), join(s0.l, s1.h), join(s1.m, s1.l),
+        const floatx4_t c = mfma_bf16_k32(w, uint4_t{join(s0.h, s0.m), join(s0.l, s1.h), join(s1.m, s1.l),
                                               join(q == 1 ? s8.l : s8.h, s8.m)}, zero);
         const uint2 act = *(const uint2*)(a2s + (sel * A2P + __mul24(py + 2, A2W) + px + 2) * 16 + half * 8);
         const Split d0 = split3(bf_lo(act.x) > 0.0f ? c[0] : 0.0f), d1 = split3(bf_hi(act.x) > 0.0f ? c[1] : 0.0f);
@@ -483,9 +440,9 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
           const uint4_t b = read_tr8(ap + ((tap / 3) * A1W + tap % 3) * 16);
-          g2[tap] = mfma32(z0, b, g2[tap]);
-          g2[tap] = mfma32(z1, b, g2[tap]);
-          g2[tap] = mfma32(z2, b, g2[tap]);
+          g2[tap] = mfma_bf16_k32(z0, b, g2[tap]);
+          g2[tap] = mfma_bf16_k32(z1, b, g2[tap]);
+          g2[tap] = mfma_bf16_k32(z2, b, g2[tap]);
         }
         // dW3[c][tap] = sum_p dy[p] a2[p + off(tap)][c]: rows 3 kx + part of
         // the tile hold the three parts' sums for tap column kx
@@ -503,7 +460,7 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
           const uint4_t b = read_tr8(bp + ((tap / 3) * A2W + tap % 3) * 16);
-          g3[tap / 3] = mfma32(l16 / 3 == tap % 3 ? pa : none, b, g3[tap / 3]);
+          g3[tap / 3] = mfma_bf16_k32(l16 / 3 == tap % 3 ? pa : none, b, g3[tap / 3]);
         }
       }
 #pragma unroll
@@ -536,14 +493,14 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
         const uint4_t w = ops[(OP_B2 + tap) * 64 + lane];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          c[u] = mfma32(*(const uint4_t*)(pb[u] + o01 - ((tap / 3) * DW + tap % 3) * 16), w, c[u]);
+          c[u] = mfma_bf16_k32(*(const uint4_t*)(pb[u] + o01 - ((tap / 3) * DW + tap % 3) * 16), w, c[u]);
       }
 #pragma unroll
       for (int j = 0; j < 5; ++j) {
         const uint4_t w = ops[(OP_B2L + j) * 64 + lane];
         const int off = j < 3 ? j * DW + sel : (j == 3 ? 2 + sel * DW : 2 * DW + 2);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) e[u] = mfma32(*(const uint4_t*)(pb[u] + o2 - off * 16), w, e[u]);
+        for (int u = 0; u < 4; ++u) e[u] = mfma_bf16_k32(*(const uint4_t*)(pb[u] + o2 - off * 16), w, e[u]);
       }
       floatx4_t g1[2];
       g1[0] = g1[1] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -573,7 +530,7 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
           const uint4_t b = {xc[ch][0].x, xc[ch][0].y, xc[ch][1].x, xc[ch][1].y};
 #pragma unroll
           for (int k = 0; k < 3; ++k)
-            g1[ch] = mfma32(uint4_t{zp[k][0].x, zp[k][0].y, zp[k][1].x, zp[k][1].y}, b, g1[ch]);
+            g1[ch] = mfma_bf16_k32(uint4_t{zp[k][0].x, zp[k][0].y, zp[k][1].x, zp[k][1].y}, b, g1[ch]);
         }
       }
 #pragma unroll
