@@ -433,7 +433,8 @@ struct RRGrid {
 // g, which leaves L^-T: step k takes row k of both matrices (symmetric: also
 // column k) and m_c = B_kc / B_kk for c > k, and subtracts m_r B_kc from B,
 // m_r A_kc + m_c (A_kr - m_r A_kk) from A and m_c g_rk from g.  A column whose
-// pivot is at most drop_tol is left out (its factors are zero, no branch).
+// pivot is at most drop_tol, or not a number, is left out: no entry of another
+// column is touched (zero factors would carry a NaN on).
 // Every thread stores its entries after a step (double-buffered: one barrier
 // per column), which takes fewer instructions than choosing the row's owners.
 // Returns the kept columns; their pivots in sh.diag.
@@ -470,9 +471,10 @@ __device__ __forceinline__ unsigned rr_reduce(RRShared& sh, double (&a)[RRGrid<K
       ac[i] = ra[ci[i]];
       gr[i] = cg[ri[i] * LD];
     }
-    const bool keep = ((goodm >> k) & 1u) && piv > drop_tol;
-    keptm |= __ballot(keep) ? 1u << k : 0u;
-    const double rp = keep ? rcp_nr(piv) : 0.0;
+    const bool keep = __ballot(((goodm >> k) & 1u) && piv > drop_tol) != 0;  // (every thread alike)
+    if (!keep) continue;
+    keptm |= 1u << k;
+    const double rp = rcp_nr(piv);
     double mr[E], mc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) {
@@ -910,7 +912,8 @@ __device__ __forceinline__ unsigned rayleigh_ritz(RRShared& sh, const double (&g
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       const int r = tr + 16 * i, c = tc + 16 * j;
-      const bool in = r < ns && c < ns;
+      // (a negligible or non-finite column is zeros)
+      const bool in = ((goodm >> r) & 1u) && ((goodm >> c) & 1u);
       const double at = sh.A[1][in ? c * LD + r : 0], bt = sh.B[1][in ? c * LD + r : 0];
       const double sc = dr[i] * dc[j];
       a[i][j] = in ? (r == c ? ga[i][j] : 0.5 * (ga[i][j] + at)) * sc : 0.0;

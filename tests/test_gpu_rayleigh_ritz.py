@@ -87,3 +87,28 @@ def test_small_ritz_values_of_a_diagonal_pencil(gsf, ns, m):
         th = gsf.rayleigh_ritz(np.diag(lam), np.eye(ns), m, 1e-10, 1e-13)[0]
         ref = np.sort(lam)[:m]
         assert np.all(np.abs(th - ref) <= 1.3e-18 + 2 * np.spacing(ref))
+
+
+@pytest.mark.parametrize("ns,m", [(6, 2), (9, 3), (12, 4), (17, 5), (24, 8)])
+def test_columns_that_are_not_numbers(gsf, ns, m):
+    """A column of NaN products is dropped and leaves the others as they are
+    without it; so is the later one of two columns whose product alone is NaN."""
+    rng = np.random.default_rng(3 * ns)
+    S = rng.standard_normal((200, ns))
+    lam = np.linspace(0.0, 1.5, 200)
+    GA, GB = S.T @ (lam[:, None] * S), S.T @ S
+    for j in (0, 3, ns - 1):
+        rest = np.arange(ns) != j
+        ref = oracle.rayleigh_ritz(GA[np.ix_(rest, rest)], GB[np.ix_(rest, rest)], m, 1e-10, 1e-13)[0]
+        for what in ("column", "entry"):
+            A, B = GA.copy(), GB.copy()
+            if what == "column":
+                A[j], A[:, j], B[j], B[:, j] = (np.nan,) * 4
+            elif j > 0:
+                B[j, 0] = B[0, j] = np.nan
+            else:
+                continue
+            th, C, kept, nk = gsf.rayleigh_ritz(A, B, m, 1e-10, 1e-13)
+            assert nk == ns - 1 and np.array_equal(kept.astype(bool), rest), (j, what)
+            assert np.abs(th - ref).max() <= TOL * np.linalg.norm(GA, 2) and not C[j].any()
+            assert np.isfinite(C).all()
