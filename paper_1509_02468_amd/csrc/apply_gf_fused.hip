@@ -8,9 +8,12 @@
 //
 // A workgroup is one wave: it owns a strip of 256 columns, four adjacent ones
 // per lane, and a chunk of rows, and walks the window-centre rows k_y top to
-// bottom.  Horizontal window sums are differences of a prefix sum along the
-// strip row (three adds in the lane, then one scan of the lanes' totals by DPP
-// shifts), so no lane loops over a window.  Per centre row:
+// bottom.  Horizontal window sums are differences of prefix sums along pieces of
+// 64 columns of the strip row (three adds in the lane, then one scan of the
+// lanes' totals by DPP shifts within rows of 16 lanes), plus the left piece's
+// total where a window's ends lie in two, so no lane loops over a window and a
+// huge or non-finite value reaches no further right than the end of the piece
+// after its own (and the window).  Per centre row:
 //   A  running FP64 vertical window sums of u = D^-1/2 x and g u over input
 //      rows k_y - r .. k_y + r (add the entering row, subtract the leaving
 //      one), their prefix sums;
@@ -81,22 +84,19 @@ __device__ __forceinline__ int fcount(int v, int len, int r) {
   return hi - lo + 1;
 }
 
-// inclusive prefix sums over the 64 lanes of a wave: shifts by 1, 2, 4, 8
-// within rows of 16 lanes, then the row totals broadcast to the rows above;
-// two at a time, each filling the other's latency
-template <int CTRL, int ROWMASK>
+// inclusive prefix sums over each row of 16 lanes: shifts by 1, 2, 4, 8; two at
+// a time, each filling the other's latency
+template <int CTRL>
 __device__ __forceinline__ void scan_step(double& v, double& w) {
-  const double a = dpp_move<CTRL, ROWMASK>(v), b = dpp_move<CTRL, ROWMASK>(w);
+  const double a = dpp_move<CTRL>(v), b = dpp_move<CTRL>(w);
   v += a;
   w += b;
 }
-__device__ __forceinline__ void wave_scan2(double& v, double& w) {
-  scan_step<0x111, 0xf>(v, w);
-  scan_step<0x112, 0xf>(v, w);
-  scan_step<0x114, 0xf>(v, w);
-  scan_step<0x118, 0xf>(v, w);
-  scan_step<0x142, 0xa>(v, w);
-  scan_step<0x143, 0xc>(v, w);
+__device__ __forceinline__ void row_scan2(double& v, double& w) {
+  scan_step<0x111>(v, w);
+  scan_step<0x112>(v, w);
+  scan_step<0x114>(v, w);
+  scan_step<0x118>(v, w);
 }
 
 // Keeps the order of the wave's LDS accesses (other lanes read what a lane
@@ -234,8 +234,8 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
       q[e] = q[e - 1] + w[e];
     }
     double tp = p[3], tq = q[3];
-    wave_scan2(tp, tq);
-    const double lp = tp - p[3], lq = tq - q[3];
+    row_scan2(tp, tq);
+    const double lp = dpp_move<0x111>(tp), lq = dpp_move<0x111>(tq);  // of the lanes to the left
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
       p[e] += lp;
@@ -251,11 +251,15 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
       P[1][e][PL + lane] = p1[e];
     }
   };
-  // the prefix values at the ends of the windows c - R .. c + R of the lane's columns c
+  // the prefix values at the ends of the windows c - R .. c + R of the lane's
+  // columns c, and the total of the piece that a window leaves for the next one
   struct Ends {
-    double hi[2][4], lo[2][4];
+    double hi[2][4], lo[2][4], total[2];
   };
+  const int l16 = lane & 15, last = l16 < 8 ? (lane & ~15) - 1 : lane | 15;  // the lane that holds it
   auto get = [&](Ends& w) {
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch) w.total[ch] = P[ch][3][PL + last];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
 #pragma unroll
@@ -264,6 +268,11 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
         w.lo[ch][e] = P[ch][(e - R - 1) & 3][PL + lane + ((e - R - 1) >> 2)];
       }
     }
+  };
+
+  auto box = [&](const Ends& w, int ch, int e) {
+    const bool two = l16 + ((e - R - 1) >> 2) < 0 || l16 + ((e + R) >> 2) > 15;  // the window's ends lie in two pieces
+    return (w.hi[ch][e] - w.lo[ch][e]) + (two ? w.total[ch] : 0.0);
   };
 
   for (int e = lane; e < 8 * PW; e += 64) (&P[0][0][0])[e] = 0.0;
@@ -345,7 +354,7 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const double mean_u = (wa.hi[0][e] - wa.lo[0][e]) * rc[e], mean_gu = (wa.hi[1][e] - wa.lo[1][e]) * rc[e];
+        const double mean_u = box(wa, 0, e) * rc[e], mean_gu = box(wa, 1, e) * rc[e];
         const double mk = (double)cur.mu[e], ik = (double)cur.inv[e];
         const double ak = (mean_gu - mk * mean_u) * ik;
         av[e] = (float)ak;
@@ -392,7 +401,7 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const double sa = w.hi[0][e] - w.lo[0][e], sb = w.hi[1][e] - w.lo[1][e];
+        const double sa = box(w, 0, e), sb = box(w, 1, e);
         nx[e] = ((double)cur.eg[e] * sa + sb) * c[e];
       }
       if (lap) {

@@ -53,13 +53,12 @@ inline int bf_num_planes(const gsf_operator_desc& d) {
 // device helpers
 // ---------------------------------------------------------------------------
 // v of the lane that a DPP control (rows of 16 lanes) brings here; 0 where that
-// lane is outside the row or this lane's row is masked off
-template <int CTRL, int ROWMASK = 0xf>
+// lane is outside the row
+template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  constexpr bool zero_fill = ROWMASK == 0xf;
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWMASK, 0xf, zero_fill);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWMASK, 0xf, zero_fill);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 template <int N>

@@ -568,6 +568,32 @@ def test_gf_one_column_strips(gsf, shape, radius):
     assert info.iters == rinfo.iters and e <= TOL[gsf.F32], e
 
 
+@pytest.mark.parametrize("shape,radius", [((41, 700), 8), ((41, 699), 8), ((30, 480), 1), ((900,), 5)])
+def test_gf_one_column_reach_of_a_value(gsf, shape, radius):
+    """The one-pass GF apply takes its horizontal sums from prefix sums of 64
+    columns: a pixel in column c enters the centres from c - r to r + 1 past the
+    end of its piece, these the outputs to r + 1 past the end of the next piece.
+    Every output left of c - 2r or right of c + 128 + r is the one of the clean
+    image, to the bit: a large value first (it would take digits off the sums
+    to its right), then ones that are not finite."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    n, cols = int(np.prod(shape)), shape[-1]
+    g = torch.rand(n, device="cuda", generator=gen)
+    x = torch.rand(n, device="cuda", generator=gen)
+    op = gsf.Operator("gf", shape, g, radius=radius, eps=1e-2, prec=gsf.F32)
+    clean = op.apply(x.reshape(-1, 1), gsf.FORM_N).reshape(-1, cols)
+    row = (n // cols) // 2
+    for c in (0, 20, 63, 64, 200, 230, cols - 1):
+        for v in (1e30, float("inf"), float("nan")):
+            bad = x.clone()
+            bad[row * cols + c] = v
+            y = op.apply(bad.reshape(-1, 1), gsf.FORM_N).reshape(-1, cols)
+            lo, hi = max(c - 2 * radius, 0), c + 128 + radius + 1
+            assert torch.equal(y[:, :lo], clean[:, :lo]), (c, v)
+            assert torch.equal(y[:, hi:], clean[:, hi:]), (c, v)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("m", [4, 8])
 @pytest.mark.parametrize("shape,radius", [((3, 2), 8), ((9, 239), 8), ((40, 240), 8), ((33, 241), 3), ((70, 255), 1),
