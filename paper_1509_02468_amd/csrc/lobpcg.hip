@@ -398,6 +398,9 @@ constexpr double kPadDiag = 1e4;  // diagonal of the padding rows: far above any
 // With Ritz values in [0, 2] and at most 24 rows the minors stay within about
 // 1e+-100 (the padding rows multiply by ~1e4 each), so no rescaling is needed.
 constexpr double kMinE2 = 1e-60;
+// A coupling below this is none to the inverse iteration: as a pivot, 1e140 in
+// the back substitution, it overflowed the vector's norm.
+constexpr double kNoCoupling = 1e-100;
 template <int KB>
 __device__ __forceinline__ int sturm_count(const double (&d)[KB], const double (&e2)[KB], double sigma) {
   double pm2 = 1.0, pm1 = d[0] - sigma;
@@ -573,16 +576,18 @@ __device__ __forceinline__ void rr_tridiagonalize(RRShared& sh, double (&a)[RRGr
     double kc = 0.0;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      pc[i] = cin[i] ? sh.pv[ci[i]] : 0.0;
+      pr[i] *= beta;
+      pc[i] = cin[i] ? beta * sh.pv[ci[i]] : 0.0;
       kc = fma(vc[i], pc[i], kc);
     }
-    // M - v w^T - w v^T with w = beta M v - (beta^2 / 2) (v^T M v) v
-    kc = 0.5 * beta * beta * row_sum(kc);
+    // M - v w^T - w v^T with w = p - (beta / 2) (v^T p) v, p = beta M v (beta^2
+    // overflows for a coupling below 1e-77)
+    kc = 0.5 * beta * row_sum(kc);
 #pragma unroll
     for (int i = 0; i < E; ++i)
 #pragma unroll
       for (int q = 0; q < E; ++q) {
-        const double wr = fma(-kc, vr[i], beta * pr[i]), wc = fma(-kc, vc[q], beta * pc[q]);
+        const double wr = fma(-kc, vr[i], pr[i]), wc = fma(-kc, vc[q], pc[q]);
         a[i][q] = fma(-vr[i], wc, fma(-wr, vc[q], a[i][q]));
       }
   }
@@ -611,7 +616,8 @@ __device__ __forceinline__ void rr_eig_pairs(RRShared& sh, int K, int m) {
 #pragma unroll
   for (int i = 0; i < KB; ++i) {
     d[i] = i < K ? sh.td[i] : kPadDiag;
-    eo[i] = i + 1 < K ? sh.te[i] : 0.0;  // T[i+1][i] = T[i][i+1]
+    const double o = i + 1 < K ? sh.te[i] : 0.0;  // T[i+1][i] = T[i][i+1]
+    eo[i] = fabs(o) < kNoCoupling ? 0.0 : o;
     e2[i] = fmax(eo[i] * eo[i], kMinE2);
   }
   double lo, hi, tnorm;

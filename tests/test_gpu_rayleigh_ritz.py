@@ -112,3 +112,12 @@ def test_columns_that_are_not_numbers(gsf, ns, m):
             assert nk == ns - 1 and np.array_equal(kept.astype(bool), rest), (j, what)
             assert np.abs(th - ref).max() <= TOL * np.linalg.norm(GA, 2) and not C[j].any()
             assert np.isfinite(C).all()
+
+
+@pytest.mark.parametrize("coupling", [1e-70, 1e-90, 1e-140])
+@pytest.mark.parametrize("ns,m", [(3, 1), (6, 2), (12, 4), (24, 8)])
+def test_couplings_near_nothing(gsf, ns, m, coupling):
+    """Columns coupled by a product far below rounding, but not by zero."""
+    rng = np.random.default_rng(5 * ns)
+    E = rng.standard_normal((ns, ns)) * coupling
+    _check(gsf, np.diag(rng.uniform(0.1, 2.0, ns)) + 0.5 * (E + E.T), np.eye(ns), m)
