@@ -387,16 +387,17 @@ __device__ __forceinline__ double max_rows(double v) {
   return fmax(readlane_d(v, 0), readlane_d(v, 16));
 }
 
-constexpr double kPadDiag = 1e4;  // diagonal of the padding rows: far above any Ritz value of L_sym (<= 2)
+constexpr double kPadDiag = 1e4;  // diagonal of the padding rows: far above any eigenvalue of a T of norm below 1
 
 // Number of eigenvalues of T below sigma: sign changes of the leading
 // principal minors p_i of T - sigma I (Sturm), by the three-term recurrence
 // p_i = (d_i - sigma) p_(i-1) - e_(i-1)^2 p_(i-2), no divisions.  A zero minor
 // needs no case of its own: with every e^2 > 0 the minor after it has the sign
 // opposite to the one before it, one change in all whichever sign the zero
-// carries (e2 holds max(e^2, kMinE2); a coupling of 1e-30 moves no eigenvalue).
-// With Ritz values in [0, 2] and at most 24 rows the minors stay within about
-// 1e+-100 (the padding rows multiply by ~1e4 each), so no rescaling is needed.
+// carries (e2 holds max(e^2, kMinE2); a coupling of 1e-30 moves no eigenvalue of
+// a T whose norm is in [0.5, 1): the caller scales it).  With at most 24 rows the
+// minors then stay within about 1e+-100 (the padding rows multiply by ~1e4
+// each), so no rescaling is needed between them.
 constexpr double kMinE2 = 1e-60;
 // A coupling below this is none to the inverse iteration: as a pivot, 1e140 in
 // the back substitution, it overflowed the vector's norm.
@@ -608,19 +609,14 @@ __device__ __forceinline__ void rr_tridiagonalize(RRShared& sh, double (&a)[RRGr
 // shifts of the bracket, which shrinks by 65 (33) per round, down to 2^-60 of
 // the Gershgorin interval), then two steps of inverse iteration from a fixed
 // start vector (Gaussian elimination with partial pivoting of T - lambda I in
-// registers).  Rows past K are padded with a diagonal far above the spectrum.
+// registers).  T is taken at a norm in [0.5, 1), by an exact power of two: the
+// counts and the padding hold at any scale of the pencil (a graph of weights of
+// 1e-30, say).  Rows past K are padded with a diagonal far above the spectrum.
 template <int KB>
 __device__ __forceinline__ void rr_eig_pairs(RRShared& sh, int K, int m) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double d[KB], e2[KB], eo[KB];
-#pragma unroll
-  for (int i = 0; i < KB; ++i) {
-    d[i] = i < K ? sh.td[i] : kPadDiag;
-    const double o = i + 1 < K ? sh.te[i] : 0.0;  // T[i+1][i] = T[i][i+1]
-    eo[i] = fabs(o) < kNoCoupling ? 0.0 : o;
-    e2[i] = fmax(eo[i] * eo[i], kMinE2);
-  }
-  double lo, hi, tnorm;
+  double lo, hi, tnorm, unit;
   {
     // Gershgorin, lane = row (lanes past K repeat row 0)
     const int i = lane < K ? lane : 0;
@@ -629,6 +625,20 @@ __device__ __forceinline__ void rr_eig_pairs(RRShared& sh, int K, int m) {
     lo = -max_rows<KB>(r - di);
     hi = max_rows<KB>(di + r);
     tnorm = fmax(fabs(lo), fabs(hi));
+    const int ex = __builtin_amdgcn_frexp_exp(tnorm);  // 0 for a zero or non-finite norm
+    const int e = ex < -1000 ? -1000 : (ex > 1000 ? 1000 : ex);
+    unit = ldexp(1.0, e);
+    const double inv = ldexp(1.0, -e);
+    lo *= inv;
+    hi *= inv;
+    tnorm *= inv;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      d[k] = k < K ? sh.td[k] * inv : kPadDiag;
+      const double o = k + 1 < K ? sh.te[k] * inv : 0.0;  // T[k+1][k] = T[k][k+1]
+      eo[k] = fabs(o) < kNoCoupling ? 0.0 : o;
+      e2[k] = fmax(eo[k] * eo[k], kMinE2);
+    }
   }
   const int half = m > 4 ? 1 : 0;            // two eigenvalues per wave
   const int G = half ? 32 : 64;              // lanes per eigenvalue
@@ -718,7 +728,7 @@ __device__ __forceinline__ void rr_eig_pairs(RRShared& sh, int K, int m) {
     for (int i = 0; i < KB; ++i) y[i] *= sc;
   }
   if (s == 0 && t < m) {
-    sh.ev[t] = lam;
+    sh.ev[t] = lam * unit;
 #pragma unroll
     for (int i = 0; i < KB; ++i) sh.Y[t][i] = i < K ? y[i] : 0.0;
     if constexpr (KB < KMAX)

@@ -114,6 +114,18 @@ def test_columns_that_are_not_numbers(gsf, ns, m):
             assert np.isfinite(C).all()
 
 
+@pytest.mark.parametrize("power", [-300, -100, -40, 30])
+@pytest.mark.parametrize("ns,m", [(3, 1), (4, 2), (9, 3), (12, 4), (17, 5), (24, 8)])
+def test_pencils_of_any_scale(gsf, ns, m, power):
+    """GA 2^power: a graph whose weights are all tiny, or a pencil far above one;
+    the gates are relative to the pencil's norm."""
+    rng = np.random.default_rng(11 * ns + m)
+    S = rng.standard_normal((200, ns))
+    lam = np.linspace(0.0, 1.5, 200)
+    GA, GB = S.T @ (lam[:, None] * S), S.T @ S
+    _check(gsf, np.ldexp(GA, power), GB, m)
+
+
 @pytest.mark.parametrize("coupling", [1e-70, 1e-90, 1e-140])
 @pytest.mark.parametrize("ns,m", [(3, 1), (6, 2), (12, 4), (24, 8)])
 def test_couplings_near_nothing(gsf, ns, m, coupling):
