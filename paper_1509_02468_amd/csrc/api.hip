@@ -213,8 +213,11 @@ gsf_status apply_any(const Operator& op, int form, int m, const void* x, int64_t
 }
 
 // GF: the one-column apply's own x^T y partials are taken where the partials'
-// buffer (two values per vector workgroup) holds them; x and y are then not
-// read once more (4096^2, FP32: a dot launch of 52 us per CG step).
+// buffer (two values per vector workgroup, 1024 at most) holds them; x and y are
+// then not read once more (4096^2, FP32: a dot launch of 52 us per CG step).
+// More workgroups, and so the separate dot launch: images whose strips times
+// rows exceed 2^18 (at r = 8 squares above 7660^2, single strips of more than
+// 2^18 rows) and signals of more than 1024 strips (229376 samples at r = 8).
 bool gf_dots(const Operator& op) {
   const int own = gf_dot_parts(op);
   return own > 0 && own <= 2 * vec_blocks(op.n);

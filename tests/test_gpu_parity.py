@@ -594,6 +594,20 @@ def test_gf_one_column_reach_of_a_value(gsf, shape, radius):
             assert torch.equal(y[:, hi:], clean[:, hi:]), (c, v)
 
 
+@pytest.mark.parametrize("shape,radius", [((229376,), 8), ((229377,), 8), ((262144, 3), 1), ((262400, 3), 1)])
+def test_gf_one_column_dot_by_apply_or_launch(gsf, shape, radius):
+    """CG on the FP32 GF operator on both sides of 1024 apply workgroups: up to
+    there the apply sums p^T q, above it a dot launch does."""
+    rng = np.random.default_rng(31)
+    g = _round(rng.uniform(0.0, 1.0, shape), gsf.F32, gsf)
+    op = gsf.Operator("gf", shape, _torch(g.ravel(), gsf.F32, gsf), radius=radius, eps=1e-2, prec=gsf.F32)
+    ref = oracle.build_operator("gf", g, radius, eps=1e-2)
+    y, info = op.cg_filter(_torch(g.ravel(), gsf.F32, gsf), 5)
+    r, rinfo = oracle.cg_filter(ref, g.ravel(), 5, data_prec="f32")
+    e = rel(y.cpu().numpy(), r)
+    assert info.iters == rinfo.iters and e <= TOL[gsf.F32], e
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("m", [4, 8])
 @pytest.mark.parametrize("shape,radius", [((3, 2), 8), ((9, 239), 8), ((40, 240), 8), ((33, 241), 3), ((70, 255), 1),
