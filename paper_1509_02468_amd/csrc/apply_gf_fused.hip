@@ -477,9 +477,9 @@ __global__ void __launch_bounds__(64) gf_fused_kernel(FusedArgs a) {
 }
 
 // Workgroups of one call: as many as the chip holds at once at r = 8 (37 KB of
-// LDS: four per CU), so that no second round is left nearly empty; more, of at
-// most 256 rows, only where the strips alone exceed that.  Short chunks walk
-// 2r rows beside their own but leave no CU idle.
+// LDS: four per CU), so that no second round is left nearly empty; where chunks
+// of at most 256 rows are more than that, the fewest rounds, all of them full.
+// Short chunks walk 2r rows beside their own but leave no CU idle.
 struct FusedGrid {
   int strips, chunks, rb;
 };
@@ -489,8 +489,9 @@ FusedGrid fused_grid(int rows, int cols, int r, bool two_d) {
   FusedGrid g;
   const int nout = kFW - 2 * ((2 * r + 3) & ~3);
   g.strips = (cols + nout - 1) / nout;
-  const int chunks = g.strips < kGroups ? kGroups / g.strips : 1;
-  g.rb = (rows + chunks - 1) / chunks;
+  const int64_t rounds = ((int64_t)rows * g.strips + kGroups * kMaxRows - 1) / (kGroups * kMaxRows);
+  const int64_t chunks = g.strips < rounds * kGroups ? rounds * kGroups / g.strips : 1;
+  g.rb = (int)((rows + chunks - 1) / chunks);
   g.rb = g.rb < kMinRows ? kMinRows : (g.rb > kMaxRows ? kMaxRows : g.rb);
   if (!two_d) g.rb = 1;
   g.chunks = (rows + g.rb - 1) / g.rb;
