@@ -124,14 +124,15 @@ struct FusedShared {
 };
 
 enum FusedMode {
-  kInner,    // every column of the strip is on the grid, x and y contiguous
-  kEdge,     // some are not; contiguous, a multiple of four columns
+  kInner,    // every column of the strip is on the grid
+  kEdge,     // some are not; a multiple of four columns
   kRagged,   // the same, any count of at least four columns
-  kGeneral,  // any strides and widths, element by element
+  kNarrow,   // fewer than four columns, element by element
 };
 
-// R: window radius; RV: vertical radius (R for images, 0 for a 1D signal).
-template <int R, int RV, FusedMode MODE>
+// R: window radius; RV: vertical radius (R for images, 0 for a 1D signal);
+// STRIDED: x and y have strides of their own and go element by element.
+template <int R, int RV, FusedMode MODE, bool STRIDED>
 __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R, RV>& sh) {
   typedef FusedShape<R, RV> Shape;
   constexpr int HL = Shape::HL, NOUT = Shape::NOUT, PL = Shape::PL, PW = Shape::PW, NR = Shape::NR;
@@ -179,25 +180,35 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
   auto clamp_row = [&](int v) { return v < 0 ? 0 : (v >= rows ? rows - 1 : v); };
 
   // the lane's four values of a row of x (or a plane), zeros off the grid
-  auto row_ld = [&](const float* plane, int v, int64_t ld) {
-    const float* p = plane + (size_t)clamp_row(v) * cols * (MODE == kGeneral ? ld : 1);
-    f4 o = {0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (MODE == kGeneral) {
+  auto row_ld = [&](const float* plane, int v) {
+    f4 o = *(const f4u*)(plane + (size_t)clamp_row(v) * cols + cb);
+    if constexpr (MODE == kRagged) {
+      o = skip & 1 ? f4{o[1], o[2], o[3], 0.0f} : o;
+      o = skip & 2 ? f4{o[2], o[3], 0.0f, 0.0f} : o;
+    }
+    if constexpr (MODE != kInner) o = skip >= 4 ? f4{0.0f, 0.0f, 0.0f, 0.0f} : o;
+    return o;
+  };
+  // one by one, unconditionally (loads under a branch each wait for the one before)
+  auto row_ld1 = [&](const float* plane, int v, int64_t ld) {
+    const float* p = plane + (size_t)clamp_row(v) * cols * ld;
+    f4 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (col + e >= 0 && col + e < cols) o[e] = p[(col + e) * ld];
-    } else {
-      o = *(const f4u*)(p + cb);
-      if constexpr (MODE == kRagged) {
-        o = skip & 1 ? f4{o[1], o[2], o[3], 0.0f} : o;
-        o = skip & 2 ? f4{o[2], o[3], 0.0f, 0.0f} : o;
-      }
-      if constexpr (MODE != kInner) o = skip >= 4 ? f4{0.0f, 0.0f, 0.0f, 0.0f} : o;
+    for (int e = 0; e < 4; ++e) {
+      const bool in = MODE == kInner || (col + e >= 0 && col + e < cols);
+      const float w = p[(in ? col + e : 0) * ld];
+      o[e] = in ? w : 0.0f;
     }
     return o;
   };
-  auto row_x = [&](int v) { return row_ld(a.x, v, a.ldx); };
-  auto row_of = [&](const float* plane, int v) { return row_ld(plane, v, 1); };
+  auto row_x = [&](int v) {
+    if constexpr (STRIDED) return row_ld1(a.x, v, a.ldx);
+    else return row_ld(a.x, v);
+  };
+  auto row_of = [&](const float* plane, int v) {
+    if constexpr (MODE == kNarrow) return row_ld1(plane, v, 1);
+    else return row_ld(plane, v);
+  };
 
   // A: the vertical sums of u and g u
   double su[4], sg[4];
@@ -285,7 +296,8 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
   for (int e = 0; e < 4; ++e) Sa[e] = Sb[e] = 0.0;
   double dot = 0.0;
 
-  const int ks = y0 - RV, ke = y1 + RV;  // centre rows of this chunk
+  // centre rows of this chunk (those above the image hold no coefficients)
+  const int ks = y0 < RV ? 0 : y0 - RV, ke = y1 + RV;
   const int wlo = y0 - 2 * RV < 0 ? 0 : y0 - 2 * RV;
   struct In {
     f4 x, g;
@@ -315,14 +327,17 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
   In in[2];
   Out ou[2];
   in[0] = fill_in(ks);
-  in[1] = fill_in(ks + 1);
   ou[0] = fill_out(ks);
-  ou[1] = fill_out(ks + 1);
-  __asm__ volatile("" ::: "memory");  // these are the oldest loads of the first pass too
-  // input rows y0 - 2RV .. y0 - 1 of the first centre row's window
   if constexpr (RV > 0) {
+    in[1] = fill_in(ks + 1);
+    ou[1] = fill_out(ks + 1);
+  }
+  __asm__ volatile("" ::: "memory");  // these are the oldest loads of the first pass too
+  // input rows of the first centre row's window, without its last
+  if constexpr (RV > 0) {
+    const int wend = ks + RV < rows ? ks + RV : rows;
     int yy = wlo;
-    for (; yy + 4 <= y0 && yy + 4 <= rows; yy += 4) {
+    for (; yy + 4 <= wend; yy += 4) {
       f4 xv[4], gv[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -332,10 +347,10 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
 #pragma unroll
       for (int q = 0; q < 4; ++q) take_row(xv[q], gv[q], yy + q, true, false);
     }
-    for (; yy < y0 && yy < rows; ++yy) take_row(row_x(yy), row_of(a.g, yy), yy, true, false);
+    for (; yy < wend; ++yy) take_row(row_x(yy), row_of(a.g, yy), yy, true, false);
   }
   stage_a(in[0], ou[0].ex, ou[0].eg, ks, false);  // no row leaves yet
-  in[0] = fill_in(ks + 2);
+  if constexpr (RV > 0) in[0] = fill_in(ks + 2);
   __asm__ volatile("" ::: "memory");
 
   int slot = 0;
@@ -383,8 +398,10 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
       slot = slot + 1 == NR ? 0 : slot + 1;
     }
     // A of the next row, while the prefix values arrive
-    stage_a(in_next, cur.ex, cur.eg, k + 1, steady);
-    in_next = fill_in(k + 3);
+    if constexpr (RV > 0) {
+      stage_a(in_next, cur.ex, cur.eg, k + 1, steady);
+      in_next = fill_in(k + 3);
+    }
     // E: the output points of row k - RV
     const int yo = k - RV;
     if (steady || (yo >= y0 && yo < y1)) {
@@ -417,7 +434,7 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
       for (int e = 0; e < 4; ++e) out[e] = (float)nx[e];
       if (lane >= HL / 4 && lane < 64 - HL / 4) {
         float* yp = a.y + ((int64_t)yo * cols + col) * a.ldy;
-        if (MODE != kGeneral && whole) {
+        if (!STRIDED && whole) {
           *(f4u*)yp = out;
         } else {
 #pragma unroll
@@ -438,21 +455,26 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
     }
     // after the last use of the old values: the loads land in their registers
     // (asked for earlier they need copies, which wait for them, every row)
-    cur = fill_out(k + 2);
+    if constexpr (RV > 0) cur = fill_out(k + 2);
   };
   // Two rows per pass, each with its own registers.  The pass has one way
   // through (an odd count's last row is past the outputs, and writes nothing):
   // with an exit between the rows every wait allowed for a pass that had
   // skipped the younger loads, and drained them all.  Rows whose windows and
-  // outputs are all away from the borders take straight-line code.
+  // outputs are all away from the borders take straight-line code.  A signal's
+  // one row takes one step.
   const int sk0 = (y0 > RV ? y0 : RV) + RV, sk1 = y1 + RV < rows - 2 * RV - 1 ? y1 + RV : rows - 2 * RV - 1;
-  for (int k = ks; k < ke; k += 2) {
-    if (RV > 0 && k >= sk0 && k + 1 < sk1) {
-      step(k, ou[0], in[1], std::true_type{});
-      step(k + 1, ou[1], in[0], std::true_type{});
-    } else {
-      step(k, ou[0], in[1], std::false_type{});
-      step(k + 1, ou[1], in[0], std::false_type{});
+  if constexpr (RV == 0) {
+    step(ks, ou[0], in[1], std::false_type{});
+  } else {
+    for (int k = ks; k < ke; k += 2) {
+      if (k >= sk0 && k + 1 < sk1) {
+        step(k, ou[0], in[1], std::true_type{});
+        step(k + 1, ou[1], in[0], std::true_type{});
+      } else {
+        step(k, ou[0], in[1], std::false_type{});
+        step(k + 1, ou[1], in[0], std::false_type{});
+      }
     }
   }
   if (a.dots != nullptr) {
@@ -461,19 +483,15 @@ __device__ __forceinline__ void gf_fused_strip(const FusedArgs& a, FusedShared<R
   }
 }
 
-template <int R, int RV, FusedMode FORM>
+template <int R, int RV, FusedMode FORM, bool STRIDED>
 __global__ void __launch_bounds__(64) gf_fused_kernel(FusedArgs a) {
   __shared__ FusedShared<R, RV> sh;
   typedef FusedShape<R, RV> Shape;
-  if constexpr (FORM == kGeneral) {
-    gf_fused_strip<R, RV, kGeneral>(a, sh);
-  } else {
-    const int first = (int)blockIdx.x * Shape::NOUT - Shape::HL;
-    if (first >= 0 && first + kFW <= a.cols)
-      gf_fused_strip<R, RV, kInner>(a, sh);
-    else
-      gf_fused_strip<R, RV, FORM == kRagged ? kRagged : kEdge>(a, sh);
-  }
+  const int first = (int)blockIdx.x * Shape::NOUT - Shape::HL;
+  if (FORM != kNarrow && first >= 0 && first + kFW <= a.cols)
+    gf_fused_strip<R, RV, kInner, STRIDED>(a, sh);
+  else
+    gf_fused_strip<R, RV, FORM, STRIDED>(a, sh);
 }
 
 // Workgroups of one call: as many as the chip holds at once at r = 8 (37 KB of
@@ -502,12 +520,14 @@ template <int R, int RV>
 void launch_fused_r(FusedArgs a, const FusedGrid& g, hipStream_t s) {
   a.rb = g.rb;
   const dim3 grid((unsigned)g.strips, (unsigned)g.chunks);
-  if (a.ldx != 1 || a.ldy != 1 || a.cols < 4)
-    gf_fused_kernel<R, RV, kGeneral><<<grid, 64, 0, s>>>(a);
+  if (a.cols < 4)
+    gf_fused_kernel<R, RV, kNarrow, true><<<grid, 64, 0, s>>>(a);
+  else if (a.ldx != 1 || a.ldy != 1)
+    gf_fused_kernel<R, RV, kRagged, true><<<grid, 64, 0, s>>>(a);
   else if (a.cols % 4 != 0)
-    gf_fused_kernel<R, RV, kRagged><<<grid, 64, 0, s>>>(a);
+    gf_fused_kernel<R, RV, kRagged, false><<<grid, 64, 0, s>>>(a);
   else
-    gf_fused_kernel<R, RV, kEdge><<<grid, 64, 0, s>>>(a);
+    gf_fused_kernel<R, RV, kEdge, false><<<grid, 64, 0, s>>>(a);
 }
 
 void launch_fused(const FusedArgs& a, int r, bool two_d, hipStream_t s) {
