@@ -120,7 +120,7 @@ constexpr int kOIter = (kOT * kOT + kNetThreads - 1) / kNetThreads;
 // it delivers later than the wait before its use allows for (outputs differed
 // from run to run), so that the two forms are never chained.
 // Bound by vector instructions (conversions, addresses, the FP64 scaling) at
-// four waves per SIMD.  An m = 4 block at 2048^2, FP32: 390 us per call, 717
+// four waves per SIMD.  An m = 4 block at 2048^2, FP32: 287 us per call, 717
 // with 28 x 28 tiles, K = 16 products only, 64-bit coordinates, FP64
 // divisions, BF16 rounding by integer operations, the guidance converted
 // again for every column and six barriers per column.
@@ -144,40 +144,6 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
   const int y0 = ty * kOT, x0 = tx * kOT;
   auto on_image = [&](int gy, int gx) { return INNER || ((unsigned)gy < (unsigned)rows && (unsigned)gx < (unsigned)cols); };
 
-  // MFMA A operands (weights): lane holds A[row = l16][k]; k = 8q + i (K = 32), 4q + i (K = 16)
-  uint4_t w1, w2[5];
-  short4_t w3a;
-  {
-    auto pack = [](const uint32_t (&v)[8]) {
-      return uint4_t{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
-    };
-    uint32_t v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int tap = 4 * q + (i >> 1);
-      v[i] = tap < 9 ? a.w[kOffW1 + l16 * 18 + (i & 1) * 9 + tap] : 0u;
-    }
-    w1 = pack(v);
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        v[i] = 2 * t + sel < 9 ? a.w[kOffW2 + l16 * 144 + (8 * half + i) * 9 + 2 * t + sel] : 0u;
-      w2[t] = pack(v);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w3a[i] = l16 < 9 ? (short)a.w[kOffW3 + (4 * q + i) * 9 + l16] : (short)0;
-    }
-  }
-  // layer-1 B operand: the lane's taps 4q + i, past the last one the zero word
-  int xo[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tap = 4 * q + i;
-    xo[i] = tap < 9 ? (tap / 3) * kXS + tap % 3 : -1;
-  }
-
   const T* R = (const T*)a.R;
   T* Z = (T*)a.Z;
   const T* G = (const T*)a.g;
@@ -189,6 +155,12 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
   // the thread's input pixels: offset (or -1) and guidance, alike for every column
   int64_t xi[kXIter];
   uint32_t gv[kXIter];
+  T rv[kXIter];
+  auto load_r = [&](int j) {
+#pragma unroll
+    for (int k = 0; k < kXIter; ++k) rv[k] = R[(xi[k] >= 0 ? xi[k] : 0) + j];
+  };
+  T g0[kXIter];
 #pragma unroll
   for (int k = 0; k < kXIter; ++k) {
     const int e = tid + k * kNetThreads;
@@ -196,13 +168,63 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
     const bool in = e < kXN && on_image(gy, gx);
     const int64_t i = in ? (int64_t)gy * cols + gx : -1;
     xi[k] = i >= 0 ? i * m : -1;
-    gv[k] = in ? d2bf((double)G[i]) << 16 : 0u;
+    g0[k] = G[i >= 0 ? i : 0];
   }
-  T rv[kXIter];
-  auto load_r = [&](int j) {
+  load_r(0);
+  // The weights, through LDS (the products' space): every lane of eight waves
+  // takes 52 of them, and from memory those loads of two bytes, far apart, took
+  // as long as two columns' work (2048^2, FP32: m = 1 200 -> 116 us, m = 4
+  // 371 -> 287).
+  uint16_t* ws = (uint16_t*)c3;
+  {
+    constexpr int kWIter = (kNetWeights + kNetThreads - 1) / kNetThreads;
+    uint16_t wv[kWIter];
 #pragma unroll
-    for (int k = 0; k < kXIter; ++k) rv[k] = xi[k] >= 0 ? R[xi[k] + j] : T(0);
-  };
+    for (int k = 0; k < kWIter; ++k) {
+      const int e = tid + k * kNetThreads;
+      wv[k] = a.w[e < kNetWeights ? e : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < kWIter; ++k)
+      if (tid + k * kNetThreads < kNetWeights) ws[tid + k * kNetThreads] = wv[k];
+  }
+  lds_barrier();
+  // MFMA A operands (weights): lane holds A[row = l16][k]; k = 8q + i (K = 32), 4q + i (K = 16)
+  uint4_t w1, w2[5];
+  short4_t w3a;
+  {
+    auto pack = [](const uint32_t (&v)[8]) {
+      return uint4_t{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+    };
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int tap = 4 * q + (i >> 1);
+      v[i] = tap < 9 ? ws[kOffW1 + l16 * 18 + (i & 1) * 9 + tap] : 0u;
+    }
+    w1 = pack(v);
+#pragma unroll
+    for (int t = 0; t < 5; ++t) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        v[i] = 2 * t + sel < 9 ? ws[kOffW2 + l16 * 144 + (8 * half + i) * 9 + 2 * t + sel] : 0u;
+      w2[t] = pack(v);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w3a[i] = l16 < 9 ? (short)ws[kOffW3 + (4 * q + i) * 9 + l16] : (short)0;
+    }
+  }
+  // layer-1 B operand: the lane's taps 4q + i, past the last one the zero word
+  int xo[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int tap = 4 * q + i;
+    xo[i] = tap < 9 ? (tap / 3) * kXS + tap % 3 : -1;
+  }
+
+#pragma unroll
+  for (int k = 0; k < kXIter; ++k) gv[k] = xi[k] >= 0 ? d2bf((double)g0[k]) << 16 : 0u;
   auto put_x = [&](int j) {
     const double s = a.colnorm[j] / rn, inv = s > 0.0 ? 1.0 / s : 0.0;
 #pragma unroll
@@ -212,9 +234,20 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
       if (e < kXN) xs[e] = v;
     }
   };
+  // the groups of 16 pixels of a1 and the rows of a2 that are worked on: all of
+  // them, or, in a tile with less than half of its rows on the image, those; the
+  // others' a1 and layer-3 products are zeros (1 x 100000, m = 4: 232 -> 152 us)
+  const int top = y0 < 2 ? 2 - y0 : 0, bottom = rows - y0 + 2 < kA1 ? rows - y0 + 2 : kA1;
+  const bool thin = !INNER && 2 * (bottom - top) < kA1;
+  const int ga = thin ? top * kA1 / 16 : 0, gb = thin ? (bottom * kA1 + 15) / 16 : kA1G;
+  const int pa = thin && top > 1 ? top - 1 : 0, pb = thin && bottom - 1 < kA2 ? bottom - 1 : kA2;
+  if (thin) {
+    const uint4_t zero4 = {0u, 0u, 0u, 0u};
+    for (int e = tid; e < 2 * kA1P; e += kNetThreads) *(uint4_t*)(a1s + 16 * e) = zero4;
+  }
   auto layer1 = [&]() {
 #pragma unroll 5
-    for (int g = wave; g < kA1G; g += kNetWaves) {
+    for (int g = ga + wave; g < gb; g += kNetWaves) {
       const int p = g * 16 + l16, pc = p < kA1N ? p : kA1N - 1;
       const int py = div_px<kA1, kA1P>(pc), px = pc - __mul24(py, kA1);
       const int base = __mul24(py, kXS) + px;
@@ -232,18 +265,28 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
   };
 
   if (tid == 0) xs[kXN] = 0u;
-  load_r(0);
   put_x(0);
   lds_barrier();
+  if (thin)
+    for (int e = tid; e < 9 * kC3P; e += kNetThreads) c3[e] = 0.0f;
   if (m > 1) load_r(1);
   layer1();
   lds_barrier();
 #pragma unroll 1
   for (int j = 0; j < m; ++j) {
+    // R at the output pixels, for r . w: asked for here, used after layer 2
+    T ro[kOIter];
+#pragma unroll
+    for (int k = 0; k < kOIter; ++k) {
+      const int e = tid + k * kNetThreads;
+      const int oy = div_px<kOT, kOIter * kNetThreads>(e), gy = y0 + oy, gx = x0 + e - __mul24(oy, kOT);
+      const bool in = e < kOT * kOT && (INNER || (gy < rows && gx < cols));
+      ro[k] = R[in ? ((int64_t)gy * cols + gx) * m + j : 0];
+    }
     // layer 2 (16 -> 16 channels, two taps per product) and layer 3 as nine
     // per-tap products c3[tap][p] = sum_c W3[c][tap] a2[p][c]
 #pragma unroll 4
-    for (int g = wave; g < kA2G; g += kNetWaves) {
+    for (int g = 2 * pa + wave; g < 2 * pb; g += kNetWaves) {
       const int py = g >> 1, px = (g & 1) * 16 + l16;
       const char* b = a1s + (half * kA1P + py * kA1 + px) * 16;
       const char* b1 = b + sel * 16;              // taps (0, 1), (4, 5), (6, 7)
@@ -288,7 +331,7 @@ __device__ __forceinline__ void net_infer_tile(const NetInferArgs& a, NetInferSh
       for (int tap = 0; tap < 9; ++tap) yv += cp[tap * kC3P + (tap / 3) * kA2 + tap % 3];
       const int64_t i = (int64_t)gy * cols + gx;
       const T wt = (T)(s * (double)yv);
-      const double r = (double)R[i * m + j];
+      const double r = (double)ro[k];
       Z[i * m + j] = wt;
       const double wd = (double)wt;
       v[0] += r * wd;

@@ -515,3 +515,22 @@ def test_precond_apply_tiles(gsf, shape, m, prec_name):
     for j in range(m):
         ref = cn.precond_apply(w.astype(np.float64), R[:, j].reshape(H, W), g.reshape(H, W)).ravel()
         assert nrel(out[:, j], ref) <= NET_TOL, j
+
+
+@pytest.mark.parametrize("rows", [2, 16, 17, 32, 44, 45, 46, 60])
+@pytest.mark.parametrize("cols", [40, 3])
+def test_precond_apply_thin_tiles(gsf, rows, cols):
+    """T(R) where a tile has less than half of its 34 rows on the image, and so
+    works on those alone: one tile of 16 or 17 rows, a second one of 14 to 16
+    (the tolerance of the module docstring, by column)."""
+    rng = np.random.default_rng(60)
+    g = rng.uniform(0.0, 1.0, (rows, cols)).astype(np.float32).astype(np.float64)
+    R = (rng.standard_normal((rows * cols, 3)) * 10.0 ** rng.uniform(-3, 3, 3)).astype(np.float32).astype(np.float64)
+    import torch
+    op = gsf.Operator("bf", (rows, cols), _dev(g.ravel(), torch.float32), 2, 2.0, 0.1, prec=gsf.F32)
+    w = convnet_init(61)
+    T = gsf.Precond(op, _dev(g.ravel(), torch.float32), _bf16_bits(w))
+    out = T.apply(_dev(R, torch.float32)).cpu().numpy()
+    for j in range(3):
+        ref = cn.precond_apply(w.astype(np.float64), R[:, j].reshape(rows, cols), g).ravel()
+        assert nrel(out[:, j], ref) <= NET_TOL, j
