@@ -324,7 +324,11 @@ __global__ void __launch_bounds__(kSmallThreads) cg1d_small_kernel(const T* __re
 template <typename T, int PTS, int RW>
 void launch_cg1d(const Operator& op, const void* x0, void* x_out, int kmax, const CgState& init, CgState* st,
                  hipStream_t s) {
-  const int per = (int)((op.n + PTS - 1) / PTS), threads = (per + 63) / 64 * 64;
+  // as few waves as hold the points; at eight points per thread at least three per
+  // SIMD, whose apply reads weights and neighbours (4097 samples, FP32, 10 steps,
+  // r = 8: 99 us, 109 with nine waves, 102 with sixteen; r = 1 35, 36, 40)
+  constexpr int kLeast = PTS < 8 ? 64 : 768;
+  const int per = (int)((op.n + PTS - 1) / PTS), full = (per + 63) / 64 * 64, threads = full < kLeast ? kLeast : full;
   cg1d_small_kernel<T, PTS, RW><<<1, threads, 0, s>>>((const T*)op.planes, op.pstride, op.ppad, op.desc.radius,
                                                       (const T*)op.diag, (const T*)op.sqd, (const T*)x0,
                                                       (T*)x_out, (int)op.n, kmax, init, st);
