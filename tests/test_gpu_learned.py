@@ -534,3 +534,11 @@ def test_precond_apply_thin_tiles(gsf, rows, cols):
     for j in range(3):
         ref = cn.precond_apply(w.astype(np.float64), R[:, j].reshape(rows, cols), g).ravel()
         assert nrel(out[:, j], ref) <= NET_TOL, j
+
+
+@pytest.mark.parametrize("shape,B", [((2, 70), 2), ((7, 33), 1), ((11, 40), 1), ((12, 40), 1), ((23, 33), 2),
+                                     ((24, 33), 1), ((25, 3), 1)])
+def test_net_training_thin_tiles(gsf, shape, B):
+    """The same where a tile has less than half of its 24 rows of a1 on the image
+    and works on those alone: one tile of 11 or 12 rows, a second one of 7 to 9."""
+    test_net_training_tiles(gsf, shape, B)
