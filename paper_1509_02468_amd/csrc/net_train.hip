@@ -226,11 +226,12 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
     __asm__ volatile("" : "+s"(ops));
     lds_barrier();  // the previous tile's reads of LDS are done
     const int tid = opaque(threadIdx.x);
-    // a tile with less than half of its rows of a1 on the image works on the
-    // groups of 16 pixels that hold them; the others' activations are zeros (a
-    // signal of 100000 samples: gradient 188 us, 303 without, forward 73, 189)
+    // forward only: a tile with less than half of its rows of a1 on the image
+    // works on the groups of 16 pixels that hold them; the others' activations are
+    // zeros (a signal of 100000 samples: 73 us, 189 without; in the training pass
+    // the runtime bounds cost 0.4% of a mini-batch of images)
     const int top = y0 < 4 ? 4 - y0 : 0, bottom = a.rows - y0 + 4 < A1H ? a.rows - y0 + 4 : A1H;
-    const bool thin = 2 * (bottom - top) < A1H;
+    const bool thin = !GRAD && 2 * (bottom - top) < A1H;
     const int ga1 = thin ? top * A1W / 16 : 0, gb1 = thin ? (bottom * A1W + 15) / 16 : A1G;
     const int ga2 = thin && top > 1 ? (top - 1) * A2W / 16 : 0;
     const int gb2 = thin && bottom - 1 < A2H ? ((bottom - 1) * A2W + 15) / 16 : A2G;
@@ -368,7 +369,7 @@ __global__ void __launch_bounds__(kT) net_train_kernel(NetTrainArgs a) {
       const char* ap = a2s + (__mul24(py, A2W) + px) * 16;
       float yv[2] = {0.0f, 0.0f};
       const int gy0 = y0 - 2 + py;
-      const bool rows_off = gy0 + 1 < 0 || gy0 >= a.rows;  // (both; y is not used there)
+      const bool rows_off = !GRAD && (gy0 + 1 < 0 || gy0 >= a.rows);  // (both; y is not used there)
       if (!rows_off) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

@@ -540,5 +540,6 @@ def test_precond_apply_thin_tiles(gsf, rows, cols):
                                      ((24, 33), 1), ((25, 3), 1)])
 def test_net_training_thin_tiles(gsf, shape, B):
     """The same where a tile has less than half of its 24 rows of a1 on the image
-    and works on those alone: one tile of 11 or 12 rows, a second one of 7 to 9."""
+    and the forward pass works on those alone: one tile of 11 or 12 rows, a second
+    one of 7 to 9."""
     test_net_training_tiles(gsf, shape, B)
