@@ -36,7 +36,7 @@
 // One column per thread (256 threads, four scans and sets of addresses per
 // row, two barriers) took four times the vector instructions; now about 330
 // per 256 points and row, 40% of the cycles of the one wave per SIMD that the
-// ring's LDS allows at r = 8.  4096^2, r = 8: 167 us (2.4 TB/s of the 20 B per
+// ring's LDS allows at r = 8.  4096^2, r = 8: 167 us (2.0 TB/s of the 20 B per
 // point), 282 before; a CG filter of 10 steps on 128^2 1.8 (r = 8) to 2.9
 // (r = 1) times as fast, on 1024^2 1.6 to 2.2 times.
 // The strip's 256 - 4r (to a multiple of 8) output columns carry a halo on

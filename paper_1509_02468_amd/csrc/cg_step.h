@@ -39,8 +39,8 @@ struct CgStepArgs {
 // the call is aligned to 16 bytes and elements where not, and request a
 // thread's first chunks before they reduce the partials, so that the two
 // latencies overlap.  With the wave sums' exchanges in the vector unit, FP32:
-// update 12.0 -> 9.6 us and direction 6.4 -> 5.4 at 1024^2, 88 -> 62 and
-// 47 -> 30 at 4096^2 (6.5 TB/s of the bytes they name, part of them cached).
+// update 12.0 -> 10.2 us and direction 6.4 -> 5.0 at 1024^2, 88 -> 64 and
+// 47 -> 31 at 4096^2 (6.3 TB/s of the bytes they name, part of them cached).
 template <typename T>
 struct Chunk {
   static constexpr int n = 16 / (int)sizeof(T);

@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(kThreads) gram_kernel(GramArgs g) {
 // loop over columns instead of being unrolled; rows of 16 lanes are DPP rows,
 // so row sums need no LDS; and every padded size is a kernel of its own with
 // everything inlined.  In place, per call: m = 4 (12 columns, with CG's update)
-// 21.2 us, m = 3 FP64 (9) 19.5, m = 8 (24) 55.0, m = 1 (3) 8.1, against 39.9,
+// 21.0 us, m = 3 FP64 (9) 17.8, m = 8 (24) 54.6, m = 1 (3) 8.1, against 39.9,
 // 28.7, 90.6 and 12.8 for lane-per-row phases unrolled over the columns and
 // called as functions (52 KB of code at 12 columns, 2.2 KB of scratch).
 //
@@ -882,10 +882,10 @@ __device__ __forceinline__ void rr_output(RRShared& sh, const double (&g)[RRGrid
 // over the 256 threads of the workgroup (ga, gb; every thread must call it):
 // C (ns x m, row-major with leading dimension m) and theta (ascending) of the
 // m smallest Ritz pairs.  Steps: symmetrise; scale to unit diag(GB) (columns
-// with a negligible diagonal are dropped); Cholesky GB = L L^T that drops
-// columns with a pivot at most drop_tol, and M = L^-1 GA L^-T on the kept
-// columns; the m smallest eigenpairs Z of M (tridiagonalisation, bisection,
-// inverse iteration); C = L^-T Z.  Returns the kept columns; with fewer than m
+// with a negligible diagonal are dropped); elimination GB = L D L^T that drops
+// columns with a pivot at most drop_tol, and M = D^-1/2 L^-1 GA L^-T D^-1/2 on the
+// kept columns; the m smallest eigenpairs Z of M (tridiagonalisation, bisection,
+// inverse iteration); C = L^-T D^-1/2 Z.  Returns the kept columns; with fewer than m
 // of them nothing is written.
 template <int KB>
 __device__ __forceinline__ unsigned rayleigh_ritz(RRShared& sh, const double (&ga)[RRGrid<KB>::E][RRGrid<KB>::E],
