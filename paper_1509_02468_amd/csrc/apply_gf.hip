@@ -714,8 +714,11 @@ void gf_apply_block(const Operator& op, T* ab, int form, const T* x, int64_t ldx
 // The strips' idle columns cost gf_block_kernel as much as those in use, so the
 // lines lie at parts of the strips in use.  Its time over the other's, r = 2 and
 // 8, 4 to 770 columns, 60 to 120000 rows:
-// - up to 5 rows per workgroup, where latency bounds both: 0.45 to 1.04 at any
-//   width; 7 rows: 0.68 to 1.0 at a quarter or more in use, 0.9 to 1.2 below;
+// - up to 5 rows per workgroup, where latency bounds both: 0.45 to 1.03 at any
+//   width, but for FP64, m = 4, r = 8 where its workgroups (20 rows walked for 4)
+//   are more than the CUs and the other's waves no more than the SIMDs: 1.01 to
+//   1.145 (fewer workgroups 0.70 to 0.89, more waves 0.92 to 1.10, r = 7 0.75 to
+//   0.94); 7 rows: 0.68 to 1.0 at a quarter or more in use, 0.9 to 1.2 below;
 //   10 rows: 0.53 to 1.0 from 0.55 on, up to 1.1 at 0.5, 1.4 at 0.03;
 // - more rows, FP32, m = 4: one strip 0.76 to 1.01 from 0.7 on and up to 1.36 at
 //   0.5, several 0.71 to 1.05 from 0.78 on and up to 1.5 at 0.5;
@@ -733,7 +736,12 @@ bool gf_block_pays(const Operator& op, int m) {
   const bool f64 = sizeof(T) == 8;
   if (op.desc.ndim == 1) return op.n >= 65536 || (f64 && m == 8);
   const GfBlkGrid g = gf_block_grid(op);
-  if (g.rb <= 5) return true;
+  if (g.rb <= 5) {
+    if (!f64 || m != 4 || op.desc.radius != 8) return true;
+    const dim3 box = gf_grid<GfCpl<4>::v>(op, gf_geom<GfCpl<4>::v>(op));
+    const int64_t groups = (int64_t)g.strips * ((op.rows + g.rb - 1) / g.rb), waves = (int64_t)box.x * box.y;
+    return groups <= 256 || waves > 1024;
+  }
   const bool one = g.strips == 1;
   double least;
   if (m == 8) least = f64 ? 0.25 : (one ? 0.5 : 0.66);

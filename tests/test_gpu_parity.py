@@ -683,6 +683,13 @@ def test_gf_block_renewed_sums(gsf, rows, radius, prec):
         assert (y[:, c:c + 2] - ref).abs().max() <= (1e-13 if prec else 1e-6) * ref.abs().max()
 
 
+@pytest.mark.parametrize("shape", [(204, 1024), (208, 1024), (512, 512), (624, 624), (632, 624), (640, 720)])
+def test_gf_block_small_grids_f64(gsf, shape):
+    """Blocks of 4 FP64 columns at r = 8 where the choice between the kernels lies
+    at 256 workgroups of the one and 1024 waves of the other, on both sides."""
+    test_gf_block_strips(gsf, shape, 8, 4, gsf.F64)
+
+
 @pytest.mark.parametrize("prec,m", [(0, 4), (0, 8), (1, 4), (1, 8)])
 @pytest.mark.parametrize("shape,radius", [((2560, 31), 8), ((2561, 31), 8), ((5200, 60), 8), ((5200, 59), 8),
                                           ((5200, 136), 8), ((5200, 164), 8), ((5200, 193), 8), ((2600, 300), 2),
