@@ -577,18 +577,17 @@ __device__ __forceinline__ void rr_tridiagonalize(RRShared& sh, double (&a)[RRGr
     double kc = 0.0;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      pr[i] *= beta;
-      pc[i] = cin[i] ? beta * sh.pv[ci[i]] : 0.0;
+      pc[i] = cin[i] ? sh.pv[ci[i]] : 0.0;
       kc = fma(vc[i], pc[i], kc);
     }
-    // M - v w^T - w v^T with w = p - (beta / 2) (v^T p) v, p = beta M v (beta^2
-    // overflows for a coupling below 1e-77)
-    kc = 0.5 * beta * row_sum(kc);
+    // M - v w^T - w v^T with w = beta M v - (beta^2 / 2) (v^T M v) v, one beta
+    // after the other (their square overflows for a coupling below 1e-77)
+    kc = 0.5 * beta * (beta * row_sum(kc));
 #pragma unroll
     for (int i = 0; i < E; ++i)
 #pragma unroll
       for (int q = 0; q < E; ++q) {
-        const double wr = fma(-kc, vr[i], pr[i]), wc = fma(-kc, vc[q], pc[q]);
+        const double wr = fma(-kc, vr[i], beta * pr[i]), wc = fma(-kc, vc[q], beta * pc[q]);
         a[i][q] = fma(-vr[i], wc, fma(-wr, vc[q], a[i][q]));
       }
   }
